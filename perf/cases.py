@@ -354,3 +354,43 @@ def tolerance(case):
     if case["path"] in ("train", "train_opts", "forward"):
         return {"rel": 1e-6, "max": 1e-4}
     return "exact"
+
+
+def exact(case, seed):
+    """What ``run`` gives for the same inputs, in fp64 with plain torch, for the paths that compute numbers."""
+    if case["path"] not in ("forward", "train", "train_opts"):
+        return None  # counted, classified or copied: tolerance() asks for the same values
+    st = prepare(case, seed)
+    weights = [t.double() for t in st["hp"].hotW]
+    mean, adagrad = case.get("pooling") == "mean", case.get("optimizer") == "adagrad"
+    state = [t.double() for t in st["state"]] if "state" in st else []
+    lr, eps = float(np.float32(LR)), float(np.float32(1e-8))
+    outs = []
+    for k, hb in enumerate(st["hbs"]):
+        pooled = torch.zeros(st["outs"][k].shape, dtype=torch.float64, device="cuda")
+        bags = []
+        for z, w in enumerate(weights):
+            slots, lengths = hb.slots[z].long(), torch.ones(hb.n_samples, dtype=torch.int64, device="cuda")
+            if hb.offsets[z] is not None:
+                lengths = hb.offsets[z].diff().long()
+            samples = torch.repeat_interleave(torch.arange(hb.n_samples, device="cuda"), lengths)
+            scale = 1.0 / lengths.clamp(min=1).double() if mean else torch.ones_like(lengths, dtype=torch.float64)
+            bags.append((slots, samples, scale))
+            for a in range(0, slots.numel(), 1 << 20):
+                pooled[:, z].index_add_(0, samples[a:a + (1 << 20)], w[slots[a:a + (1 << 20)]])
+            pooled[:, z] *= scale[:, None]
+        outs.append(pooled)
+        if case["path"] == "forward":
+            return pooled
+        for z, (slots, samples, scale) in enumerate(bags):
+            up = st["gouts"][k][:, z].double() * scale[:, None]
+            grad = torch.zeros_like(weights[z])
+            for a in range(0, slots.numel(), 1 << 20):
+                grad.index_add_(0, slots[a:a + (1 << 20)], up[samples[a:a + (1 << 20)]])
+            if adagrad:
+                state[z] += grad.square().mean(dim=1)
+                grad /= (state[z].sqrt() + eps)[:, None]  # a row that no lookup names has a gradient of zero
+            weights[z] -= lr * grad
+    if case["path"] == "train":
+        return {"out": outs, "weights": weights}
+    return {"out": outs[0], "weights": weights, "state": state}
