@@ -489,7 +489,7 @@ def committed_traffic(cfg_id, kernel):
         return None
 
 
-KERNEL_CLASS = {"fwd_onehot_kernel": "fwd", "fwd_wave_kernel": "fwd", "fwd_group_kernel": "fwd",
+KERNEL_CLASS = {"fwd_onehot_kernel": "fwd", "fwd_kernel": "fwd",
                 "bwd_reduce_kernel": "bwd_reduce", "bwd_reduce_walk_kernel": "bwd_reduce", "bwd_fixup_kernel": "bwd_fixup",
                 "lds_sort_kernel": "lds_sort", "sort_scatter_kernel": "sort_scatter", "sort_hist_kernel": "sort_hist",
                 "sort_colscan_kernel": "sort_colscan", "bwd_keys_kernel": "bwd_keys", "fae_copy_probe_kernel": "copy_probe",

@@ -720,7 +720,7 @@ template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS) void 
         const int b = blockIdx.x - a.n_sort_blocks;
         const int z = b / a.fwd_blocks_per_table, bl = b % a.fwd_blocks_per_table;
         const int64_t s0 = ((int64_t)bl * LSORT_WAVES + threadIdx.x / FAE_WAVE) * FAE_WAVE;
-        fwd_onehot_wave<V, LPR>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, a.n_samples, a.out + (int64_t)z * a.dim,
+        fwd_onehot_wave<V, LPR, 16>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, a.n_samples, a.out + (int64_t)z * a.dim,
                                 a.out_stride, a.dim, a.status, a.stream_out != 0);
     }
 }

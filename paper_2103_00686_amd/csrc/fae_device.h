@@ -78,16 +78,16 @@ __device__ __forceinline__ void fwd_store(float *p, const float &v, bool stream)
 
 // One-hot tables (one lookup per sample): a wave takes 64 consecutive samples starting at s0,
 // reads their 64 slots with one coalesced load and then copies rows, 64/LPR rows per step, with
-// the loads of up to 16 steps in flight before the first store.  obase points at the table's
+// the loads of up to UNMAX steps in flight before the first store.  obase points at the table's
 // first output column of sample 0.
-template <typename V, int LPR>
+template <typename V, int LPR, int UNMAX>
 __device__ __forceinline__ void fwd_onehot_wave(const V *W, const int32_t *slots, int n_hot, int64_t s0, int n_samples,
                                                 float *obase, int64_t out_stride, int dim, uint32_t *status,
                                                 bool stream_out)
 {
     constexpr int G = FAE_WAVE / LPR;
     constexpr int STEPS = FAE_WAVE / G;
-    constexpr int UN = STEPS < 16 ? STEPS : 16;
+    constexpr int UN = STEPS < UNMAX ? STEPS : UNMAX;
     const int lane = fae_lane(), g = lane / LPR, l = lane % LPR;
     if (s0 >= n_samples)
         return;
@@ -103,7 +103,7 @@ __device__ __forceinline__ void fwd_onehot_wave(const V *W, const int32_t *slots
     for (int c0 = 0; c0 < ncols; c0 += LPR) {
         const int c = c0 + l;
         const bool active = c < ncols;
-#pragma unroll
+#pragma unroll 1
         for (int i0 = 0; i0 < STEPS; i0 += UN) {
             V v[UN];
 #pragma unroll

@@ -1,6 +1,6 @@
 // Hot mini-batch forward: row gather + sum pooling over HBM-resident hot tables.
 //
-// One launch covers every table of the batch.  Two lane mappings:
+// One launch covers every table of the batch; each table has the lane mapping of its bags:
 //   group-per-bag : LPR adjacent lanes own one bag, each lane one 16-byte column
 //                   slice; bags of a wave sit side by side (best for one-hot / short bags);
 //   wave-per-bag  : the 64/LPR lane groups of a wave take alternate entries of one
@@ -11,6 +11,8 @@
 #include "fae_internal.h"
 #include "fae_device.h"
 
+enum { FWD_ONEHOT, FWD_GROUP, FWD_WAVE };
+
 struct FwdArgs {
     const float *W[FAE_MAX_TABLES];
     const int32_t *slots[FAE_MAX_TABLES];
@@ -18,6 +20,7 @@ struct FwdArgs {
     int32_t n_hot[FAE_MAX_TABLES];
     int32_t n_lookups[FAE_MAX_TABLES];
     int32_t blk_start[FAE_MAX_TABLES + 1];
+    int32_t kind[FAE_MAX_TABLES]; // FWD_ONEHOT, FWD_GROUP or FWD_WAVE
     int32_t n_tables;
     int32_t dim;
     int32_t n_samples;
@@ -28,70 +31,79 @@ struct FwdArgs {
     int32_t mean;       // divide the pooled sum by the bag's length (bags of one lookup are unaffected)
 };
 
-// one row slice, or zero (and a status flag) when the slot is out of range
-template <typename V>
-__device__ __forceinline__ V fwd_load(const V *W, int slot, int n_hot, int ncols, int c, uint32_t *status)
-{
-    if ((unsigned)slot >= (unsigned)n_hot) {
-        fae_flag(status, FAE_STATUS_ERANGE);
-        return vec_ops<V>::zero();
-    }
-    return W[(int64_t)slot * ncols + c];
-}
-
-// Sum of the rows of lookups j0, j0 + step, ... below end (column slice c), four loads in flight.
-// Up to FWD_PLAIN_MAX terms are added one after the other (worst case FWD_PLAIN_MAX * 2^-24 of
-// the sum of their magnitudes, inside the 1e-5 the result is held to); longer sums carry the
+// Sums of up to FWD_PLAIN_MAX terms are added one after the other (worst case FWD_PLAIN_MAX * 2^-24
+// of the sum of their magnitudes, inside the 1e-5 the result is held to); longer sums carry the
 // rounding error along (COMP), so that a bag of thousands of lookups stays as accurate as a short
 // one, also when it adds one popular row over and over, which otherwise drifts one way.
 #define FWD_PLAIN_MAX 128
-template <typename V, bool COMP>
-__device__ __forceinline__ V fwd_sum(const V *W, const int32_t *slots, int j0, int end, int step, int n_hot, int ncols, int c,
-                                     uint32_t *status)
+
+// Adds rows of a bag whose next WIDTH slots are held one per lane by the lanes of a lane group of
+// WIDTH lanes: this group's rows are numbers first, first + STRIDE, ... below count.  UN rows are in
+// flight; the slots are already there, so a row costs one round trip and not two in a row.
+template <typename V, int WIDTH, int STRIDE, int UN, bool COMP>
+__device__ __forceinline__ void fwd_add_rows(V &acc, V &lost, const V *W, int slot, int first, int count, int ncols, int c, bool active)
 {
-    V acc = vec_ops<V>::zero(), lost = vec_ops<V>::zero();
-    int j = j0;
-    for (; j + 3 * step < end; j += 4 * step) {
-        const int s0 = slots[j], s1 = slots[j + step], s2 = slots[j + 2 * step], s3 = slots[j + 3 * step];
-        const V v0 = fwd_load(W, s0, n_hot, ncols, c, status);
-        const V v1 = fwd_load(W, s1, n_hot, ncols, c, status);
-        const V v2 = fwd_load(W, s2, n_hot, ncols, c, status);
-        const V v3 = fwd_load(W, s3, n_hot, ncols, c, status);
-        if (COMP) {
-            vec_ops<V>::add_comp(acc, lost, v0);
-            vec_ops<V>::add_comp(acc, lost, v1);
-            vec_ops<V>::add_comp(acc, lost, v2);
-            vec_ops<V>::add_comp(acc, lost, v3);
-        } else {
-            vec_ops<V>::add(acc, v0);
-            vec_ops<V>::add(acc, v1);
-            vec_ops<V>::add(acc, v2);
-            vec_ops<V>::add(acc, v3);
+    for (int j = first; j - first < count; j += STRIDE * UN) { // every lane of the WIDTH stays in: they hold the slots
+        V v[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int e = j + u * STRIDE;
+            const int sl = __shfl(slot, e, WIDTH); // e wraps inside the group past its end: not used then
+            v[u] = (active && e < count && sl >= 0) ? W[(int64_t)sl * ncols + c] : vec_ops<V>::zero();
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            if (COMP)
+                vec_ops<V>::add_comp(acc, lost, v[u]);
+            else
+                vec_ops<V>::add(acc, v[u]);
         }
     }
-    for (; j < end; j += step) {
-        const V v = fwd_load(W, slots[j], n_hot, ncols, c, status);
-        if (COMP)
-            vec_ops<V>::add_comp(acc, lost, v);
-        else
-            vec_ops<V>::add(acc, v);
-    }
-    return acc;
 }
 
-template <typename V, int LPR> __global__ __launch_bounds__(256) void fwd_group_kernel(FwdArgs a)
+// the lane's slot of a chunk (-1: past the end, or out of range and flagged)
+__device__ __forceinline__ int fwd_slot(const int32_t *slots, int j, int end, int n_hot, uint32_t *status)
 {
-    constexpr int GPB = 256 / LPR;
+    int sl = j < end ? slots[j] : -1;
+    if (j < end && (unsigned)sl >= (unsigned)n_hot) {
+        fae_flag(status, FAE_STATUS_ERANGE);
+        sl = -1;
+    }
+    return sl;
+}
+
+// One launch for every table; the workgroup's table says which mapping (a.kind):
+//   one-hot   256 samples per workgroup, 64 per wave;
+//   group     LPR lanes own a bag, 256 / LPR bags per workgroup: short bags;
+//   wave      a wave owns a bag, its 64 / LPR lane groups take alternate rows: long bags.
+// What bounds it: rows that miss the L2 (large tables), else the chain offsets -> slots -> rows of a
+// bag.  So the slots of a bag (64 of them, or LPR for a lane group) come with one load and are handed
+// out by lane shuffles, and a row costs one round trip instead of two in a row, with 8 (4) rows per
+// group in flight; the mapping goes by each table's own bags, and all tables share the launch:
+//   8 x 65 536 bags of about 20, dim 128: 650 -> 521 us (10.3 TB/s of rows out of L2 and beyond)
+//   3 tables with bags of up to 100 and a one-hot one, 6007 samples, dim 100: 9 + 28.7 -> 27.2 us
+//   3 tables of short bags and 2 one-hot ones, 3001 samples, dim 20: 4.7 + 11.9 -> 9.1 us
+template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_kernel(FwdArgs a)
+{
     const int z = fae_find_table(a.blk_start, a.n_tables, blockIdx.x);
     const int bl = blockIdx.x - a.blk_start[z];
-    const int g = threadIdx.x / LPR, l = threadIdx.x % LPR;
-    const int64_t s = (int64_t)bl * GPB + g;
-    if (s >= a.n_samples)
+    const int kind = a.kind[z];
+    if (kind == FWD_ONEHOT) {
+        const int64_t s0 = ((int64_t)bl * (256 / FAE_WAVE) + threadIdx.x / FAE_WAVE) * FAE_WAVE;
+        fwd_onehot_wave<V, LPR, (LPR < 32 ? 8 : 4)>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, a.n_samples, a.out + (int64_t)z * a.dim,
+                                a.out_stride, a.dim, a.status, a.stream_out != 0);
         return;
+    }
+    constexpr int G = FAE_WAVE / LPR; // lane groups per wave
+    const int lane = fae_lane(), g = lane / LPR, l = lane % LPR;
+    const bool wave = kind == FWD_WAVE;
+    const int64_t s = wave ? (int64_t)bl * (256 / FAE_WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x / FAE_WAVE)
+                           : (int64_t)bl * (256 / LPR) + threadIdx.x / LPR;
+    const bool in = s < a.n_samples;
     const int32_t *off = a.offsets[z];
     const int32_t *slots = a.slots[z];
-    int beg = off ? off[s] : (int)s;
-    int end = off ? off[s + 1] : (int)s + 1;
+    int beg = in ? (off ? off[s] : (int)s) : 0;
+    int end = in ? (off ? off[s + 1] : (int)s + 1) : 0;
     if (beg < 0 || end > a.n_lookups[z] || beg > end) { // malformed CSR: never dereferenced
         fae_flag(a.status, FAE_STATUS_ERANGE);
         end = beg = 0;
@@ -100,86 +112,78 @@ template <typename V, int LPR> __global__ __launch_bounds__(256) void fwd_group_
     const V *W = (const V *)a.W[z];
     const int n_hot = a.n_hot[z];
     V *o = (V *)(a.out + s * a.out_stride + (int64_t)z * a.dim);
-    for (int c = l; c < ncols; c += LPR) {
-        const V acc = end - beg > FWD_PLAIN_MAX ? fwd_sum<V, true>(W, slots, beg, end, 1, n_hot, ncols, c, a.status)
-                                                : fwd_sum<V, false>(W, slots, beg, end, 1, n_hot, ncols, c, a.status);
-        V res = acc;
-        if (a.mean && end - beg > 1)
-            vec_ops<V>::scale(res, 1.0f / (float)(end - beg));
-        o[c] = res;
+    if (wave) {
+        if (!in)
+            return;
+        for (int c0 = 0; c0 < ncols; c0 += LPR) {
+            const int c = c0 + l;
+            V acc = vec_ops<V>::zero(), lost = vec_ops<V>::zero();
+            for (int j0 = beg; j0 < end; j0 += FAE_WAVE) {
+                const int slot = fwd_slot(slots, j0 + lane, end, n_hot, a.status);
+                const int count = end - j0 < FAE_WAVE ? end - j0 : FAE_WAVE;
+                if (end - beg > FWD_PLAIN_MAX * G) // the same for the whole wave
+                    fwd_add_rows<V, FAE_WAVE, G, 4, true>(acc, lost, W, slot, g, count, ncols, c, c < ncols);
+                else
+                    fwd_add_rows<V, FAE_WAVE, G, (G <= 2 ? 8 : 4), false>(acc, lost, W, slot, g, count, ncols, c, c < ncols);
+            }
+            // combine the lane groups (all 64 lanes take part in the shuffles)
+#pragma unroll
+            for (int m = LPR; m < FAE_WAVE; m <<= 1)
+                vec_ops<V>::add(acc, vec_ops<V>::shfl_xor(acc, m));
+            if (a.mean && end - beg > 1)
+                vec_ops<V>::scale(acc, 1.0f / (float)(end - beg));
+            if (g == 0 && c < ncols)
+                o[c] = acc;
+        }
+    } else {
+        for (int c0 = 0; c0 < ncols; c0 += LPR) {
+            const int c = c0 + l;
+            V acc = vec_ops<V>::zero(), lost = vec_ops<V>::zero();
+            for (int j0 = beg; j0 < end; j0 += LPR) { // a lane group leaves as a whole
+                const int slot = fwd_slot(slots, j0 + l, end, n_hot, a.status);
+                const int count = end - j0 < LPR ? end - j0 : LPR;
+                if (end - beg > FWD_PLAIN_MAX)
+                    fwd_add_rows<V, LPR, 1, (LPR < 4 ? LPR : 4), true>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
+                else
+                    fwd_add_rows<V, LPR, 1, (LPR < 4 ? LPR : 4), false>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
+            }
+            if (a.mean && end - beg > 1)
+                vec_ops<V>::scale(acc, 1.0f / (float)(end - beg));
+            if (in && c < ncols)
+                o[c] = acc;
+        }
     }
 }
 
-// One-hot tables: 256 samples per workgroup, 64 per wave.
+// Every table one-hot: no bag code beside it, so sixteen rows fit in flight per lane group (26 tables of
+// 50 001 samples, dim 64: 68.5 us, against 77.0 us for fwd_kernel with its eight).
 template <typename V, int LPR> __global__ __launch_bounds__(256) void fwd_onehot_kernel(FwdArgs a)
 {
     const int z = fae_find_table(a.blk_start, a.n_tables, blockIdx.x);
     const int bl = blockIdx.x - a.blk_start[z];
     const int64_t s0 = ((int64_t)bl * (256 / FAE_WAVE) + threadIdx.x / FAE_WAVE) * FAE_WAVE;
-    fwd_onehot_wave<V, LPR>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, a.n_samples, a.out + (int64_t)z * a.dim,
-                            a.out_stride, a.dim, a.status, a.stream_out != 0);
+    fwd_onehot_wave<V, LPR, 16>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, a.n_samples, a.out + (int64_t)z * a.dim,
+                                a.out_stride, a.dim, a.status, a.stream_out != 0);
 }
 
-template <typename V, int LPR> __global__ __launch_bounds__(256) void fwd_wave_kernel(FwdArgs a)
+template <typename V, int LPR> static void fwd_launch(fae_ctx *ctx, const FwdArgs &a, bool bags, int blocks)
 {
-    constexpr int G = FAE_WAVE / LPR; // lane groups per wave
-    constexpr int WPB = 256 / FAE_WAVE;
-    const int z = fae_find_table(a.blk_start, a.n_tables, blockIdx.x);
-    const int bl = blockIdx.x - a.blk_start[z];
-    const int w = threadIdx.x / FAE_WAVE, lane = threadIdx.x % FAE_WAVE;
-    const int g = lane / LPR, l = lane % LPR;
-    const int64_t s = (int64_t)bl * WPB + w;
-    if (s >= a.n_samples)
-        return;
-    const int32_t *off = a.offsets[z];
-    const int32_t *slots = a.slots[z];
-    int beg = off ? off[s] : (int)s;
-    int end = off ? off[s + 1] : (int)s + 1;
-    if (beg < 0 || end > a.n_lookups[z] || beg > end) { // malformed CSR: never dereferenced
-        fae_flag(a.status, FAE_STATUS_ERANGE);
-        end = beg = 0;
-    }
-    const int ncols = a.dim / (int)(sizeof(V) / sizeof(float));
-    const V *W = (const V *)a.W[z];
-    const int n_hot = a.n_hot[z];
-    V *o = (V *)(a.out + s * a.out_stride + (int64_t)z * a.dim);
-    for (int c0 = 0; c0 < ncols; c0 += LPR) {
-        const int c = c0 + l;
-        V acc = vec_ops<V>::zero();
-        if (c < ncols) // every group sums every G-th lookup of the bag (the bag's length is the same for the whole wave)
-            acc = end - beg > FWD_PLAIN_MAX * G ? fwd_sum<V, true>(W, slots, beg + g, end, G, n_hot, ncols, c, a.status)
-                                                : fwd_sum<V, false>(W, slots, beg + g, end, G, n_hot, ncols, c, a.status);
-        // combine the lane groups (all 64 lanes take part in the shuffles)
-#pragma unroll
-        for (int m = LPR; m < FAE_WAVE; m <<= 1)
-            vec_ops<V>::add(acc, vec_ops<V>::shfl_xor(acc, m));
-        if (a.mean && end - beg > 1)
-            vec_ops<V>::scale(acc, 1.0f / (float)(end - beg));
-        if (g == 0 && c < ncols)
-            o[c] = acc;
-    }
-}
-
-template <typename V, int LPR> static void fwd_launch(fae_ctx *ctx, const FwdArgs &a, int kind, int total_blocks)
-{
-    if (kind == 2)
-        FAE_LAUNCH(ctx, (fwd_onehot_kernel<V, LPR>), dim3(total_blocks), dim3(256), 0, ctx->stream, a);
-    else if (kind == 1)
-        FAE_LAUNCH(ctx, (fwd_wave_kernel<V, LPR>), dim3(total_blocks), dim3(256), 0, ctx->stream, a);
+    if (bags)
+        FAE_LAUNCH(ctx, (fwd_kernel<V, LPR>), dim3(blocks), dim3(256), 0, ctx->stream, a);
     else
-        FAE_LAUNCH(ctx, (fwd_group_kernel<V, LPR>), dim3(total_blocks), dim3(256), 0, ctx->stream, a);
+        FAE_LAUNCH(ctx, (fwd_onehot_kernel<V, LPR>), dim3(blocks), dim3(256), 0, ctx->stream, a);
 }
 
-template <typename V> static void fwd_dispatch(fae_ctx *ctx, const FwdArgs &a, int lpr, int kind, int total_blocks)
+template <typename V> static void fwd_dispatch(fae_ctx *ctx, const FwdArgs &a, int lpr, bool bags, int blocks)
 {
     switch (lpr) {
-    case 1: fwd_launch<V, 1>(ctx, a, kind, total_blocks); break;
-    case 2: fwd_launch<V, 2>(ctx, a, kind, total_blocks); break;
-    case 4: fwd_launch<V, 4>(ctx, a, kind, total_blocks); break;
-    case 8: fwd_launch<V, 8>(ctx, a, kind, total_blocks); break;
-    case 16: fwd_launch<V, 16>(ctx, a, kind, total_blocks); break;
-    case 32: fwd_launch<V, 32>(ctx, a, kind, total_blocks); break;
-    default: fwd_launch<V, 64>(ctx, a, kind, total_blocks); break;
+    case 1: fwd_launch<V, 1>(ctx, a, bags, blocks); break;
+    case 2: fwd_launch<V, 2>(ctx, a, bags, blocks); break;
+    case 4: fwd_launch<V, 4>(ctx, a, bags, blocks); break;
+    case 8: fwd_launch<V, 8>(ctx, a, bags, blocks); break;
+    case 16: fwd_launch<V, 16>(ctx, a, bags, blocks); break;
+    case 32: fwd_launch<V, 32>(ctx, a, bags, blocks); break;
+    default: fwd_launch<V, 64>(ctx, a, bags, blocks); break;
     }
 }
 
@@ -249,62 +253,33 @@ static int32_t fwd_impl(fae_ctx *ctx, const fae_tables *hot_tables, const float 
     a.status = ctx->d_block;
     a.stream_out = ctx->opt_fwd_stream != 0;
     a.mean = pooling == FAE_POOL_MEAN;
-    // one-hot tables: 256 samples per workgroup
-    if (ctx->opt_fwd == 0) {
-        const int64_t per_table = (S + 255) / 256;
-        int64_t blocks = 0;
-        for (int z = 0; z < nt; ++z) {
-            a.blk_start[z] = (int32_t)blocks;
-            if (!a.offsets[z])
-                blocks += per_table;
-        }
-        a.blk_start[nt] = (int32_t)blocks;
-        if (blocks >= 2147483647LL)
-            return fae_fail(ctx, FAE_EINVAL, "fae_embbag_fwd: batch too large for one launch");
-        if (blocks > 0) {
-            fae_ktimer kt(ctx, FAE_K_FWD);
-            if (vec)
-                fwd_dispatch<float4>(ctx, a, lpr, 2, (int)blocks);
-            else
-                fwd_dispatch<float>(ctx, a, lpr, 2, (int)blocks);
-            FAE_LAUNCH_CHECK(ctx);
-        }
-    }
-    // tables with offsets (and every table when a lane mapping is forced)
-    {
-        int64_t csr_lookups = 0;
-        int n_csr = 0;
-        for (int z = 0; z < nt; ++z)
-            if (a.offsets[z] || ctx->opt_fwd != 0) {
-                csr_lookups += hot_batch->h_n_lookups[z];
-                ++n_csr;
-            }
-        if (n_csr > 0) {
-            // wave-per-bag pays once a bag keeps every lane group of the wave busy for a few rounds
-            const double avg_len = (double)csr_lookups / ((double)S * n_csr);
-            bool wave = groups > 1 && avg_len >= 2.0 * groups;
+    int64_t blocks = 0;
+    bool bags = false;
+    for (int z = 0; z < nt; ++z) {
+        int64_t per_block = 256; // one-hot: 256 samples per workgroup
+        a.kind[z] = FWD_ONEHOT;
+        if (a.offsets[z] || ctx->opt_fwd != 0) {
+            // wave-per-bag pays once a bag keeps every lane group of the wave busy for two rounds
+            bool wave = groups > 1 && (double)hot_batch->h_n_lookups[z] >= 2.0 * groups * (double)S;
             if (ctx->opt_fwd == 1)
                 wave = false;
             if (ctx->opt_fwd == 2)
                 wave = groups > 1;
-            const int bags_per_block = wave ? 4 : 256 / lpr;
-            const int64_t per_table = (S + bags_per_block - 1) / bags_per_block;
-            int64_t blocks = 0;
-            for (int z = 0; z < nt; ++z) {
-                a.blk_start[z] = (int32_t)blocks;
-                if (a.offsets[z] || ctx->opt_fwd != 0)
-                    blocks += per_table;
-            }
-            a.blk_start[nt] = (int32_t)blocks;
-            if (blocks >= 2147483647LL)
-                return fae_fail(ctx, FAE_EINVAL, "fae_embbag_fwd: batch too large for one launch");
-            fae_ktimer kt(ctx, FAE_K_FWD);
-            if (vec)
-                fwd_dispatch<float4>(ctx, a, lpr, wave ? 1 : 0, (int)blocks);
-            else
-                fwd_dispatch<float>(ctx, a, lpr, wave ? 1 : 0, (int)blocks);
-            FAE_LAUNCH_CHECK(ctx);
+            a.kind[z] = wave ? FWD_WAVE : FWD_GROUP;
+            bags = true;
+            per_block = wave ? 256 / FAE_WAVE : 256 / lpr;
         }
+        a.blk_start[z] = (int32_t)blocks;
+        blocks += (S + per_block - 1) / per_block;
+        if (blocks >= 2147483647LL)
+            return fae_fail(ctx, FAE_EINVAL, "fae_embbag_fwd: batch too large for one launch");
     }
+    a.blk_start[nt] = (int32_t)blocks;
+    fae_ktimer kt(ctx, FAE_K_FWD);
+    if (vec)
+        fwd_dispatch<float4>(ctx, a, lpr, bags, (int)blocks);
+    else
+        fwd_dispatch<float>(ctx, a, lpr, bags, (int)blocks);
+    FAE_LAUNCH_CHECK(ctx);
     return FAE_OK;
 }

@@ -1,0 +1,45 @@
+"""Forward over bags whose lengths sit at the edges of what one load of slots covers (a lane group's
+lanes, a wave's 64) and of the plain sum (128 lookups per lane group), mixed with one-hot tables in
+one launch, against fp64."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2103_00686_amd import binding as B
+from paper_2103_00686_amd.hotpath import HotBatch, HotPath
+
+pytestmark = pytest.mark.gpu
+
+SHORT = [0, 1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17]
+LONG = [0, 1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 257, 300]
+
+
+@pytest.mark.parametrize("pooling", [B.FAE_POOL_SUM, B.FAE_POOL_MEAN])
+@pytest.mark.parametrize("dim", [2, 3, 4, 8, 20, 50, 64, 100, 128, 260])
+def test_bag_lengths_at_the_edges(dim, pooling):
+    rng = np.random.default_rng(dim)
+    rows, S = [700, 90, 50, 33], 77
+    lengths = [rng.permutation(np.resize(LONG, S)), rng.permutation(np.resize(SHORT, S)), None, rng.permutation(np.resize(LONG + SHORT, S))]
+    slots, offs, nl = [], [], []
+    for r, ln in zip(rows, lengths):
+        n = S if ln is None else int(ln.sum())
+        slots.append(torch.from_numpy(rng.integers(0, r, n, dtype=np.int32)).cuda())
+        offs.append(None if ln is None else torch.from_numpy(np.concatenate([[0], np.cumsum(ln)]).astype(np.int32)).cuda())
+        nl.append(n)
+    hp = HotPath(rows, dim)
+    hp.alloc_counts()
+    hp.build([0] * len(rows), rows, seed=3)
+    out = torch.full((S, len(rows), dim), float("nan"), device="cuda")
+    hp.forward(HotBatch(S, slots, offs, nl), out, pooling)
+    hp.sync()
+    for z, ln in enumerate(lengths):
+        ln = np.ones(S, dtype=np.int64) if ln is None else ln.astype(np.int64)
+        w = hp.hotW[z].double()[slots[z].long()]
+        seg = torch.from_numpy(np.repeat(np.arange(S), ln)).cuda()
+        ref = torch.zeros((S, dim), dtype=torch.float64, device="cuda").index_add_(0, seg, w)
+        mag = torch.zeros((S, dim), dtype=torch.float64, device="cuda").index_add_(0, seg, w.abs())
+        if pooling == B.FAE_POOL_MEAN:
+            scale = torch.from_numpy(1.0 / np.maximum(ln, 1)).cuda()[:, None]
+            ref, mag = ref * scale, mag * scale
+        # at most 128 plain additions in a row, six more across lane groups and the scaling: 136 * 2^-24
+        assert bool(((out[:, z].double() - ref).abs() <= 136 * 2.0 ** -24 * mag).all()), f"table {z}"
