@@ -234,12 +234,13 @@ __device__ __forceinline__ void fae_flag(uint32_t *status, uint32_t bit)
 // round for up to eight tables):
 // a search that walks up to the owner is a chain of dependent loads as long as the table's
 // number, which the workgroups of the last tables pay in full before their first useful load.
-__device__ __forceinline__ int fae_find_table(const int32_t *blk_start, int nt, int b)
+template <typename I, typename J> __device__ __forceinline__ int fae_find_table(const I *blk_start, int nt, J block)
 {
     static_assert(FAE_MAX_TABLES == 64, "two levels of eight");
     if (nt <= 1)
         return 0;
-    int v[8]; // every load of a round is issued whatever the others return (the array has an entry for every index)
+    const I b = (I)block;
+    I v[8]; // every load of a round is issued whatever the others return (the array has an entry for every index)
     int base = 0;
     if (nt > 8) {
 #pragma unroll
@@ -257,6 +258,12 @@ __device__ __forceinline__ int fae_find_table(const int32_t *blk_start, int nt, 
     for (int i = 1; i < 8; ++i)
         z += ((base + i < nt) & (b >= v[i])) ? 1 : 0;
     return z;
+}
+
+// a / b for a >= 0: a 32-bit division where the numbers allow it
+__device__ __forceinline__ int64_t fae_div_small(int64_t a, uint32_t b)
+{
+    return a <= 0xffffffffLL ? (int64_t)((uint32_t)a / b) : (int64_t)((uint64_t)a / b);
 }
 
 // raw row id j of an index array that holds int32 or int64 values; -1 if it is outside [0, rows)
