@@ -3,24 +3,50 @@
 // stays capturable in a HIP graph).
 #include "fae_internal.h"
 
+// Sixteen entries per thread and round: a round is one load, two barriers and one store one after
+// the other, so the time goes by the rounds (30 000 entries: 18.6 us with four per thread, 8.4 us).
 __global__ __launch_bounds__(1024) void fae_scan_kernel(int32_t *data, int64_t n)
 {
+    constexpr int PER = 16;
     __shared__ int lds[1024 / FAE_WAVE + 1];
+    const bool aligned = (((uintptr_t)data) & 15) == 0;
     int carry = 0;
-    for (int64_t base = 0; base < n; base += 4096) {
-        const int64_t i0 = base + (int64_t)threadIdx.x * 4;
-        int v[4];
+    for (int64_t base = 0; base < n; base += 1024 * PER) {
+        const int64_t i0 = base + (int64_t)threadIdx.x * PER;
+        const bool whole = aligned && i0 + PER <= n;
+        int v[PER];
+        if (whole) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            v[k] = (i0 + k < n) ? data[i0 + k] : 0;
+            for (int k = 0; k < PER; k += 4) {
+                const int4 t = *(const int4 *)(data + i0 + k);
+                v[k] = t.x; v[k + 1] = t.y; v[k + 2] = t.z; v[k + 3] = t.w;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                v[k] = (i0 + k < n) ? data[i0 + k] : 0;
+        }
+        int own = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            own += v[k];
         int total;
-        int ex = fae_block_excl_scan<1024>(v[0] + v[1] + v[2] + v[3], lds, &total);
-        int run = carry + ex;
+        int run = carry + fae_block_excl_scan<1024>(own, lds, &total);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (i0 + k < n)
-                data[i0 + k] = run;
-            run += v[k];
+        for (int k = 0; k < PER; ++k) {
+            const int t = v[k];
+            v[k] = run;
+            run += t;
+        }
+        if (whole) {
+#pragma unroll
+            for (int k = 0; k < PER; k += 4)
+                *(int4 *)(data + i0 + k) = make_int4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                if (i0 + k < n)
+                    data[i0 + k] = v[k];
         }
         carry += total;
     }
