@@ -93,7 +93,8 @@ typedef struct {
 
 /* ---- context -------------------------------------------------------------- */
 /* Bind a context to a device and a HIP stream (hipStream_t passed as void*;
- * NULL = the default stream).  Allocates the two 4 KiB status blocks. */
+ * NULL = the default stream).  Allocates the two 4 KiB status blocks and 0.5 MiB
+ * of pinned host memory for what fae_choose_cutoff reads back. */
 int32_t fae_create(fae_ctx **out, int32_t device, void *hip_stream);
 void fae_destroy(fae_ctx *ctx);
 const char *fae_last_error(const fae_ctx *ctx);

@@ -68,7 +68,8 @@ extern "C" int32_t fae_create(fae_ctx **out, int32_t device, void *hip_stream)
         delete ctx;
         return FAE_EHIP;
     }
-    if (hipHostMalloc((void **)&ctx->h_block, FAE_BLK_WORDS * sizeof(uint32_t), hipHostMallocDefault) !=
+    if (hipHostMalloc((void **)&ctx->h_block, (FAE_BLK_WORDS + FAE_MAX_TABLES * FAE_WINDOW_STRIDE) * sizeof(uint32_t),
+                      hipHostMallocDefault) !=
         hipSuccess) {
         (void)hipFree(ctx->d_block);
         delete ctx;
@@ -277,12 +278,15 @@ int32_t fae_readback(fae_ctx *ctx, int first, int n)
     return FAE_OK;
 }
 
-int32_t fae_sync_status(fae_ctx *ctx)
+int32_t fae_sync_status(fae_ctx *ctx) { return fae_readback_status(ctx, 0); }
+
+// One copy and one wait for both: the block starts with the status word.
+int32_t fae_readback_status(fae_ctx *ctx, int n)
 {
     for (int i = 0; i < fae_ctx::N_AUX; ++i)
         if (ctx->aux_stream[i])
             FAE_HIP(ctx, hipStreamSynchronize(ctx->aux_stream[i]));
-    int32_t rc = fae_readback(ctx, FAE_BLK_STATUS, 1);
+    int32_t rc = fae_readback(ctx, FAE_BLK_STATUS, n > 0 ? FAE_BLK_SCALARS + n : 1);
     if (rc != FAE_OK)
         return rc;
     uint32_t st = ctx->h_block[FAE_BLK_STATUS];

@@ -22,6 +22,7 @@
 #define FAE_BLK_STATUS 0
 #define FAE_BLK_SCALARS 64 // first word usable for scalar read-backs
 #define FAE_BLK_WORDS 1024
+#define FAE_WINDOW_STRIDE 2050 // words per table of a window of the access histogram; their pinned mirror follows h_block
 
 struct fae_timed_launch {
     int id;
@@ -172,6 +173,8 @@ int32_t fae_bwd_scratch_resolve(fae_ctx *ctx, int device, void **out);
 int32_t fae_readback(fae_ctx *ctx, int first, int n);
 // wait for the stream, fetch + clear the sticky status; maps it to an error code
 int32_t fae_sync_status(fae_ctx *ctx);
+// the same together with the first n scalars of the device block (fetched whatever the status says)
+int32_t fae_readback_status(fae_ctx *ctx, int n);
 int32_t fae_check_tables(fae_ctx *ctx, const fae_tables *t, const char *who);
 int32_t fae_check_batch(fae_ctx *ctx, const fae_tables *t, const fae_batch *b, const char *who);
 // data[0..n) -> exclusive prefix sums in place, data[n] = total (one workgroup; n+1 entries)

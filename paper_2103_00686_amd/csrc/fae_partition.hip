@@ -425,11 +425,11 @@ extern "C" int32_t fae_partition_batch(fae_ctx *ctx, const fae_tables *tables, c
             FAE_LAUNCH(ctx, part_emit_kernel<false>, dim3((unsigned)tiles), dim3(PT_THREADS), 0, ctx->stream, a);
         FAE_LAUNCH_CHECK(ctx);
     }
-    rc = fae_readback(ctx, FAE_BLK_SCALARS, nt + 1);
-    if (rc != FAE_OK)
+    rc = fae_readback_status(ctx, nt + 1);
+    if (rc == FAE_EHIP)
         return rc;
     *h_n_hot_samples = (int64_t)ctx->h_block[FAE_BLK_SCALARS];
     for (int z = 0; z < nt; ++z)
         h_n_hot_lookups[z] = (int64_t)ctx->h_block[FAE_BLK_SCALARS + 1 + z];
-    return fae_sync_status(ctx);
+    return rc;
 }

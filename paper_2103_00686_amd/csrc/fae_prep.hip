@@ -3,8 +3,6 @@
 // Embedding Replicator (hot rows gathered into their own HBM-resident tables).
 #include <stdlib.h>
 
-#include <vector>
-
 #include "fae_internal.h"
 
 // =================================================================================
@@ -181,7 +179,8 @@ extern "C" int32_t fae_profile(fae_ctx *ctx, const fae_tables *tables, const fae
 // =================================================================================
 #define CW_BINS 2048
 #define CW_TILE 8192 // rows per workgroup: 32 per thread, eight 16-byte loads
-#define CW_STRIDE (CW_BINS + 2) // per table: bins, rows above the window, max count
+#define CW_STRIDE FAE_WINDOW_STRIDE // per table: bins, rows above the window, max count
+static_assert(CW_STRIDE == CW_BINS + 2, "what the pinned mirror is sized for");
 #define CW_LOCAL 4 // the lowest bins of the window are counted in registers
 
 struct CwArgs {
@@ -296,8 +295,10 @@ struct Window {
     const fae_tables *t;
     const uint32_t *const *h_counts;
     uint32_t *d_hist;
-    std::vector<uint32_t> host; // [nt][CW_STRIDE]
+    uint32_t *host; // [nt][CW_STRIDE], pinned
     uint32_t lo[FAE_MAX_TABLES];
+    int at[FAE_MAX_TABLES];        // per table: a bin of the window ...
+    uint32_t left[FAE_MAX_TABLES]; // ... and the rows in it and above
 
     int32_t run(const uint32_t *new_lo)
     {
@@ -331,23 +332,32 @@ struct Window {
             FAE_LAUNCH(ctx, count_window_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a);
             FAE_LAUNCH_CHECK(ctx);
         }
-        host.resize((size_t)nt * CW_STRIDE);
-        FAE_HIP(ctx, hipMemcpyAsync(host.data(), d_hist, host.size() * sizeof(uint32_t), hipMemcpyDeviceToHost,
+        FAE_HIP(ctx, hipMemcpyAsync(host, d_hist, (size_t)nt * CW_STRIDE * sizeof(uint32_t), hipMemcpyDeviceToHost,
                                     ctx->stream));
         FAE_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        // bins -> suffix sums: host[z][b] = #rows with count >= lo_z + b
-        for (int z = 0; z < nt; ++z) {
-            uint32_t *h = &host[(size_t)z * CW_STRIDE];
-            for (int b = CW_BINS - 1; b >= 0; --b)
-                h[b] += h[b + 1];
+        for (int z = 0; z < nt; ++z) { // rows with count >= lo_z
+            const uint32_t *h = host + (size_t)z * CW_STRIDE;
+            uint32_t all = 0;
+            for (int b = 0; b <= CW_BINS; ++b)
+                all += h[b];
+            at[z] = 0;
+            left[z] = all;
         }
         return FAE_OK;
     }
     bool covers(int z, uint64_t H) const { return H >= lo[z] && H <= (uint64_t)lo[z] + CW_BINS; }
-    // rows of table z with count >= H (H inside the window)
-    int64_t n_hot(int z, uint64_t H) const
+    // Rows of table z with count >= H (H inside the window).  The thresholds asked for mostly rise by
+    // a few bins at a time, so the sum goes on from the one before (a running sum over every bin of
+    // every table took as long as a kernel, and most of it was never asked for).
+    int64_t n_hot(int z, uint64_t H)
     {
-        return (int64_t)host[(size_t)z * CW_STRIDE + (size_t)(H - lo[z])];
+        const uint32_t *h = host + (size_t)z * CW_STRIDE;
+        const int b = (int)(H - lo[z]);
+        for (; at[z] < b; ++at[z])
+            left[z] -= h[at[z]];
+        for (; at[z] > b; --at[z])
+            left[z] += h[at[z] - 1];
+        return (int64_t)left[z];
     }
     uint32_t max_count(int z) const { return host[(size_t)z * CW_STRIDE + CW_BINS + 1]; }
 };
@@ -370,7 +380,7 @@ extern "C" int32_t fae_count_hot(fae_ctx *ctx, const fae_tables *tables, const u
     if (!ws || ws_bytes < fae_choose_cutoff_workspace_bytes(tables))
         return fae_fail(ctx, FAE_ENOSPC, "fae_count_hot: workspace too small");
     FAE_HIP(ctx, hipSetDevice(ctx->device));
-    Window w{ctx, tables, h_counts, (uint32_t *)ws, {}, {}};
+    Window w{ctx, tables, h_counts, (uint32_t *)ws, ctx->h_block + FAE_BLK_WORDS, {}, {}, {}};
     rc = w.run(h_cutoff);
     if (rc != FAE_OK)
         return rc;
@@ -403,7 +413,7 @@ extern "C" int32_t fae_choose_cutoff(fae_ctx *ctx, const fae_tables *tables, con
     auto H_of = [&](int z, uint64_t c) -> uint64_t {
         return small[z] ? 0ull : scaled_cutoff(c, (uint64_t)h_T[z], (uint64_t)t_denom);
     };
-    Window w{ctx, tables, h_counts, (uint32_t *)ws, {}, {}};
+    Window w{ctx, tables, h_counts, (uint32_t *)ws, ctx->h_block + FAE_BLK_WORDS, {}, {}, {}};
     uint32_t lo0[FAE_MAX_TABLES] = {0};
     rc = w.run(lo0);
     if (rc != FAE_OK)
@@ -758,12 +768,11 @@ extern "C" int32_t fae_build_hot_tables(fae_ctx *ctx, const fae_tables *tables, 
         FAE_LAUNCH(ctx, build_scatter_kernel, dim3((unsigned)tiles), dim3(256), 0, ctx->stream, a);
         FAE_LAUNCH_CHECK(ctx);
     }
-    rc = fae_readback(ctx, FAE_BLK_SCALARS, nt);
-    if (rc != FAE_OK)
+    rc = fae_readback_status(ctx, nt);
+    if (rc == FAE_EHIP)
         return rc;
     for (int z = 0; z < nt; ++z)
         h_n_hot_out[z] = (int64_t)ctx->h_block[FAE_BLK_SCALARS + z];
-    rc = fae_sync_status(ctx);
     if (rc != FAE_OK)
         return rc; // capacity overflow: hot_ids are incomplete, do not gather
 
