@@ -17,6 +17,8 @@
 #define SORT_TILE_SMALL (SORT_THREADS * SORT_ITEMS_SMALL)
 #define SORT_SMALL_MAX_TILES 1024 // small tiles are used up to this many of them
 
+#define SORT_DIRECT_MAX_TILES 128  // small tiles per table up to which every tile adds up its table's counts itself
+
 #define BWD_SPAN_MAX 256 // sorted lookups per wave in the reduce kernel (multiple of 64)
 #define BWD_SPAN_MIN 64
 #define DBG_TILE 2048
@@ -41,6 +43,11 @@ struct BwdArgs {
     int32_t *ticket;   // [SWEEP_MAX_PASSES] next tile to hand out, per pass (use_ticket only)
     int32_t use_ticket; // chained passes: tiles are handed out by a counter instead of by workgroup number
     int32_t *ghist;    // [n_tables][SWEEP_MAX_PASSES][RADIX] digit counts of a table, per pass
+    // tiles that add up their table's counts themselves
+    int32_t direct;
+    int32_t n_clear, clear_slice; // words from `flags` on that the keys kernel clears, and each block's share
+    int32_t *tcount;      // [total_tiles][RADIX] digit counts of every tile of this pass
+    int32_t *tcount_next; // the same of the next pass, filled by this one (null in the last pass)
     uint32_t *state;   // [SWEEP_MAX_PASSES][total_tiles][RADIX] flag (2 bits) | count (30 bits)
     // pooling / optimizer variants
     int32_t mean;      // every lookup receives its bag's gradient divided by the bag's length
@@ -117,6 +124,7 @@ struct BwdPlan {
     int64_t N;
     int64_t tiles;
     int64_t small_tiles; // tiles of SORT_TILE_SMALL keys
+    int64_t most_tiles;  // the same of the table that has most of them
     int64_t max_spans; // with the smallest span
     int64_t dbg_tiles;
 };
@@ -128,6 +136,7 @@ struct BwdWs {
     float *partial;
     int32_t *flags;
     int64_t n_flags;
+    int32_t *tcount; // [SWEEP_MAX_PASSES][small tiles][RADIX], behind the flags; null: too many tiles
     int32_t *dbg_tile_sums, *dbg_rstart;
     bool ok;
     size_t used;

@@ -36,11 +36,14 @@ BwdPlan bwd_plan(int nt, const int64_t *h_n_lookups)
     p.N = 0;
     p.tiles = 0;
     p.small_tiles = 0;
+    p.most_tiles = 0;
     p.max_spans = 0;
     for (int z = 0; z < nt; ++z) {
         p.N += h_n_lookups[z];
         p.tiles += (h_n_lookups[z] + SORT_TILE - 1) / SORT_TILE;
-        p.small_tiles += (h_n_lookups[z] + SORT_TILE_SMALL - 1) / SORT_TILE_SMALL;
+        const int64_t small = (h_n_lookups[z] + SORT_TILE_SMALL - 1) / SORT_TILE_SMALL;
+        p.small_tiles += small;
+        p.most_tiles = small > p.most_tiles ? small : p.most_tiles;
         p.max_spans += (h_n_lookups[z] + BWD_SPAN_MIN - 1) / BWD_SPAN_MIN;
     }
     p.dbg_tiles = (p.N + DBG_TILE - 1) / DBG_TILE;
@@ -71,6 +74,8 @@ BwdWs bwd_carve(void *ws, size_t bytes, const BwdPlan &p, int nt, int dim, int s
     w.n_flags = p.max_spans + nt + 1;
     w.flags = cv.take<int32_t>((size_t)w.n_flags); // directly in front of the sweep area: one fill clears both
     w.sweep = cv.take<uint32_t>(64 + ((size_t)nt + sweep_tiles) * SWEEP_MAX_PASSES * RADIX);
+    // the chained passes' words and the tiles' counts are never both in use
+    w.tcount = p.small_tiles <= SORT_SMALL_MAX_TILES && p.most_tiles <= SORT_DIRECT_MAX_TILES ? (int32_t *)w.sweep : nullptr;
     w.partial = cv.take<float>((size_t)(p.max_spans * BWD_SPAN_MIN / span + nt + 1) * 2 * dim);
     w.dbg_tile_sums = cv.take<int32_t>((size_t)p.dbg_tiles + 2);
     w.dbg_rstart = cv.take<int32_t>((size_t)p.N + 2);
