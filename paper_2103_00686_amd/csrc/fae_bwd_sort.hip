@@ -503,7 +503,7 @@ __global__ __launch_bounds__(LSORT_THREADS) void lds_sort_kernel(LsortArgs a)
 // host side
 // ---------------------------------------------------------------------------------
 // Workgroups per small table for the LDS sort: enough parts to occupy the chip, never lists
-// below ~512 lookups.  part_shift[z]: part of a key = key >> shift; blk_start: prefix of
+// below ~64 lookups (a part of up to 256 is sorted by counting, whose time goes by its length).  part_shift[z]: part of a key = key >> shift; blk_start: prefix of
 // workgroups per table (tables not sorted in LDS get none).  Returns the number of workgroups.
 static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fae_batch *hot_batch, const bool *in_lds,
                int n_lds, int32_t *blk_start, int32_t *part_shift, int64_t other_blocks)
@@ -527,7 +527,7 @@ static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fa
         while ((hot_tables->h_rows[z] >> kbits) != 0)
             ++kbits;
         int parts = want;
-        while (parts > 1 && hot_batch->h_n_lookups[z] / parts < 512)
+        while (parts > 1 && hot_batch->h_n_lookups[z] / parts < 64)
             parts >>= 1;
         int pbits = 0;
         while ((1 << pbits) < parts)

@@ -136,6 +136,8 @@ __device__ __forceinline__ void fwd_onehot_wave(const V *W, const int32_t *slots
 #define LSORT_WAVES (LSORT_THREADS / FAE_WAVE)
 #define LSORT_MAX 16384
 #define LSORT_MAX_BLOCKS 1024
+#define LSORT_RANK_MAX 256 // keys of a part up to which places are counted instead of sorted by digits
+#define LSORT_RANK_LANES (LSORT_THREADS / LSORT_RANK_MAX)
 
 // LSD radix passes inside LDS on a 16-bit permutation: perm0[0..n_sel) holds indices into
 // `keys`; sorts them stably by the low `nbits` bits of (keys[idx] - sub), ping-ponging between
@@ -338,12 +340,48 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
         n_below = both >> 16;
         n_sel = both & 0xffff;
         int at = ex & 0xffff;
+        int *sel = &wcnt[0][0]; // the keys of a short part, in input order (the counters are not in use yet)
+        const bool few = n_sel <= LSORT_RANK_MAX;
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            if (kk[i] >= 0 && (kk[i] >> pshift) == part)
+            if (kk[i] >= 0 && (kk[i] >> pshift) == part) {
+                if (few)
+                    sel[at] = kk[i];
                 perm[0][at++] = (unsigned short)(e0 + i);
+            }
     }
     __syncthreads();
+    // A short part: every key's place is the number of keys that go before it, counted outright by
+    // LSORT_RANK_LANES lanes per key.  A radix pass costs two sweeps, a scan and five barriers however
+    // short the list (one table of 1024 lookups, forward and sort in one launch: 9.7 -> 7.4 us).
+    if (n_sel <= LSORT_RANK_MAX) {
+        const int *sel = &wcnt[0][0];
+        const int i = threadIdx.x / LSORT_RANK_LANES, q = threadIdx.x % LSORT_RANK_LANES;
+        const int key = i < n_sel ? sel[i] : 0;
+        int rank = 0;
+        if (i < n_sel) {
+#pragma unroll 8
+            for (int j = q; j < n_sel; j += LSORT_RANK_LANES) {
+                const int k = sel[j];
+                rank += (k < key || (k == key && j < i)) ? 1 : 0;
+            }
+        }
+#pragma unroll
+        for (int m = 1; m < LSORT_RANK_LANES; m <<= 1)
+            rank += __shfl_xor(rank, m, FAE_WAVE);
+        if (i < n_sel && q == 0) {
+            const int e = perm[0][i];
+            int sm = e;
+            if (off) {
+                sm = fae_sample_of(off, n_samples, e);
+                if (off[sm] > e || off[sm + 1] <= e)
+                    fae_flag(status, FAE_STATUS_ERANGE); // malformed CSR
+            }
+            keys_out[n_below + rank] = key;
+            vals_out[n_below + rank] = sm;
+        }
+        return;
+    }
 
     // LSD passes over the bits below part_shift
     const int cur = lds_radix_passes(keyA, 0, n_sel, pshift, perm[0], perm[1], wcnt, scan_lds);
