@@ -69,8 +69,8 @@ __device__ __forceinline__ int part_owner(const int *s_off, int n, int j)
 // store per lookup and no pass of its own, and the position among the hot samples never leaves LDS.
 // The lookups of a tile of a table with offsets are one range: a lookup finds its sample in the
 // tile's offsets in LDS instead of searching all offsets in memory.
-//   26 one-hot tables, 262 144 samples: 56 us in two kernels, 140 -> 112 us a call (before: 76 us in
-//   seven launches: clear, mark, count, scan, lists, offsets, slots)
+//   26 one-hot tables, 262 144 samples: 56 us in two kernels, 140 -> 99 us a call (before: 76 us in
+//   seven launches: clear, mark, count, scan, lists, offsets, slots; and two waits instead of one)
 #define PT_LK 8
 
 // table of item i (see below); with tiles of whole waves it is the same for every lane, and said so
