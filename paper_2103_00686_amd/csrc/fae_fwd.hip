@@ -61,8 +61,9 @@ __device__ __forceinline__ void fwd_add_rows(V &acc, V &lost, const V *W, int sl
     }
 }
 
-// the lane's slot of a chunk (-1: past the end, or out of range and flagged)
-__device__ __forceinline__ int fwd_slot(const int32_t *slots, int j, int end, int n_hot, uint32_t *status)
+// The lane's slot of a chunk (-1: past the end, or out of range and flagged).  Lookups are numbered
+// without a sign here: the last chunk of a bag may step past 2^31.
+__device__ __forceinline__ int fwd_slot(const int32_t *slots, uint32_t j, uint32_t end, int n_hot, uint32_t *status)
 {
     int sl = j < end ? slots[j] : -1;
     if (j < end && (unsigned)sl >= (unsigned)n_hot) {
@@ -118,9 +119,9 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_ker
         for (int c0 = 0; c0 < ncols; c0 += LPR) {
             const int c = c0 + l;
             V acc = vec_ops<V>::zero(), lost = vec_ops<V>::zero();
-            for (int j0 = beg; j0 < end; j0 += FAE_WAVE) {
+            for (uint32_t j0 = beg; j0 < (uint32_t)end; j0 += FAE_WAVE) {
                 const int slot = fwd_slot(slots, j0 + lane, end, n_hot, a.status);
-                const int count = end - j0 < FAE_WAVE ? end - j0 : FAE_WAVE;
+                const int count = end - j0 < FAE_WAVE ? (int)(end - j0) : FAE_WAVE;
                 if (end - beg > FWD_PLAIN_MAX * G) // the same for the whole wave
                     fwd_add_rows<V, FAE_WAVE, G, 4, true>(acc, lost, W, slot, g, count, ncols, c, c < ncols);
                 else
@@ -139,9 +140,9 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_ker
         for (int c0 = 0; c0 < ncols; c0 += LPR) {
             const int c = c0 + l;
             V acc = vec_ops<V>::zero(), lost = vec_ops<V>::zero();
-            for (int j0 = beg; j0 < end; j0 += LPR) { // a lane group leaves as a whole
+            for (uint32_t j0 = beg; j0 < (uint32_t)end; j0 += LPR) { // a lane group leaves as a whole
                 const int slot = fwd_slot(slots, j0 + l, end, n_hot, a.status);
-                const int count = end - j0 < LPR ? end - j0 : LPR;
+                const int count = end - j0 < LPR ? (int)(end - j0) : LPR;
                 if (end - beg > FWD_PLAIN_MAX)
                     fwd_add_rows<V, LPR, 1, (LPR < 4 ? LPR : 4), true>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
                 else

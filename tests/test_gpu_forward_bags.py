@@ -43,3 +43,25 @@ def test_bag_lengths_at_the_edges(dim, pooling):
             ref, mag = ref * scale, mag * scale
         # at most 128 plain additions in a row, six more across lane groups and the scaling: 136 * 2^-24
         assert bool(((out[:, z].double() - ref).abs() <= 136 * 2.0 ** -24 * mag).all()), f"table {z}"
+
+
+@pytest.mark.parametrize("variant", [1, 2])  # a lane group per bag, a wave per bag
+@pytest.mark.parametrize("dim", [4, 64])
+def test_bags_at_the_end_of_the_longest_list(dim, variant):
+    """A list of the most lookups that a call takes: the chunk behind the last bag's end lies past 2^31.
+    Only the last 300 entries belong to a bag and are read."""
+    n, rows = (1 << 31) - 2, 1000
+    slots = torch.empty(n, dtype=torch.int32, device="cuda")
+    tail = torch.randint(0, rows, (300,), dtype=torch.int32, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2))
+    slots[-300:] = tail
+    off = torch.tensor([n - 300, n - 129, n - 3, n], dtype=torch.int32, device="cuda")
+    hp = HotPath([rows], dim)
+    hp.alloc_counts()
+    hp.build([0], [rows], seed=3)
+    B.fae_set_option(hp.ctx, "fwd_variant", variant)
+    out = hp.forward(HotBatch(3, [slots], [off], [n]))
+    hp.sync()
+    w = hp.hotW[0].double()[tail.long()]
+    for s, (b, e) in enumerate([(0, 171), (171, 297), (297, 300)]):
+        # up to 171 terms: 136 * 2^-24 covers the plain sum's 128 and what a compensated one leaves
+        assert bool(((out[s, 0].double() - w[b:e].sum(0)).abs() <= 136 * 2.0 ** -24 * w[b:e].abs().sum(0)).all())
