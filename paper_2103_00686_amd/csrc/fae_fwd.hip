@@ -53,10 +53,10 @@ __device__ __forceinline__ void fwd_add_rows(V &acc, V &lost, const V *W, int sl
         }
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            if (COMP)
-                vec_ops<V>::add_comp(acc, lost, v[u]);
-            else
+            if (!COMP)
                 vec_ops<V>::add(acc, v[u]);
+            else if (j + u * STRIDE < count) // a zero behind an infinite sum would make it NaN: inf - inf in the carried error
+                vec_ops<V>::add_comp(acc, lost, v[u]);
         }
     }
 }

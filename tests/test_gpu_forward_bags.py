@@ -65,3 +65,28 @@ def test_bags_at_the_end_of_the_longest_list(dim, variant):
     for s, (b, e) in enumerate([(0, 171), (171, 297), (297, 300)]):
         # up to 171 terms: 136 * 2^-24 covers the plain sum's 128 and what a compensated one leaves
         assert bool(((out[s, 0].double() - w[b:e].sum(0)).abs() <= 136 * 2.0 ** -24 * w[b:e].abs().sum(0)).all())
+
+
+@pytest.mark.parametrize("dim", [1, 2, 4, 8, 16, 64, 128, 256])
+@pytest.mark.parametrize("variant", [1, 2])
+def test_an_infinite_last_row_stays_infinite(dim, variant):
+    """The sum of a long bag (more than 128 lookups per lane group, so the rounding error is carried
+    along) whose last row is infinite: nothing may be added behind it, not even a zero."""
+    rows = 100
+    ncols = dim // 4 if dim % 4 == 0 else dim
+    lpr = 1
+    while lpr < min(ncols, 64):
+        lpr *= 2
+    groups = 64 // lpr if variant == 2 else 1
+    ln = np.array([128 * groups + x for x in (1, 2, 3, 5, 7, 11, 13, 30, 37, 63)])
+    off = np.concatenate([[0], np.cumsum(ln)])
+    slots = np.random.default_rng(dim).integers(0, rows - 1, off[-1], dtype=np.int32)
+    slots[off[1:] - 1] = rows - 1
+    hp = HotPath([rows], dim)
+    hp.alloc_counts()
+    hp.build([0], [rows], seed=3)
+    hp.hotW[0][rows - 1] = float("inf")
+    B.fae_set_option(hp.ctx, "fwd_variant", variant)
+    out = hp.forward(HotBatch(len(ln), [torch.from_numpy(slots).cuda()], [torch.from_numpy(off.astype(np.int32)).cuda()], [int(off[-1])]))
+    hp.sync()
+    assert bool((out == float("inf")).all())
