@@ -61,6 +61,48 @@ __device__ __forceinline__ void fwd_add_rows(V &acc, V &lost, const V *W, int sl
     }
 }
 
+// The same for a lane group of one or two lanes, which takes eight lookups at a time, j0 .. j0 + 7:
+// a lane reads 8 / LPR consecutive slots at once, lookup e is in register e % PER of lane e / PER, and
+// the eight rows are in flight together.  nl: length of the list (entries behind the bag are read, not used).
+template <typename V, int LPR, bool COMP>
+__device__ __forceinline__ void fwd_add_narrow(V &acc, V &lost, const V *W, const int32_t *slots, uint32_t j0, int count, uint32_t nl,
+                                               int n_hot, int ncols, int c, uint32_t *status)
+{
+    constexpr int PER = 8 / LPR;
+    const int first = threadIdx.x % LPR * PER;
+    int slot[PER];
+    if (j0 + 8 <= nl) {
+        __builtin_memcpy(slot, slots + j0 + first, sizeof(slot)); // one load; the bag may start at any entry
+    } else {
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            slot[k] = first + k < count ? slots[j0 + first + k] : 0;
+    }
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if ((unsigned)slot[k] >= (unsigned)n_hot) {
+            bad |= first + k < count;
+            slot[k] = -1;
+        }
+    }
+    if (bad)
+        fae_flag(status, FAE_STATUS_ERANGE);
+    V v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int sl = LPR == 1 ? slot[e % PER] : __shfl(slot[e % PER], e / PER, LPR);
+        v[e] = (e < count && sl >= 0 && c < ncols) ? W[(int64_t)sl * ncols + c] : vec_ops<V>::zero();
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if (!COMP)
+            vec_ops<V>::add(acc, v[e]);
+        else if (e < count)
+            vec_ops<V>::add_comp(acc, lost, v[e]);
+    }
+}
+
 // The lane's slot of a chunk (-1: past the end, or out of range and flagged).  Lookups are numbered
 // without a sign here: the last chunk of a bag may step past 2^31.
 __device__ __forceinline__ int fwd_slot(const int32_t *slots, uint32_t j, uint32_t end, int n_hot, uint32_t *status)
@@ -79,12 +121,20 @@ __device__ __forceinline__ int fwd_slot(const int32_t *slots, uint32_t j, uint32
 //   wave      a wave owns a bag, its 64 / LPR lane groups take alternate rows: long bags.
 // What bounds it: rows that miss the L2 (large tables), else the chain offsets -> slots -> rows of a
 // bag.  So the slots of a bag (64 of them, or LPR for a lane group) come with one load and are handed
-// out by lane shuffles, and a row costs one round trip instead of two in a row, with 8 (4) rows per
-// group in flight; the mapping goes by each table's own bags, and all tables share the launch:
+// out by lane shuffles, and a row costs one round trip instead of two in a row, with 8 rows per group
+// in flight in the wave mapping of LPR >= 32 and 4 elsewhere; the mapping goes by each table's own bags,
+// and all tables share the launch:
 //   8 x 65 536 bags of about 20, dim 128: 650 -> 521 us (10.3 TB/s of rows out of L2 and beyond)
 //   3 tables with bags of up to 100 and a one-hot one, 6007 samples, dim 100: 9 + 28.7 -> 27.2 us
 //   3 tables of short bags and 2 one-hot ones, 3001 samples, dim 20: 4.7 + 11.9 -> 9.1 us
-template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_kernel(FwdArgs a)
+// A group of one or two lanes would get one or two rows out of such a load, so it reads eight slots at a
+// time (fwd_add_narrow), which takes a few registers more at LPR 2 than eight waves per SIMD leave (with
+// spills 12.2 us for 3 x 32 768 bags of 1-10, dim 8, without 10.5).  Bags of 1-100 in five tables, 65 536 samples:
+//   dim 2 (LPR 2, scalar): 172 -> 103 us; dim 8 (LPR 2): 228 -> 140 us (four slots and rows in turn: 185 us)
+//   3 tables, 2048 samples, dim 4 (LPR 1): 53.6 -> 24.2 us (31.4 us); dim 1: 35.9 -> 18.1 us (17.1 us)
+// Groups of four keep one slot per lane: the registers of eight cost the wave mapping more (84 -> 89 us for
+// five tables of 32 768 bags of 1-100, dim 16) than the group mapping gains from them (33.3 -> 29.7 us, bags of 1-30).
+template <typename V, int LPR> __global__ __launch_bounds__(256, LPR == 2 ? 7 : 8) void fwd_kernel(FwdArgs a)
 {
     const int z = fae_find_table(a.blk_start, a.n_tables, blockIdx.x);
     const int bl = blockIdx.x - a.blk_start[z];
@@ -140,13 +190,21 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_ker
         for (int c0 = 0; c0 < ncols; c0 += LPR) {
             const int c = c0 + l;
             V acc = vec_ops<V>::zero(), lost = vec_ops<V>::zero();
-            for (uint32_t j0 = beg; j0 < (uint32_t)end; j0 += LPR) { // a lane group leaves as a whole
-                const int slot = fwd_slot(slots, j0 + l, end, n_hot, a.status);
-                const int count = end - j0 < LPR ? (int)(end - j0) : LPR;
-                if (end - beg > FWD_PLAIN_MAX)
-                    fwd_add_rows<V, LPR, 1, (LPR < 4 ? LPR : 4), true>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
-                else
-                    fwd_add_rows<V, LPR, 1, (LPR < 4 ? LPR : 4), false>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
+            constexpr int CHUNK = LPR < 4 ? 8 : LPR;
+            for (uint32_t j0 = beg; j0 < (uint32_t)end; j0 += CHUNK) { // a lane group leaves as a whole
+                const int count = end - j0 < CHUNK ? (int)(end - j0) : CHUNK;
+                if constexpr (LPR < 4) {
+                    if (end - beg > FWD_PLAIN_MAX)
+                        fwd_add_narrow<V, LPR, true>(acc, lost, W, slots, j0, count, a.n_lookups[z], n_hot, ncols, c, a.status);
+                    else
+                        fwd_add_narrow<V, LPR, false>(acc, lost, W, slots, j0, count, a.n_lookups[z], n_hot, ncols, c, a.status);
+                } else {
+                    const int slot = fwd_slot(slots, j0 + l, end, n_hot, a.status);
+                    if (end - beg > FWD_PLAIN_MAX)
+                        fwd_add_rows<V, LPR, 1, 4, true>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
+                    else
+                        fwd_add_rows<V, LPR, 1, 4, false>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
+                }
             }
             if (a.mean && end - beg > 1)
                 vec_ops<V>::scale(acc, 1.0f / (float)(end - beg));

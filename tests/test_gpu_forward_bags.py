@@ -90,3 +90,35 @@ def test_an_infinite_last_row_stays_infinite(dim, variant):
     out = hp.forward(HotBatch(len(ln), [torch.from_numpy(slots).cuda()], [torch.from_numpy(off.astype(np.int32)).cuda()], [int(off[-1])]))
     hp.sync()
     assert bool((out == float("inf")).all())
+
+
+@pytest.mark.parametrize("dim", [1, 2, 4, 8, 12])
+def test_narrow_rows(dim):
+    """Rows of one, two and four lanes, whose slots come eight at a time (the first two) from any entry on:
+    every length up to two such loads and around the plain sum's limit; a slot that no row has is reported
+    and adds nothing, and a bag does not see the ones of the bags behind it."""
+    rng = np.random.default_rng(dim)
+    ln = np.concatenate([rng.permutation(np.repeat(np.arange(18), 5)), [127, 128, 129, 136, 137, 7]])
+    off = np.concatenate([[0], np.cumsum(ln)])
+    rows, n = 200, int(off[-1])
+    slots = rng.integers(0, rows, n, dtype=np.int32)
+    bad = rng.permutation(n)[:40]
+    wrong = slots.copy()
+    wrong[bad] = rng.choice([-1, rows, 1 << 30], 40)
+    hp = HotPath([rows], dim)
+    hp.alloc_counts()
+    hp.build([0], [rows], seed=3)
+    B.fae_set_option(hp.ctx, "fwd_variant", 1)
+    w = hp.hotW[0].double().cpu().numpy()
+    for s, keep in ((slots, np.ones(n, dtype=bool)), (wrong, ~np.isin(np.arange(n), bad))):
+        out = hp.forward(HotBatch(len(ln), [torch.from_numpy(s).cuda()], [torch.from_numpy(off.astype(np.int32)).cuda()], [n]))
+        if keep.all():
+            hp.sync()
+        else:
+            with pytest.raises(B.FaeError, match="out of range"):
+                hp.sync()
+        seg = np.repeat(np.arange(len(ln)), ln)[keep]
+        ref, mag = np.zeros((len(ln), dim)), np.zeros((len(ln), dim))
+        np.add.at(ref, seg, w[slots[keep]])
+        np.add.at(mag, seg, np.abs(w[slots[keep]]))
+        assert (np.abs(out[:, 0].double().cpu().numpy() - ref) <= 128 * 2.0 ** -24 * mag).all()
