@@ -214,6 +214,14 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, LPR == 2 ? 7 : 
     }
 }
 
+// One-hot tables beside bags: from this many bytes of their pooled rows on they get a launch of their
+// own, fwd_onehot_kernel's.  Below, one launch for all is shorter (its bags and rows overlap, and a launch
+// is saved), above the deeper copy is worth more.  One launch / two, microseconds:
+//   25 one-hot tables and one of bags of 1-10: 26 x 4096 x 64 (100 MiB) 12.6 / 15.2, 50 001 x 64 (305 MiB) 99 / 106,
+//   90 000 x 64 (549 MiB) 176 / 173, 131 072 x 64 (800 MiB) 248 / 238, 131 072 x 128 (1.6 GiB) 482 / 465;
+//   10 and one: 131 072 x 128 (640 MiB) 214.5 / 217; 13 and three: 65 536 x 256 (832 MiB) 335 / 336
+#define FWD_SPLIT_BYTES (768LL << 20)
+
 // Every table one-hot: no bag code beside it, so sixteen rows fit in flight per lane group (26 tables of
 // 50 001 samples, dim 64: 68.5 us, against 77.0 us for fwd_kernel with its eight).
 template <typename V, int LPR> __global__ __launch_bounds__(256) void fwd_onehot_kernel(FwdArgs a)
@@ -312,10 +320,8 @@ static int32_t fwd_impl(fae_ctx *ctx, const fae_tables *hot_tables, const float 
     a.status = ctx->d_block;
     a.stream_out = ctx->opt_fwd_stream != 0;
     a.mean = pooling == FAE_POOL_MEAN;
-    int64_t blocks = 0;
-    bool bags = false;
+    int n_bags = 0;
     for (int z = 0; z < nt; ++z) {
-        int64_t per_block = 256; // one-hot: 256 samples per workgroup
         a.kind[z] = FWD_ONEHOT;
         if (a.offsets[z] || ctx->opt_fwd != 0) {
             // wave-per-bag pays once a bag keeps every lane group of the wave busy for two rounds
@@ -325,20 +331,29 @@ static int32_t fwd_impl(fae_ctx *ctx, const fae_tables *hot_tables, const float 
             if (ctx->opt_fwd == 2)
                 wave = groups > 1;
             a.kind[z] = wave ? FWD_WAVE : FWD_GROUP;
-            bags = true;
-            per_block = wave ? 256 / FAE_WAVE : 256 / lpr;
+            ++n_bags;
         }
-        a.blk_start[z] = (int32_t)blocks;
-        blocks += (S + per_block - 1) / per_block;
-        if (blocks >= 2147483647LL)
-            return fae_fail(ctx, FAE_EINVAL, "fae_embbag_fwd: batch too large for one launch");
     }
-    a.blk_start[nt] = (int32_t)blocks;
-    fae_ktimer kt(ctx, FAE_K_FWD);
-    if (vec)
-        fwd_dispatch<float4>(ctx, a, lpr, bags, (int)blocks);
-    else
-        fwd_dispatch<float>(ctx, a, lpr, bags, (int)blocks);
-    FAE_LAUNCH_CHECK(ctx);
+    const bool split = n_bags > 0 && (int64_t)(nt - n_bags) * S * dim * 4 >= FWD_SPLIT_BYTES;
+    for (int part = split ? 0 : 1; part < 2; ++part) { // the one-hot tables by themselves, then the others (or all)
+        int64_t blocks = 0;
+        for (int z = 0; z < nt; ++z) {
+            a.blk_start[z] = (int32_t)blocks;
+            const bool bag = a.kind[z] != FWD_ONEHOT;
+            if (split && bag != (part == 1))
+                continue;
+            const int64_t per_block = !bag ? 256 : (a.kind[z] == FWD_WAVE ? 256 / FAE_WAVE : 256 / lpr);
+            blocks += (S + per_block - 1) / per_block;
+            if (blocks >= 2147483647LL)
+                return fae_fail(ctx, FAE_EINVAL, "fae_embbag_fwd: batch too large for one launch");
+        }
+        a.blk_start[nt] = (int32_t)blocks;
+        fae_ktimer kt(ctx, FAE_K_FWD);
+        if (vec)
+            fwd_dispatch<float4>(ctx, a, lpr, n_bags > 0 && part == 1, (int)blocks);
+        else
+            fwd_dispatch<float>(ctx, a, lpr, n_bags > 0 && part == 1, (int)blocks);
+        FAE_LAUNCH_CHECK(ctx);
+    }
     return FAE_OK;
 }

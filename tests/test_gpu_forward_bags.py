@@ -122,3 +122,28 @@ def test_narrow_rows(dim):
         np.add.at(ref, seg, w[slots[keep]])
         np.add.at(mag, seg, np.abs(w[slots[keep]]))
         assert (np.abs(out[:, 0].double().cpu().numpy() - ref) <= 128 * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("S", [131072, 131071])  # 768 MiB of one-hot rows: a launch of their own; less: one for all
+def test_large_one_hot_tables_beside_bags(S):
+    rows, dim = [500, 60_000, 9, 3000], 512
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    ln = torch.randint(0, 4, (S,), device="cuda", generator=gen)
+    off = torch.zeros(S + 1, dtype=torch.int32, device="cuda")
+    off[1:] = ln.cumsum(0)
+    nl = [S, S, int(off[-1]), S]
+    slots = [torch.randint(0, r, (n,), dtype=torch.int32, device="cuda", generator=gen) for r, n in zip(rows, nl)]
+    hp = HotPath(rows, dim)
+    hp.alloc_counts()
+    hp.build([0] * 4, rows, seed=3)
+    out = torch.full((S, 4, dim), float("nan"), device="cuda")
+    hp.forward(HotBatch(S, slots, [None, None, off, None], nl), out)
+    hp.sync()
+    for z in (0, 1, 3):
+        assert torch.equal(out[:, z], hp.hotW[z][slots[z].long()])
+    w = hp.hotW[2][slots[2].long()]
+    pooled = torch.zeros((S, dim), device="cuda")
+    for k in range(3):  # the same additions in the same order
+        has = ln > k
+        pooled[has] += w[(off[:-1].long() + k)[has]]
+    assert torch.equal(out[:, 2], pooled)
