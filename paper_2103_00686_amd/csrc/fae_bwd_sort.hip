@@ -71,22 +71,9 @@ __device__ __forceinline__ void bwd_keys_thread(const BwdArgs &a, int z, int j0,
     }
 }
 
-// how many of the workgroup's threads hold `flag` (every thread calls it; red: 256 / 64 + 1 ints)
-__device__ __forceinline__ int keys_block_count(bool flag, int *red)
-{
-    const int c = __popcll(__ballot(flag));
-    __syncthreads(); // red may still be read from a previous call
-    if (fae_lane() == 0)
-        red[threadIdx.x / FAE_WAVE] = c;
-    __syncthreads();
-    return red[0] + red[1] + red[2] + red[3];
-}
-
 // Each thread handles four consecutive lookups (16-byte loads and stores when aligned).
 // Tables with offsets: which sample a lookup belongs to is found by the workgroup together.
-//   1. the sample of the workgroup's first lookup: an upper-bound search over the offsets in
-//      which every round probes 256 evenly spaced entries at once (three dependent loads for
-//      65 536 samples, where a search by one thread makes seventeen);
+//   1. the sample of the workgroup's first lookup;
 //   2. every later bag that starts among the workgroup's 1024 lookups marks its first lookup
 //      with its sample number (the largest one wins where empty bags share a start);
 //   3. a running maximum over the marks gives every lookup its sample.
@@ -112,20 +99,9 @@ __global__ __launch_bounds__(256) void bwd_keys_kernel(BwdArgs a)
 #pragma unroll
         for (int q = 0; q < KEYS_PER_THREAD; ++q)
             s_mark[threadIdx.x * KEYS_PER_THREAD + q] = -1;
-        // 1. entries of offsets[0 .. n_samples] that are <= jb: all before lo are, none from hi on is
-        int lo = 0, hi = a.n_samples + 1;
-        while (hi - lo > 256) {
-            const int step = (hi - lo + 255) / 256;
-            const int64_t idx = (int64_t)lo + (int64_t)(threadIdx.x + 1) * step - 1; // last entry of piece threadIdx.x
-            const bool le = idx < hi && off[idx] <= jb;
-            const int c = keys_block_count(le, s_red); // pieces that lie wholly at or below jb
-            lo += c * step;
-            hi = lo + step < hi ? lo + step : hi;
-        }
-        const bool le = lo + (int)threadIdx.x < hi && off[lo + threadIdx.x] <= jb;
-        int s_first = lo + keys_block_count(le, s_red) - 1;
-        s_first = s_first < 0 ? 0 : (s_first >= a.n_samples ? a.n_samples - 1 : s_first);
-        // 2. (also orders the clearing of s_mark above before the marks: keys_block_count has barriers)
+        // 1.
+        const int s_first = fae_block_sample_of(off, a.n_samples, jb, s_red);
+        // 2. (also orders the clearing of s_mark above before the marks: fae_block_sample_of has barriers)
         for (int64_t s = (int64_t)s_first + 1 + threadIdx.x; s < a.n_samples; s += 256) {
             const int o = off[s];
             if (o >= jend)
@@ -149,7 +125,7 @@ __global__ __launch_bounds__(256) void bwd_keys_kernel(BwdArgs a)
             if (fae_lane() >= d)
                 run = run > o ? run : o;
         }
-        __syncthreads(); // s_red was read by keys_block_count
+        __syncthreads(); // s_red was read by fae_block_sample_of
         if (fae_lane() == FAE_WAVE - 1)
             s_red[threadIdx.x / FAE_WAVE] = run;
         __syncthreads();

@@ -20,6 +20,7 @@
 
 // word offsets inside the 4 KiB device / pinned-host blocks
 #define FAE_BLK_STATUS 0
+#define FAE_BLK_HEAVY 32   // number of the last partition call that had a heavy tile
 #define FAE_BLK_SCALARS 64 // first word usable for scalar read-backs
 #define FAE_BLK_WORDS 1024
 #define FAE_WINDOW_STRIDE 2050 // words per table of a window of the access histogram; their pinned mirror follows h_block
@@ -33,6 +34,7 @@ struct fae_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     uint32_t *d_block = nullptr; // device, FAE_BLK_WORDS words
+    uint32_t part_calls = 0;     // calls of the partition so far
     uint32_t *h_block = nullptr; // pinned host mirror
     int n_cu = 256;
     int64_t opt_profile = 0; // 0 auto, 1 global atomics, 2 LDS-privatised
@@ -335,6 +337,37 @@ __device__ __forceinline__ int fae_sample_of(const int32_t *offsets, int n_sampl
 {
     int s = fae_upper_bound(offsets, 0, n_samples + 1, j) - 1;
     return s < 0 ? 0 : (s >= n_samples ? n_samples - 1 : s); // in range even for a malformed CSR
+}
+
+// how many of a workgroup's 256 threads hold `flag` (every thread calls it; red: 256 / 64 + 1 ints)
+__device__ __forceinline__ int fae_block_count(bool flag, int *red)
+{
+    const int c = __popcll(__ballot(flag));
+    __syncthreads(); // red may still be read from a previous call
+    if (fae_lane() == 0)
+        red[threadIdx.x / FAE_WAVE] = c;
+    __syncthreads();
+    return red[0] + red[1] + red[2] + red[3];
+}
+
+// The sample that owns lookup j, found by a workgroup of 256 threads together (in range even for a
+// malformed CSR): an upper-bound search over the offsets in which every round probes 256 evenly
+// spaced entries at once (three dependent loads for 65 536 samples, where a search by one thread
+// makes seventeen).
+__device__ __forceinline__ int fae_block_sample_of(const int32_t *off, int n_samples, int j, int *red)
+{
+    int lo = 0, hi = n_samples + 1; // entries of off[0 .. n_samples] before lo are <= j, none from hi on is
+    while (hi - lo > 256) {
+        const int step = (hi - lo + 255) / 256;
+        const int64_t idx = (int64_t)lo + (int64_t)(threadIdx.x + 1) * step - 1; // last entry of piece threadIdx.x
+        const bool le = idx < hi && off[idx] <= j;
+        const int c = fae_block_count(le, red); // pieces that lie wholly at or below j
+        lo += c * step;
+        hi = lo + step < hi ? lo + step : hi;
+    }
+    const bool le = lo + (int)threadIdx.x < hi && off[lo + threadIdx.x] <= j;
+    const int s = lo + fae_block_count(le, red) - 1;
+    return s < 0 ? 0 : (s >= n_samples ? n_samples - 1 : s);
 }
 
 #endif // __HIPCC__
