@@ -12,12 +12,12 @@
 #define SORT_ITEMS 16
 #define SORT_WAVES (SORT_THREADS / FAE_WAVE)
 #define SORT_TILE (SORT_THREADS * SORT_ITEMS)
-// short lists: smaller tiles, so that a chained pass has enough workgroups and a short chain per tile
+// short lists: smaller tiles, so that a pass has enough workgroups and, where its tiles are chained, a short chain per tile
 #define SORT_ITEMS_SMALL 4
 #define SORT_TILE_SMALL (SORT_THREADS * SORT_ITEMS_SMALL)
 #define SORT_SMALL_MAX_TILES 1024 // small tiles are used up to this many of them
 
-#define SORT_DIRECT_MAX_TILES 128  // small tiles per table up to which every tile adds up its table's counts itself
+#define SORT_DIRECT_MAX_TILES 128 // small tiles per table up to which every tile may add up its table's counts itself
 
 #define BWD_SPAN_MAX 256 // sorted lookups per wave in the reduce kernel (multiple of 64)
 #define BWD_SPAN_MIN 64

@@ -2,8 +2,10 @@
 // (Sec. 2.2, Sec. 6.2: the embedding update of hot mini-batches runs on the GPU).
 //   keys     key = hot slot, value = sample id, per table segment
 //   sort     inside LDS for tables of up to 16 K lookups (split over workgroups by key range),
-//            else stable LSD radix passes over only the bits a hot slot can occupy: one chained
-//            kernel per pass for short lists, histogram / column scan / scatter for long ones
+//            else stable LSD radix passes over only the bits a hot slot can occupy: one kernel per
+//            pass for short lists, whose tiles add up their table's digit counts themselves (direct:
+//            few tiles, most of them in a few tables) or are chained through published counts;
+//            histogram / column scan / scatter for long ones
 // Also here: the sort started ahead of the backward (side stream), and the launch that carries
 // the forward's row copies and the LDS sort together.
 #include "fae_bwd.h"
@@ -231,9 +233,9 @@ __global__ __launch_bounds__(256) void sort_colscan_kernel(BwdArgs a)
 // clears the later passes' counts and the reduce kernel's flags), and the keys kernel counts one
 // digit instead of one per pass.  Keys and passes against the chained form:
 //   207 K lookups in two tables, 22 bits: 44 -> 39 us; 110 K in five tables, 18 bits: 37 -> 33 us
-// The counts read grow with the square of a table's tiles (1 KB each), so the form is used up to
-// SORT_DIRECT_MAX_TILES of them per table, and only for the lists that take small tiles: at 1.3 M
-// lookups in 26 tables a pass took 19 us (chained, tiles of 4096: 17.5 us).
+// The counts read grow with the square of a table's tiles (1 KB each); the rule is in bwd_sort_stage.
+// Sixteen of them in flight and four waves per SIMD (99 registers; with the loop unrolled it took 239 and
+// ran two): fewer in flight cost more than more waves give (1 x 128 tiles: 43.0 us, eight in flight 44.2, four 47).
 // SCATTER_CHAINED: the whole pass is this one kernel.  A tile publishes its digit counts,
 // then adds up the published counts of the tiles before it (walking back until it meets a
 // tile that already published its running total) and publishes its own running total.  A
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(256) void sort_colscan_kernel(BwdArgs a)
 // ~35 ns per workgroup, one device-wide atomic after the other: half the time of a pass over
 // a short list.  sort_variant 4 does it that way.)
 enum { SCATTER_COUNTED, SCATTER_CHAINED, SCATTER_DIRECT };
-template <int MODE, int ITEMS> __global__ __launch_bounds__(SORT_THREADS) void sort_scatter_kernel(BwdArgs a)
+template <int MODE, int ITEMS> __global__ __launch_bounds__(SORT_THREADS, MODE == SCATTER_DIRECT ? 4 : 1) void sort_scatter_kernel(BwdArgs a)
 {
     constexpr int TILE = SORT_THREADS * ITEMS;
     constexpr bool CHAINED = MODE == SCATTER_CHAINED;
@@ -294,6 +296,7 @@ template <int MODE, int ITEMS> __global__ __launch_bounds__(SORT_THREADS) void s
         const int32_t *tc = a.tcount + (int64_t)a.tile_start[z] * RADIX + 4 * lane;
         int4 before = make_int4(0, 0, 0, 0), all = make_int4(0, 0, 0, 0);
         if (4 * lane <= a.mask)
+#pragma unroll 1
             for (int r0 = w; r0 < tiles_z; r0 += UN * SORT_WAVES) {
                 int4 c[UN];
 #pragma unroll
@@ -566,9 +569,22 @@ int32_t bwd_sort_stage(fae_ctx *ctx, hipStream_t st, const fae_tables *hot_table
         ++bits;
     const int passes = tiles > 0 ? (bits + RADIX_BITS - 1) / RADIX_BITS : 0;
     const int digit_bits = passes > 0 ? (bits + passes - 1) / passes : RADIX_BITS;
-    // Tiles that add up their table's counts themselves: where the tiles are small and every table has
-    // few enough of them (sort_variant 1, 3 and 4 force the other forms).
-    const bool direct = passes > 0 && w.tcount != nullptr && (ctx->opt_sort == 0 || ctx->opt_sort == 2);
+    // Tiles that add up their table's counts themselves (sort_variant 1, 3 and 4 force the other forms).  What
+    // that reads grows with the square of a table's tiles, and what it saves is the chain from tile to tile,
+    // so it pays where the tiles fit the chip at once (one per compute unit) and a few tables hold most of
+    // them.  Backward, microseconds, chained / direct:
+    //   1 x 64 tiles 43.2 / 38.9, 1 x 128 49.8 / 43.0, 2 x 64 47.1 / 42.6, 4 x 30 45.2 / 42.1, 4 x 50 50.8 / 48.0
+    //   2 x 128 57.4 / 55.7, 4 x 64 54.3 / 55.5, 5 x 22 42.8 / 42.1; 8 x 18 44.6 / 45.2, 8 x 25 48.3 / 49.5, 13 x 18 50.4 / 52.1
+    //   3 x 100 59.1 / 63.5, 8 x 64 71 / 78, 26 x 20 70 / 81, 8 x 128 104 / 127
+    int64_t small_total = 0, small_most = 0;
+    for (int z = 0; z < nt; ++z)
+        if (!in_lds[z]) {
+            const int64_t t = (hot_batch->h_n_lookups[z] + SORT_TILE_SMALL - 1) / SORT_TILE_SMALL;
+            small_total += t;
+            small_most = t > small_most ? t : small_most;
+        }
+    const bool direct = passes > 0 && w.tcount != nullptr && small_total <= ctx->n_cu && small_total <= 6 * small_most &&
+                        (ctx->opt_sort == 0 || ctx->opt_sort == 2);
     // Short lists: one kernel per pass (tiles chained through published counts), which saves
     // two launches per pass where launches are what a pass costs.  Long lists keep the
     // three-kernel passes: there the chained kernel's waits cost as much as the launches
