@@ -24,24 +24,46 @@ struct SyncArgs {
 };
 
 typedef float sync_v4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 sync_load(const float4 *p)
+template <bool STREAM> __device__ __forceinline__ float4 sync_load(const float4 *p)
 {
+    if (!STREAM)
+        return *p;
     const sync_v4 v = __builtin_nontemporal_load((const sync_v4 *)p);
     return make_float4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ float sync_load(const float *p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ void sync_store(float4 *p, const float4 &v)
+template <bool STREAM> __device__ __forceinline__ float sync_load(const float *p)
+{
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool STREAM> __device__ __forceinline__ void sync_store(float4 *p, const float4 &v)
 {
     const sync_v4 t = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(t, (sync_v4 *)p);
+    if (STREAM)
+        __builtin_nontemporal_store(t, (sync_v4 *)p);
+    else
+        *p = v;
 }
-__device__ __forceinline__ void sync_store(float *p, float v) { __builtin_nontemporal_store(v, p); }
+template <bool STREAM> __device__ __forceinline__ void sync_store(float *p, float v)
+{
+    if (STREAM)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
+// Bytes of hot rows from which on both sides are streamed past the caches.  Nothing that is copied is
+// read again by the launch, but the other direction or a training step comes next, and below, the hot rows
+// and their places in the full tables are still in the last-level cache (256 MB) by then.  Both
+// directions, microseconds, cached / streamed: 49 MiB 31.8 / 41.7, 98 MiB 59.4 / 76.2, 146 MiB 93.8 / 111.9,
+// 159 MiB 118.6 / 121.2, 195 MiB 162.9 / 147.1, 391 MiB 316 / 291; one direction and a forward: 98 MiB
+// 44.5 / 50.5, 146 MiB 70.2 / 68.7, 159 MiB 86.9 / 80.9, 195 MiB 95.3 / 84.9 (10 MiB: no difference).
+#define SYNC_STREAM_BYTES (144LL << 20)
 
 // A workgroup takes 1024 consecutive vectors; a vector's row comes from one division per workgroup
-// and a small offset.  Nothing that is copied is read again by the launch, and neither side fits a
-// second-level cache, so both are streamed past it: 0.92 M rows of 64, one direction 102 -> 88 us,
-// 4.6 -> 5.4 TB/s (the addresses alone, without the streaming accesses, changed nothing).
-template <typename V> __global__ __launch_bounds__(SYNC_THREADS) void sync_rows_kernel(SyncArgs a)
+// and a small offset, which shortens the small copies (a division and a walk over the tables per vector
+// before: both directions of 8 x 10 000 rows of 64 41 -> 25 us).  0.92 M rows of 64, streamed, one
+// direction: 102 -> 88 us, 4.6 -> 5.4 TB/s.
+template <typename V, bool STREAM> __global__ __launch_bounds__(SYNC_THREADS) void sync_rows_kernel(SyncArgs a)
 {
     constexpr int VW = sizeof(V) / sizeof(float);
     const int64_t b = blockIdx.x;
@@ -85,11 +107,11 @@ template <typename V> __global__ __launch_bounds__(SYNC_THREADS) void sync_rows_
 #pragma unroll
     for (int k = 0; k < SYNC_UNROLL; ++k)
         if (src[k] >= 0)
-            v[k] = sync_load(from + src[k]);
+            v[k] = sync_load<STREAM>(from + src[k]);
 #pragma unroll
     for (int k = 0; k < SYNC_UNROLL; ++k)
         if (src[k] >= 0)
-            sync_store(to + dst[k], v[k]);
+            sync_store<STREAM>(to + dst[k], v[k]);
     if (bad)
         fae_flag(a.status, FAE_STATUS_ERANGE);
 }
@@ -118,8 +140,9 @@ extern "C" int32_t fae_sync_hot_rows(fae_ctx *ctx, const fae_tables *tables, con
         vec = vec && ((((uintptr_t)h_hotW[z]) | ((uintptr_t)h_W[z])) & 15) == 0;
     }
     const int vw = vec ? 4 : 1;
-    int64_t blocks = 0;
+    int64_t blocks = 0, bytes = 0;
     for (int z = 0; z < nt; ++z) {
+        bytes += h_n_hot[z] * dim * 4;
         a.hotW[z] = h_hotW[z];
         a.W[z] = h_W[z];
         a.hot_ids[z] = h_hot_ids[z];
@@ -139,10 +162,16 @@ extern "C" int32_t fae_sync_hot_rows(fae_ctx *ctx, const fae_tables *tables, con
         return fae_fail(ctx, FAE_EINVAL, "fae_sync_hot_rows: more than 2^31 workgroups; split the call by tables");
     FAE_HIP(ctx, hipSetDevice(ctx->device));
     fae_ktimer kt(ctx, FAE_K_SYNC_ROWS);
-    if (vec)
-        FAE_LAUNCH(ctx, sync_rows_kernel<float4>, dim3((unsigned)blocks), dim3(SYNC_THREADS), 0, ctx->stream, a);
+    const dim3 grid((unsigned)blocks), block(SYNC_THREADS);
+    const bool stream = bytes >= SYNC_STREAM_BYTES;
+    if (vec && stream)
+        FAE_LAUNCH(ctx, (sync_rows_kernel<float4, true>), grid, block, 0, ctx->stream, a);
+    else if (vec)
+        FAE_LAUNCH(ctx, (sync_rows_kernel<float4, false>), grid, block, 0, ctx->stream, a);
+    else if (stream)
+        FAE_LAUNCH(ctx, (sync_rows_kernel<float, true>), grid, block, 0, ctx->stream, a);
     else
-        FAE_LAUNCH(ctx, sync_rows_kernel<float>, dim3((unsigned)blocks), dim3(SYNC_THREADS), 0, ctx->stream, a);
+        FAE_LAUNCH(ctx, (sync_rows_kernel<float, false>), grid, block, 0, ctx->stream, a);
     FAE_LAUNCH_CHECK(ctx);
     return FAE_OK;
 }

@@ -60,6 +60,32 @@ def test_sync_rows_both_directions_bit_exact(dev, dim):
         assert W2d[z].cpu().numpy().tobytes() == W2[z].tobytes()           # the source is not written
 
 
+@pytest.mark.parametrize("dim", [64, 63])  # 16-byte and scalar columns
+@pytest.mark.parametrize("extra", [-1, 0])  # rows of 144 MiB are streamed past the caches, fewer are not
+def test_sync_rows_of_either_kind_of_access(dev, dim, extra):
+    n = -(-(144 << 20) // (4 * dim)) + extra
+    n_hot = [n // 3, 0, n - n // 3]
+    rows = [2 * r + 5 for r in n_hot]
+    gen = torch.Generator(device=dev).manual_seed(dim)
+    hp = HotPath(rows, dim, 0)
+    hp.n_hot = n_hot
+    hp.hot_ids = [torch.randperm(r, device=dev, generator=gen)[:h].sort().values.int() for r, h in zip(rows, n_hot)]
+    hp.hotW = [torch.randn((max(h, 1), dim), device=dev, generator=gen) for h in n_hot]
+    W = [torch.randn((r, dim), device=dev, generator=gen) for r in rows]
+    want = [w.clone() for w in W]
+    for z, h in enumerate(n_hot):
+        want[z][hp.hot_ids[z].long()] = hp.hotW[z][:h]
+    hp.sync_to_full(W)
+    hp.sync()
+    assert all(torch.equal(a, b) for a, b in zip(W, want))
+    for w in W:
+        w.mul_(-2.0)
+    hp.sync_from_full(W)
+    hp.sync()
+    for z, h in enumerate(n_hot):
+        assert torch.equal(hp.hotW[z][:h], W[z][hp.hot_ids[z].long()])
+
+
 def test_sync_rows_reports_bad_ids_and_arguments(dev):
     rows, dim = [100], 8
     ids = np.array([3, 250, 7], dtype=np.int32)                           # 250 is outside the table
