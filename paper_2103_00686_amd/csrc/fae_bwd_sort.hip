@@ -482,8 +482,10 @@ __global__ __launch_bounds__(LSORT_THREADS) void lds_sort_kernel(LsortArgs a)
 // host side
 // ---------------------------------------------------------------------------------
 // Workgroups per small table for the LDS sort: enough parts to occupy the chip, never lists
-// below ~64 lookups (a part of up to 256 is sorted by counting, whose time goes by its length).  part_shift[z]: part of a key = key >> shift; blk_start: prefix of
-// workgroups per table (tables not sorted in LDS get none).  Returns the number of workgroups.
+// below ~64 lookups (a part of up to 256 is sorted by counting, whose time goes by its length; a step of
+// 8 x 1024 lookups, parts down to 512, 256, 128, 64, 32: 19.3, 17.6, 17.6, 17.5, 17.4 us; of 1 x 512: 15.8, 14.6,
+// 14.8, 14.7, 14.1 us).  part_shift[z]: part of a key = key >> shift; blk_start: prefix of workgroups per
+// table (tables not sorted in LDS get none).  Returns the number of workgroups.
 static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fae_batch *hot_batch, const bool *in_lds,
                int n_lds, int32_t *blk_start, int32_t *part_shift, int64_t other_blocks)
 {
