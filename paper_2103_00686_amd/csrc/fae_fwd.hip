@@ -31,11 +31,31 @@ struct FwdArgs {
     int32_t mean;       // divide the pooled sum by the bag's length (bags of one lookup are unaffected)
 };
 
-// Sums of up to FWD_PLAIN_MAX terms are added one after the other (worst case FWD_PLAIN_MAX * 2^-24
+// Sums of up to FWD_PLAIN_MAX terms per lane group are plain ones (worst case FWD_PLAIN_MAX * 2^-24
 // of the sum of their magnitudes, inside the 1e-5 the result is held to); longer sums carry the
 // rounding error along (COMP), so that a bag of thousands of lookups stays as accurate as a short
 // one, also when it adds one popular row over and over, which otherwise drifts one way.
 #define FWD_PLAIN_MAX 128
+
+// A lane group that owns a bag alone adds the rows it has in flight in pairs, FWD_PART rows into one part
+// and the parts up: for a bag of n rows chains of FWD_PART / 4 and n / FWD_PART additions and no more than
+// a wave's lane groups have when they share the bag.  Which of the two a table gets goes by its own average
+// length, and its rounding error should not (bags of 1-6 and one of 120 in forty, dim 16, against 64 bits:
+// one after the other 1.4e-7, shared 6.0e-8, in parts 6.2e-8; dim 64: 1.4e-7, 7.8e-8, 6.2e-8; same time).
+#define FWD_PART 16
+template <typename V, int N> __device__ __forceinline__ void fwd_add_pairs(V &part, V (&v)[N])
+{
+#pragma unroll
+    for (int m = N / 2; m > 0; m /= 2)
+#pragma unroll
+        for (int i = 0; i < m; ++i) {
+            v[i] = v[2 * i];
+            vec_ops<V>::add(v[i], v[2 * i + 1]);
+        }
+    vec_ops<V>::add(part, v[0]);
+}
+// rows of lookups up to `done` of the bag are in: is the part full?
+__device__ __forceinline__ bool fwd_part_full(uint32_t done) { return done % FWD_PART == 0; }
 
 // Adds rows of a bag whose next WIDTH slots are held one per lane by the lanes of a lane group of
 // WIDTH lanes: this group's rows are numbers first, first + STRIDE, ... below count.  UN rows are in
@@ -61,11 +81,39 @@ __device__ __forceinline__ void fwd_add_rows(V &acc, V &lost, const V *W, int sl
     }
 }
 
+// The same for a lane group that owns its bag alone (plain sum): the chunk's rows are done .. of the bag
+template <typename V, int LPR>
+__device__ __forceinline__ void fwd_add_parts(V &acc, V &part, const V *W, int slot, int count, uint32_t done, int ncols, int c, bool active)
+{
+    for (int j = 0; j < count; j += 4) {
+        V v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int sl = __shfl(slot, j + u, LPR); // LPR is a multiple of 4
+            v[u] = (active && j + u < count && sl >= 0) ? W[(int64_t)sl * ncols + c] : vec_ops<V>::zero();
+        }
+        fwd_add_pairs(part, v);
+        if (fwd_part_full(done + j + 4)) {
+            vec_ops<V>::add(acc, part);
+            part = vec_ops<V>::zero();
+        }
+    }
+}
+
+// lane 0's or lane 1's value of a group of one or two lanes (both are active); from: known at compile time
+template <int LPR> __device__ __forceinline__ int fwd_pair_lane(int v, int from)
+{
+    if (LPR == 1)
+        return v;
+    return from == 0 ? __builtin_amdgcn_mov_dpp(v, 0xA0, 0xf, 0xf, false)  // lanes 0, 0, 2, 2 of every four
+                     : __builtin_amdgcn_mov_dpp(v, 0xF5, 0xf, 0xf, false); // lanes 1, 1, 3, 3
+}
+
 // The same for a lane group of one or two lanes, which takes eight lookups at a time, j0 .. j0 + 7:
 // a lane reads 8 / LPR consecutive slots at once, lookup e is in register e % PER of lane e / PER, and
 // the eight rows are in flight together.  nl: length of the list (entries behind the bag are read, not used).
 template <typename V, int LPR, bool COMP>
-__device__ __forceinline__ void fwd_add_narrow(V &acc, V &lost, const V *W, const int32_t *slots, uint32_t j0, int count, uint32_t nl,
+__device__ __forceinline__ void fwd_add_narrow(V &acc, V &lost, const V *W, const int32_t *slots, uint32_t j0, int count, uint32_t done, uint32_t nl,
                                                int n_hot, int ncols, int c, uint32_t *status)
 {
     constexpr int PER = 8 / LPR;
@@ -91,15 +139,20 @@ __device__ __forceinline__ void fwd_add_narrow(V &acc, V &lost, const V *W, cons
     V v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const int sl = LPR == 1 ? slot[e % PER] : __shfl(slot[e % PER], e / PER, LPR);
+        const int sl = fwd_pair_lane<LPR>(slot[e % PER], e / PER);
         v[e] = (e < count && sl >= 0 && c < ncols) ? W[(int64_t)sl * ncols + c] : vec_ops<V>::zero();
     }
+    if constexpr (COMP) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        if (!COMP)
-            vec_ops<V>::add(acc, v[e]);
-        else if (e < count)
-            vec_ops<V>::add_comp(acc, lost, v[e]);
+        for (int e = 0; e < 8; ++e)
+            if (e < count)
+                vec_ops<V>::add_comp(acc, lost, v[e]);
+    } else {
+        fwd_add_pairs(lost, v); // the part
+    }
+    if (!COMP && fwd_part_full(done + 8)) {
+        vec_ops<V>::add(acc, lost);
+        lost = vec_ops<V>::zero();
     }
 }
 
@@ -128,13 +181,12 @@ __device__ __forceinline__ int fwd_slot(const int32_t *slots, uint32_t j, uint32
 //   3 tables with bags of up to 100 and a one-hot one, 6007 samples, dim 100: 9 + 28.7 -> 27.2 us
 //   3 tables of short bags and 2 one-hot ones, 3001 samples, dim 20: 4.7 + 11.9 -> 9.1 us
 // A group of one or two lanes would get one or two rows out of such a load, so it reads eight slots at a
-// time (fwd_add_narrow), which takes a few registers more at LPR 2 than eight waves per SIMD leave (with
-// spills 12.2 us for 3 x 32 768 bags of 1-10, dim 8, without 10.5).  Bags of 1-100 in five tables, 65 536 samples:
-//   dim 2 (LPR 2, scalar): 172 -> 103 us; dim 8 (LPR 2): 228 -> 140 us (four slots and rows in turn: 185 us)
-//   3 tables, 2048 samples, dim 4 (LPR 1): 53.6 -> 24.2 us (31.4 us); dim 1: 35.9 -> 18.1 us (17.1 us)
-// Groups of four keep one slot per lane: the registers of eight cost the wave mapping more (84 -> 89 us for
-// five tables of 32 768 bags of 1-100, dim 16) than the group mapping gains from them (33.3 -> 29.7 us, bags of 1-30).
-template <typename V, int LPR> __global__ __launch_bounds__(256, LPR == 2 ? 7 : 8) void fwd_kernel(FwdArgs a)
+// time (fwd_add_narrow).  One slot per lane / four slots and rows in turn / now, microseconds:
+//   five tables, 65 536 bags of 1-100: dim 2 (LPR 2, scalar) 174 / 130 / 92; dim 8 (LPR 2) 228 / 184 / 139
+//   three tables, 2048 bags of 1-100: dim 4 (LPR 1) 53 / 31 / 24, dim 1 35.4 / 17.1 / 15.1
+// Groups of four keep one slot per lane: with eight rows in flight the kernel takes the wave mapping more
+// (84 -> 89 us for five tables of 32 768 bags of 1-100, dim 16) than the group mapping gains (33.3 -> 29.7 us, bags of 1-30).
+template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_kernel(FwdArgs a)
 {
     const int z = fae_find_table(a.blk_start, a.n_tables, blockIdx.x);
     const int bl = blockIdx.x - a.blk_start[z];
@@ -162,20 +214,19 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, LPR == 2 ? 7 : 
     const int ncols = a.dim / (int)(sizeof(V) / sizeof(float));
     const V *W = (const V *)a.W[z];
     const int n_hot = a.n_hot[z];
-    V *o = (V *)(a.out + s * a.out_stride + (int64_t)z * a.dim);
     if (wave) {
         if (!in)
             return;
-        for (int c0 = 0; c0 < ncols; c0 += LPR) {
+        for (int c0 = 0; c0 == 0 || (LPR == FAE_WAVE && c0 < ncols); c0 += LPR) { // fewer lanes: the row is no wider than they are
             const int c = c0 + l;
             V acc = vec_ops<V>::zero(), lost = vec_ops<V>::zero();
             for (uint32_t j0 = beg; j0 < (uint32_t)end; j0 += FAE_WAVE) {
                 const int slot = fwd_slot(slots, j0 + lane, end, n_hot, a.status);
                 const int count = end - j0 < FAE_WAVE ? (int)(end - j0) : FAE_WAVE;
                 if (end - beg > FWD_PLAIN_MAX * G) // the same for the whole wave
-                    fwd_add_rows<V, FAE_WAVE, G, 4, true>(acc, lost, W, slot, g, count, ncols, c, c < ncols);
+                    fwd_add_rows<V, FAE_WAVE, G, (LPR < 4 ? LPR : 4), true>(acc, lost, W, slot, g, count, ncols, c, c < ncols);
                 else
-                    fwd_add_rows<V, FAE_WAVE, G, (G <= 2 ? 8 : 4), false>(acc, lost, W, slot, g, count, ncols, c, c < ncols);
+                    fwd_add_rows<V, FAE_WAVE, G, (LPR < 4 ? LPR : G <= 2 ? 8 : 4), false>(acc, lost, W, slot, g, count, ncols, c, c < ncols);
             }
             // combine the lane groups (all 64 lanes take part in the shuffles)
 #pragma unroll
@@ -184,32 +235,36 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, LPR == 2 ? 7 : 
             if (a.mean && end - beg > 1)
                 vec_ops<V>::scale(acc, 1.0f / (float)(end - beg));
             if (g == 0 && c < ncols)
-                o[c] = acc;
+                ((V *)(a.out + s * a.out_stride + (int64_t)z * a.dim))[c] = acc;
         }
     } else {
-        for (int c0 = 0; c0 < ncols; c0 += LPR) {
+        for (int c0 = 0; c0 == 0 || (LPR == FAE_WAVE && c0 < ncols); c0 += LPR) { // fewer lanes: the row is no wider than they are
             const int c = c0 + l;
             V acc = vec_ops<V>::zero(), lost = vec_ops<V>::zero();
-            constexpr int CHUNK = LPR < 4 ? 8 : LPR;
-            for (uint32_t j0 = beg; j0 < (uint32_t)end; j0 += CHUNK) { // a lane group leaves as a whole
-                const int count = end - j0 < CHUNK ? (int)(end - j0) : CHUNK;
-                if constexpr (LPR < 4) {
+            if constexpr (LPR < 4) {
+                for (uint32_t j0 = beg; j0 < (uint32_t)end; j0 += 8) { // a lane group leaves as a whole
+                    const int count = end - j0 < 8 ? (int)(end - j0) : 8;
                     if (end - beg > FWD_PLAIN_MAX)
-                        fwd_add_narrow<V, LPR, true>(acc, lost, W, slots, j0, count, a.n_lookups[z], n_hot, ncols, c, a.status);
+                        fwd_add_narrow<V, LPR, true>(acc, lost, W, slots, j0, count, j0 - beg, a.n_lookups[z], n_hot, ncols, c, a.status);
                     else
-                        fwd_add_narrow<V, LPR, false>(acc, lost, W, slots, j0, count, a.n_lookups[z], n_hot, ncols, c, a.status);
-                } else {
+                        fwd_add_narrow<V, LPR, false>(acc, lost, W, slots, j0, count, j0 - beg, a.n_lookups[z], n_hot, ncols, c, a.status);
+                }
+            } else {
+                for (uint32_t j0 = beg; j0 < (uint32_t)end; j0 += LPR) { // a lane group leaves as a whole
+                    const int count = end - j0 < LPR ? (int)(end - j0) : LPR;
                     const int slot = fwd_slot(slots, j0 + l, end, n_hot, a.status);
                     if (end - beg > FWD_PLAIN_MAX)
                         fwd_add_rows<V, LPR, 1, 4, true>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
                     else
-                        fwd_add_rows<V, LPR, 1, 4, false>(acc, lost, W, slot, 0, count, ncols, c, c < ncols);
+                        fwd_add_parts<V, LPR>(acc, lost, W, slot, count, j0 - beg, ncols, c, c < ncols);
                 }
             }
+            if (end - beg <= FWD_PLAIN_MAX)
+                vec_ops<V>::add(acc, lost); // the last part
             if (a.mean && end - beg > 1)
                 vec_ops<V>::scale(acc, 1.0f / (float)(end - beg));
             if (in && c < ncols)
-                o[c] = acc;
+                ((V *)(a.out + s * a.out_stride + (int64_t)z * a.dim))[c] = acc;
         }
     }
 }
