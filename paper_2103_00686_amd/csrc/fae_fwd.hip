@@ -37,11 +37,12 @@ struct FwdArgs {
 // one, also when it adds one popular row over and over, which otherwise drifts one way.
 #define FWD_PLAIN_MAX 128
 
-// A lane group that owns a bag alone adds the rows it has in flight in pairs, FWD_PART rows into one part
-// and the parts up: for a bag of n rows chains of FWD_PART / 4 and n / FWD_PART additions and no more than
+// A lane group that owns a bag alone adds the rows it has in flight in pairs, about FWD_PART rows into one
+// part and the parts up: for a bag of n rows chains of FWD_PART / 4 and n / FWD_PART additions, about what
 // a wave's lane groups have when they share the bag.  Which of the two a table gets goes by its own average
 // length, and its rounding error should not (bags of 1-6 and one of 120 in forty, dim 16, against 64 bits:
 // one after the other 1.4e-7, shared 6.0e-8, in parts 6.2e-8; dim 64: 1.4e-7, 7.8e-8, 6.2e-8; same time).
+// A part ends with the slots at hand (LPR rows), with fewer than eight lanes after FWD_PART rows of the bag.
 #define FWD_PART 16
 template <typename V, int N> __device__ __forceinline__ void fwd_add_pairs(V &part, V (&v)[N])
 {
@@ -54,8 +55,11 @@ template <typename V, int N> __device__ __forceinline__ void fwd_add_pairs(V &pa
         }
     vec_ops<V>::add(part, v[0]);
 }
-// rows of lookups up to `done` of the bag are in: is the part full?
-__device__ __forceinline__ bool fwd_part_full(uint32_t done) { return done % FWD_PART == 0; }
+template <typename V> __device__ __forceinline__ void fwd_end_part(V &acc, V &part)
+{
+    vec_ops<V>::add(acc, part);
+    part = vec_ops<V>::zero();
+}
 
 // Adds rows of a bag whose next WIDTH slots are held one per lane by the lanes of a lane group of
 // WIDTH lanes: this group's rows are numbers first, first + STRIDE, ... below count.  UN rows are in
@@ -81,7 +85,7 @@ __device__ __forceinline__ void fwd_add_rows(V &acc, V &lost, const V *W, int sl
     }
 }
 
-// The same for a lane group that owns its bag alone (plain sum): the chunk's rows are done .. of the bag
+// The same for a lane group that owns its bag alone (plain sum); done: rows of the bag that are in already
 template <typename V, int LPR>
 __device__ __forceinline__ void fwd_add_parts(V &acc, V &part, const V *W, int slot, int count, uint32_t done, int ncols, int c, bool active)
 {
@@ -93,11 +97,9 @@ __device__ __forceinline__ void fwd_add_parts(V &acc, V &part, const V *W, int s
             v[u] = (active && j + u < count && sl >= 0) ? W[(int64_t)sl * ncols + c] : vec_ops<V>::zero();
         }
         fwd_add_pairs(part, v);
-        if (fwd_part_full(done + j + 4)) {
-            vec_ops<V>::add(acc, part);
-            part = vec_ops<V>::zero();
-        }
     }
+    if (LPR >= 8 || (done + LPR) % FWD_PART == 0)
+        fwd_end_part(acc, part);
 }
 
 // lane 0's or lane 1's value of a group of one or two lanes (both are active); from: known at compile time
@@ -150,10 +152,8 @@ __device__ __forceinline__ void fwd_add_narrow(V &acc, V &lost, const V *W, cons
     } else {
         fwd_add_pairs(lost, v); // the part
     }
-    if (!COMP && fwd_part_full(done + 8)) {
-        vec_ops<V>::add(acc, lost);
-        lost = vec_ops<V>::zero();
-    }
+    if (!COMP && (done + 8) % FWD_PART == 0)
+        fwd_end_part(acc, lost);
 }
 
 // The lane's slot of a chunk (-1: past the end, or out of range and flagged).  Lookups are numbered
@@ -214,6 +214,7 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_ker
     const int ncols = a.dim / (int)(sizeof(V) / sizeof(float));
     const V *W = (const V *)a.W[z];
     const int n_hot = a.n_hot[z];
+    V *const o = (V *)(a.out + s * a.out_stride + (int64_t)z * a.dim);
     if (wave) {
         if (!in)
             return;
@@ -235,7 +236,7 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_ker
             if (a.mean && end - beg > 1)
                 vec_ops<V>::scale(acc, 1.0f / (float)(end - beg));
             if (g == 0 && c < ncols)
-                ((V *)(a.out + s * a.out_stride + (int64_t)z * a.dim))[c] = acc;
+                o[c] = acc;
         }
     } else {
         for (int c0 = 0; c0 == 0 || (LPR == FAE_WAVE && c0 < ncols); c0 += LPR) { // fewer lanes: the row is no wider than they are
@@ -264,7 +265,7 @@ template <typename V, int LPR> __global__ __launch_bounds__(256, 8) void fwd_ker
             if (a.mean && end - beg > 1)
                 vec_ops<V>::scale(acc, 1.0f / (float)(end - beg));
             if (in && c < ncols)
-                ((V *)(a.out + s * a.out_stride + (int64_t)z * a.dim))[c] = acc;
+                o[c] = acc;
         }
     }
 }
