@@ -16,7 +16,8 @@
  *     by the caller.  The library allocates no user-visible device memory: bulk
  *     scratch comes in through (ws, ws_bytes), sized by the *_workspace_bytes()
  *     queries.  A context owns only one 4 KiB device block and one 4 KiB pinned
- *     host block for status words and scalar read-backs.
+ *     host block for status words and scalar read-backs, and 0.5 MiB of pinned
+ *     host memory for the cutoff's window.
  *   - All kernels are enqueued on the stream given to fae_create().  Calls are
  *     asynchronous unless documented as synchronising.
  *   - Index validation happens on the device: an index outside [0, rows), a slot

@@ -377,17 +377,24 @@ static int32_t fwd_impl(fae_ctx *ctx, const fae_tables *hot_tables, const float 
     a.stream_out = ctx->opt_fwd_stream != 0;
     a.mean = pooling == FAE_POOL_MEAN;
     int n_bags = 0;
+    for (int z = 0; z < nt; ++z)
+        n_bags += a.offsets[z] || ctx->opt_fwd != 0;
+    // A wave per bag pays once a bag keeps every lane group of the wave busy for two rounds.  Eight groups and
+    // more do from one and a half rounds on where a wave for every bag finds room on the chip at once (32 to a
+    // CU) or nearly so: there the longest bag's chain is the time.  Three tables of bags of 1-30, dim 20, us by
+    // wave | by group: 2048 samples 6.5 | 8.2, 3001 7.2 | 9.1, 6007 11.3 | 11.0, 12000 17.9 | 15.3; of 10-20:
+    // 3001 7.1 | 7.5, 4500 8.9 | 8.2; of 1-60, dim 16, 2048: 6.5 | 13.6.  Two groups, bags of 1-5, dim 100,
+    // 3001: 6.3 | 6.0; with four no difference.  With one round: bags of 1-20, dim 32, 4500: 8.3 | 7.1.
+    const double rounds = groups >= 8 && (double)S * n_bags <= 40.0 * ctx->n_cu ? 1.5 : 2.0;
     for (int z = 0; z < nt; ++z) {
         a.kind[z] = FWD_ONEHOT;
         if (a.offsets[z] || ctx->opt_fwd != 0) {
-            // wave-per-bag pays once a bag keeps every lane group of the wave busy for two rounds
-            bool wave = groups > 1 && (double)hot_batch->h_n_lookups[z] >= 2.0 * groups * (double)S;
+            bool wave = groups > 1 && (double)hot_batch->h_n_lookups[z] >= rounds * groups * (double)S;
             if (ctx->opt_fwd == 1)
                 wave = false;
             if (ctx->opt_fwd == 2)
                 wave = groups > 1;
             a.kind[z] = wave ? FWD_WAVE : FWD_GROUP;
-            ++n_bags;
         }
     }
     const bool split = n_bags > 0 && (int64_t)(nt - n_bags) * S * dim * 4 >= FWD_SPLIT_BYTES;

@@ -170,3 +170,32 @@ def test_a_long_bag_among_short_ones_is_as_accurate(dim):
     # pairs of pairs (2 roundings) or of eight (3), up to 16 rows to a part (3 more), the parts: 120 / 16, with
     # eight lanes per row 120 / 8
     assert bool(((out[::40, 0].double() - n * row).abs() <= (6 + n // (8 if dim == 32 else 16) + 1) * 2.0 ** -24 * n * row.abs()).all())
+
+
+@pytest.mark.parametrize("S", [5120, 5121])  # with two tables the last count with a wave from one and a half rounds on
+@pytest.mark.parametrize("dim", [16, 20, 64])  # 16 and 8 lane groups; 4 keep two rounds
+def test_bags_of_one_and_a_half_rounds(dim, S):
+    groups = {16: 16, 20: 8, 64: 4}[dim]
+    rng = np.random.default_rng(S)
+    # one table of exactly 1.5 lookups for each lane group a bag, one of a single lookup less
+    lengths = [rng.integers(0, 3 * groups + 1, S) for _ in range(2)]
+    for ln, n in zip(lengths, [(3 * groups * S + 1) // 2, (3 * groups * S + 1) // 2 - 1]):
+        while ln.sum() != n:
+            d = int(np.sign(n - ln.sum()))
+            i = rng.integers(0, S, abs(int(n - ln.sum())))
+            ln[np.unique(i)] += d
+            np.clip(ln, 0, 3 * groups, out=ln)
+    slots = [torch.from_numpy(rng.integers(0, 900, int(ln.sum()), dtype=np.int32)).cuda() for ln in lengths]
+    offs = [torch.from_numpy(np.concatenate([[0], np.cumsum(ln)]).astype(np.int32)).cuda() for ln in lengths]
+    hp = HotPath([900, 900], dim)
+    hp.alloc_counts()
+    hp.build([0, 0], [900, 900], seed=3)
+    out = hp.forward(HotBatch(S, slots, offs, [int(ln.sum()) for ln in lengths]))
+    hp.sync()
+    for z, ln in enumerate(lengths):
+        w = hp.hotW[z].double()[slots[z].long()]
+        seg = torch.from_numpy(np.repeat(np.arange(S), ln)).cuda()
+        ref = torch.zeros((S, dim), dtype=torch.float64, device="cuda").index_add_(0, seg, w)
+        mag = torch.zeros((S, dim), dtype=torch.float64, device="cuda").index_add_(0, seg, w.abs())
+        # at most 3 * groups rows to a bag, added in no more than that many roundings
+        assert bool(((out[:, z].double() - ref).abs() <= (3 * groups + 1) * 2.0 ** -24 * mag).all()), f"table {z}"

@@ -255,11 +255,10 @@ def test_forward_backward_shapes(dev, variant, dim):
                           (50_000, 3, 2, 0, 0), (300_000, 0, 2, 0, 0), (300_000, 1, 1, 64, 0), (300_000, 3, 1, 0, 1), (300_000, 4, 1, 0, 0),
                           (50_000, 0, 2, 0, 0), (300_000, 0, 2, 64, 1), (300_000, 3, 2, 256, 0)])
 def test_backward_long_runs_and_many_tiles(dev, S_, sort_variant, reduce_variant, span, fixup):
-    """One slot repeated tens of thousands of times (a run that crosses hundreds of spans and, in
-    the key-range sort, a single value larger than the LDS buffers), runs of about two spans,
-    several sort tiles, three radix passes.  50 000 lookups take the key-range sort (or the
-    global passes when forced: 1 = three kernels per pass, 3 = one chained kernel per pass),
-    300 000 the global passes (chained by default at this size)."""
+    """One slot repeated tens of thousands of times (a run that crosses hundreds of spans and
+    several sort tiles), runs of about two spans, three radix passes.  Both lengths take the global passes: 50 000 lookups
+    one direct kernel per pass by default, 300 000 one chained kernel (forced: 1 = three kernels
+    per pass, 3 and 4 = one chained kernel per pass)."""
     rng = np.random.default_rng(7)
     dim, n_hot = 64, 5_000_000
     slots = rng.integers(0, n_hot, S_).astype(np.int32)
