@@ -81,13 +81,14 @@ __device__ __forceinline__ int part_owner(const int *entries, int n, int j)
 // (a whole sector of a cache line each), so a thread keeps PT_LK of them in flight; a
 // tile sees all tables of its samples, so that "some access is cold" needs no cleared array, no
 // store per lookup and no pass of its own, and the position among the hot samples never leaves LDS.
-//   26 one-hot tables, 262 144 samples: 56 us in two kernels, 140 -> 99 us a call (before: 76 us in
+//   26 one-hot tables, 262 144 samples: 50 us in two kernels, 140 -> 94 us a call (before: 76 us in
 //   seven launches: clear, mark, count, scan, lists, offsets, slots; and two waits instead of one)
 // Tables with offsets: the offsets of the tile's samples are put into LDS for as many tables at a time
 // as fit, and the lookups of all of these are walked as one list, so neither a table nor a sample
 // costs a round of its own.  A tile whose lookups are much more than its share (few samples, or a
 // sample with a history far longer than the others') would keep one workgroup busy for long after the rest of the
 // chip has ended; it is left to part_spread_kernel, which takes lookups 2048 at a time whoever owns them.
+//
 // The tables with offsets, in LDS: where the lanes of a wave ask for different tables, an entry of the
 // kernel's arguments is one more dependent load.  The pointers are said to be global: read back from LDS
 // they could otherwise point anywhere.
@@ -123,7 +124,38 @@ struct PartTables {
         }
     }
     __device__ __forceinline__ int row(int c, int j, int wide) const { return fae_load_row((const void *)idx[c], j, wide, rows[c]); }
+    __device__ __forceinline__ const PT_GLOBAL int32_t *offset(int c) const { return offsets[c]; }
+    __device__ __forceinline__ const PT_GLOBAL int32_t *map(int c) const { return remap[c]; }
+    __device__ __forceinline__ PT_GLOBAL int32_t *slot(int c) const { return slots[c]; }
+    __device__ __forceinline__ PT_GLOBAL int32_t *hoffset(int c) const { return hoffsets[c]; }
+    __device__ __forceinline__ int lookup(int c) const { return lookups[c]; }
+    static constexpr int LOADS = PT_LK; // a thread's offsets in flight
+    // the table among c0 .. c0 + nb - 1 that lookup i of the tile is in
+    __device__ __forceinline__ int owner(const int *pre, int nb, int i) const { return part_owner(pre, nb, i); }
 };
+// A single table with offsets: every lane asks for the same entry, so the kernel's arguments do, and neither the
+// tile's lookups before a table nor a barrier for the entries is needed (microseconds a call, as one of several /
+// so: 131 843 samples of bags of 1-39 71.7 / 68.8, 14 000 of 1-3 32.6 / 30.9, beside 25 one-hot tables,
+// 4096 samples 57.4 / 54.8).  With two tables the entries in LDS cost nothing any more (34.6 / 34.6).
+struct PartOne {
+    const PartArgs &a;
+    __device__ __forceinline__ int row(int, int j, int wide) const { return fae_load_row(a.idx[0], j, wide, a.n_rows[0]); }
+    __device__ __forceinline__ const int32_t *offset(int) const { return a.offsets[0]; }
+    __device__ __forceinline__ const int32_t *map(int) const { return a.remap[0]; }
+    __device__ __forceinline__ int32_t *slot(int) const { return a.slots[0]; }
+    __device__ __forceinline__ int32_t *hoffset(int) const { return a.hoffsets[0]; }
+    __device__ __forceinline__ int lookup(int) const { return a.n_lookups[0]; }
+    static constexpr int LOADS = 1; // a tile has no more samples than a workgroup has threads
+    __device__ __forceinline__ int owner(const int *, int, int) const { return 0; }
+};
+
+template <bool ONE> __device__ __forceinline__ const auto &part_tab(const PartTables &all, const PartOne &one)
+{
+    if constexpr (ONE)
+        return one;
+    else
+        return all;
+}
 
 // table of item i (see below); with tiles of whole waves it is the same for every lane, and said so
 // its descriptors are scalar loads
@@ -135,48 +167,49 @@ template <bool WAVE_TILES> __device__ __forceinline__ int part_table(const PartA
 
 // Offsets of the tile's ns samples (and the closing one) of tables c0 .. c0 + nb - 1, T + 1 words apart.
 // Returns whether a sample's are malformed, as far as this thread has seen (CHECK).
-template <bool CHECK>
-__device__ __forceinline__ bool part_load_offsets(const PartArgs &a, const PartTables &tab, int c0, int nb, int s0, int ns, int *s_off)
+template <bool CHECK, typename Tab>
+__device__ __forceinline__ bool part_load_offsets(const PartArgs &a, const Tab &tab, int c0, int nb, int s0, int ns, int *s_off)
 {
     const int T = 1 << a.tile_log, items = nb << a.tile_log;
     bool bad = false;
-    for (int i0 = threadIdx.x; i0 < items; i0 += PT_ROUND) {
-        int v[PT_LK], e[PT_LK];
+    for (int i0 = threadIdx.x; i0 < items; i0 += Tab::LOADS * PT_THREADS) {
+        int v[Tab::LOADS], e[Tab::LOADS];
 #pragma unroll
-        for (int k = 0; k < PT_LK; ++k) { // every load goes out before the first is stored
+        for (int k = 0; k < Tab::LOADS; ++k) { // every load goes out before the first is stored
             const int i = i0 + k * PT_THREADS, s = i & (T - 1);
             v[k] = e[k] = 0;
             if (i < items && s < ns) {
-                const PT_GLOBAL int32_t *off = tab.offsets[c0 + (i >> a.tile_log)] + s0 + s;
+                const auto *off = tab.offset(c0 + (i >> a.tile_log)) + s0 + s;
                 v[k] = off[0];
                 if (CHECK)
                     e[k] = off[1];
             }
         }
 #pragma unroll
-        for (int k = 0; k < PT_LK; ++k) {
+        for (int k = 0; k < Tab::LOADS; ++k) {
             const int i = i0 + k * PT_THREADS, s = i & (T - 1), c = i >> a.tile_log;
             if (i < items && s < ns) {
                 s_off[c * (T + 1) + s] = v[k];
                 if (CHECK)
-                    (void)part_len(v[k], e[k], tab.lookups[c0 + c], a.n_samples, s0 + s, &bad);
+                    (void)part_len(v[k], e[k], tab.lookup(c0 + c), a.n_samples, s0 + s, &bad);
             }
         }
     }
     if (threadIdx.x < nb)
-        s_off[threadIdx.x * (T + 1) + ns] = tab.offsets[c0 + threadIdx.x][s0 + ns];
+        s_off[threadIdx.x * (T + 1) + ns] = tab.offset(c0 + threadIdx.x)[s0 + ns];
     return bad;
 }
 
 // s_pre[c] = lookups of the tile in the tables before c of c0 .. c0 + nb - 1; returns those of all of them.
 // Called by one wave.  A table with more than limit, which is at most 2^24, counts as limit + 1, so that the sum
 // stays in range; a malformed one as none.
-__device__ __forceinline__ int part_prefix(const PartTables &tab, int c0, int nb, int s0, int ns, int limit, int *s_pre)
+template <typename Tab>
+__device__ __forceinline__ int part_prefix(const Tab &tab, int c0, int nb, int s0, int ns, int limit, int *s_pre)
 {
     const int lane = fae_lane();
     int len = 0;
     if (lane < nb) {
-        const int lo = tab.offsets[c0 + lane][s0], hi = tab.offsets[c0 + lane][s0 + ns];
+        const int lo = tab.offset(c0 + lane)[s0], hi = tab.offset(c0 + lane)[s0 + ns];
         len = lo < 0 || hi < lo ? 0 : hi - lo > limit ? limit + 1 : hi - lo;
     }
     const int incl = fae_wave_incl_scan(len);
@@ -187,12 +220,20 @@ __device__ __forceinline__ int part_prefix(const PartTables &tab, int c0, int nb
     return __shfl(incl, FAE_WAVE - 1, FAE_WAVE);
 }
 
+// the same of a lone table, whose offsets are in LDS
+__device__ __forceinline__ int part_lone_lookups(const int *s_off, int ns, int limit)
+{
+    const int lo = s_off[0], hi = s_off[ns];
+    return lo < 0 || hi < lo ? 0 : hi - lo > limit ? limit + 1 : hi - lo;
+}
+
 #define PT_ROWS 4 // rows of counts that a wave takes together: their loads and sums do not depend on one another
 
 // The tile's counts: hot samples, then the hot lookups of each table with offsets.  (In a heavy tile a
 // sample counts as hot until the spread kernel finds a cold access of it, and takes it out of the counts.)
 // held: offsets of every table in LDS, or null
-__device__ __forceinline__ void part_count(const PartArgs &a, const PartTables &tab, int tile, const uint32_t *s_cold, const int *held)
+template <typename Tab>
+__device__ __forceinline__ void part_count(const PartArgs &a, const Tab &tab, int tile, const uint32_t *s_cold, const int *held)
 {
     const int T = 1 << a.tile_log, s0 = tile << a.tile_log;
     const int ns = a.n_samples - s0 < T ? a.n_samples - s0 : T;
@@ -229,7 +270,8 @@ __device__ __forceinline__ void part_count(const PartArgs &a, const PartTables &
 }
 
 // takes the n listed samples of heavy tiles, which counted as hot, out of their tiles' counts
-__device__ __forceinline__ void part_uncount(const PartArgs &a, const PartTables &tab, const int *samples, int n)
+template <typename Tab>
+__device__ __forceinline__ void part_uncount(const PartArgs &a, const Tab &tab, const int *samples, int n)
 {
     const int rows = 1 + a.n_csr;
     for (int i = threadIdx.x; i < n * rows; i += PT_THREADS) {
@@ -237,18 +279,20 @@ __device__ __forceinline__ void part_uncount(const PartArgs &a, const PartTables
         bool ignored = false;
         int len = 1;
         if (row > 0)
-            len = part_len(tab.offsets[z][s], tab.offsets[z][s + 1], tab.lookups[z], a.n_samples, s, &ignored);
+            len = part_len(tab.offset(z)[s], tab.offset(z)[s + 1], tab.lookup(z), a.n_samples, s, &ignored);
         if (len > 0)
             atomicSub(a.tile_sums + (int64_t)row * a.n_tiles + (s >> a.tile_log), len);
     }
 }
 
-template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8) void part_classify_kernel(PartArgs a)
+template <bool WAVE_TILES, bool BAGS, bool ONE = false> __global__ __launch_bounds__(PT_THREADS, 8) void part_classify_kernel(PartArgs a)
 {
     __shared__ uint32_t s_cold[PT_MAX_TILE];
     __shared__ int s_off[PT_OFF_WORDS];
     __shared__ int s_pre[FAE_MAX_TABLES + 1];
     __shared__ PartTables s_tab;
+    const PartOne one{a};
+    const auto &tab = part_tab<ONE>(s_tab, one);
     __shared__ int s_bad, s_heavy;
     const int T = 1 << a.tile_log, s0 = blockIdx.x << a.tile_log;
     const int ns = a.n_samples - s0 < T ? a.n_samples - s0 : T;
@@ -257,7 +301,7 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
     s_cold[t] = 0u;
     if (t == 0)
         s_bad = s_heavy = 0;
-    if (BAGS)
+    if (BAGS && !ONE)
         s_tab.fill(a);
     __syncthreads();
     const int nb_max = PT_OFF_WORDS / (T + 1);
@@ -292,20 +336,23 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
         }
     }
     if constexpr (BAGS) {
-        if (t >= PT_THREADS - FAE_WAVE) { // the wave that has offsets to load last
-            const int total = part_prefix(s_tab, 0, a.n_csr, s0, ns, a.heavy_min, s_pre);
+        if (!ONE && t >= PT_THREADS - FAE_WAVE) { // the wave that has offsets to load last
+            const int total = part_prefix(tab, 0, a.n_csr, s0, ns, a.heavy_min, s_pre);
             if (t == PT_THREADS - 1)
                 s_heavy = total > a.heavy_min;
         }
         for (int c0 = 0; c0 < a.n_csr; c0 += nb_max) {
             const int nb = a.n_csr - c0 < nb_max ? a.n_csr - c0 : nb_max;
             // a sample's offsets are checked whether it is hot or cold
-            if (part_load_offsets<true>(a, s_tab, c0, nb, s0, ns, s_off))
+            if (part_load_offsets<true>(a, tab, c0, nb, s0, ns, s_off))
                 s_bad = 1;
             __syncthreads();
-            if (s_bad == 0 && s_heavy == 0) { // a malformed tile is not walked: the call reports it
-                const int total = s_pre[c0 + nb]; // s_pre: over all tables
-                for (int i0 = s_pre[c0] + t; i0 < total; i0 += PT_ROUND) {
+            const int from = ONE ? 0 : s_pre[c0]; // s_pre: over all tables
+            const int total = ONE ? part_lone_lookups(s_off, ns, a.heavy_min) : s_pre[c0 + nb];
+            if (ONE && t == 0)
+                s_heavy = total > a.heavy_min; // read again behind the next barrier only
+            if (s_bad == 0 && (ONE ? total <= a.heavy_min : s_heavy == 0)) { // a malformed tile is not walked: the call reports it
+                for (int i0 = from + t; i0 < total; i0 += PT_ROUND) {
                     int r[PT_LK], m[PT_LK], c[PT_LK], j[PT_LK];
 #pragma unroll
                     for (int k = 0; k < PT_LK; ++k) {
@@ -314,14 +361,14 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
                         c[k] = 0;
                         j[k] = 0;
                         if (i < total) {
-                            c[k] = part_owner(s_pre + c0, nb, i);
-                            j[k] = s_off[c[k] * (T + 1)] + (i - s_pre[c0 + c[k]]);
-                            r[k] = s_tab.row(c0 + c[k], j[k], a.wide);
+                            c[k] = tab.owner(s_pre + c0, nb, i);
+                            j[k] = s_off[c[k] * (T + 1)] + (i - (ONE ? 0 : s_pre[c0 + c[k]]));
+                            r[k] = tab.row(c0 + c[k], j[k], a.wide);
                         }
                     }
 #pragma unroll
                     for (int k = 0; k < PT_LK; ++k)
-                        m[k] = r[k] >= 0 ? s_tab.remap[c0 + c[k]][r[k]] : -1;
+                        m[k] = r[k] >= 0 ? tab.map(c0 + c[k])[r[k]] : -1;
 #pragma unroll
                     for (int k = 0; k < PT_LK; ++k) {
                         if (r[k] == -2)
@@ -348,7 +395,7 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
                 *a.any_heavy = a.stamp; // every writer stores the same value
         }
     }
-    part_count(a, s_tab, blockIdx.x, s_cold, BAGS && held ? s_off : nullptr);
+    part_count(a, tab, blockIdx.x, s_cold, BAGS && held ? s_off : nullptr);
 }
 
 // Lookups of the heavy tiles: a workgroup takes a round of PT_ROUND consecutive lookups of a table,
@@ -500,7 +547,7 @@ __global__ __launch_bounds__(PT_THREADS, 8) void part_spread_kernel(PartArgs a)
     part_spread<false>(a, blockIdx.x, gridDim.x, s_off, s_dst, s_list, s_red, s_tab);
 }
 
-template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8) void part_emit_kernel(PartArgs a)
+template <bool WAVE_TILES, bool BAGS, bool ONE, bool SPREAD> __global__ __launch_bounds__(PT_THREADS, 8) void part_emit_kernel(PartArgs a)
 {
     __shared__ int lds[PT_THREADS / FAE_WAVE + 1];
     __shared__ int s_base[FAE_MAX_TABLES + 1]; // per row: what the tiles before this one hold
@@ -508,8 +555,10 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
     __shared__ int s_off[PT_OFF_WORDS], s_dst[PT_OFF_WORDS]; // of a sample: its first lookup, and its first hot one
     __shared__ int s_pre[FAE_MAX_TABLES + 1];
     __shared__ PartTables s_tab;
+    const PartOne one{a};
+    const auto &tab = part_tab<ONE>(s_tab, one);
     static_assert(PT_OFF_WORDS > PT_SLAB, "the spread part uses the same room");
-    if (BAGS && blockIdx.x >= (unsigned)a.n_tiles) {
+    if (SPREAD && blockIdx.x >= (unsigned)a.n_tiles) {
         part_spread<true>(a, blockIdx.x - a.n_tiles, gridDim.x - a.n_tiles, s_off, s_dst, nullptr, lds, s_tab);
         return;
     }
@@ -520,7 +569,7 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
     const int state = BAGS ? a.tile_state[tile] : PT_LIGHT;
     const bool leave = BAGS && a.leave && *a.any_heavy == a.stamp;
     const int nb_max = PT_OFF_WORDS / (T + 1);
-    if (BAGS)
+    if (BAGS && !ONE)
         s_tab.fill(a);
     // what the tiles before this one hold
     const int w = __builtin_amdgcn_readfirstlane(t / FAE_WAVE);
@@ -558,10 +607,11 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
         }
     }
     if constexpr (BAGS) {
-        __syncthreads();
-        if (t >= PT_THREADS - FAE_WAVE)
-            (void)part_prefix(s_tab, 0, a.n_csr, s0, ns, a.heavy_min, s_pre);
-        (void)part_load_offsets<false>(a, s_tab, 0, a.n_csr < nb_max ? a.n_csr : nb_max, s0, ns, s_off);
+        if (!ONE)
+            __syncthreads();
+        if (!ONE && t >= PT_THREADS - FAE_WAVE)
+            (void)part_prefix(tab, 0, a.n_csr, s0, ns, a.heavy_min, s_pre);
+        (void)part_load_offsets<false>(a, tab, 0, a.n_csr < nb_max ? a.n_csr : nb_max, s0, ns, s_off);
     }
     int n_here;
     const int pos = fae_block_excl_scan<PT_THREADS>(hot ? 1 : 0, lds, &n_here); // its barriers also publish s_base
@@ -617,12 +667,12 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
         for (int c0 = 0; c0 < a.n_csr; c0 += nb_max) {
             const int nb = a.n_csr - c0 < nb_max ? a.n_csr - c0 : nb_max;
             if (c0 > 0) {
-                (void)part_load_offsets<false>(a, s_tab, c0, nb, s0, ns, s_off);
+                (void)part_load_offsets<false>(a, tab, c0, nb, s0, ns, s_off);
                 __syncthreads();
             }
             // where a sample's hot lookups go: `lanes` lanes per table, each with `per` consecutive samples
             for (int c = t / lanes; c < nb; c += PT_THREADS / lanes) {
-                const int z = c0 + c, nl = s_tab.lookups[z], l = t & (lanes - 1);
+                const int z = c0 + c, nl = tab.lookup(z), l = t & (lanes - 1);
                 int len[PT_MAX_TILE / FAE_WAVE], own = 0;
 #pragma unroll
                 for (int q = 0; q < PT_MAX_TILE / FAE_WAVE; ++q) {
@@ -645,18 +695,19 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
                     if (q < per && s < ns) {
                         s_dst[c * (T + 1) + s] = at;
                         if (s_hot[s] >= 0)
-                            s_tab.hoffsets[z][h0 + s_hot[s]] = at;
+                            tab.hoffset(z)[h0 + s_hot[s]] = at;
                     }
                     at += len[q];
                 }
                 if (last && l == lanes - 1) {
-                    s_tab.hoffsets[z][h0 + n_here] = at;
+                    tab.hoffset(z)[h0 + n_here] = at;
                     a.scalars[1 + a.number[z]] = (uint32_t)at;
                 }
             }
             __syncthreads();
-            const int total = state == PT_LIGHT && n_here > 0 ? s_pre[c0 + nb] : 0;
-            for (int i0 = s_pre[c0] + t; i0 < total; i0 += PT_ROUND) {
+            const int from = ONE ? 0 : s_pre[c0];
+            const int total = state != PT_LIGHT || n_here == 0 ? 0 : ONE ? part_lone_lookups(s_off, ns, a.heavy_min) : s_pre[c0 + nb];
+            for (int i0 = from + t; i0 < total; i0 += PT_ROUND) {
                 static_assert(FAE_MAX_TABLES <= 256, "a table's number fits a byte");
                 uint32_t tables[PT_LK / 4] = {}; // a byte each: as words they cost the eighth wave per SIMD
                 int r[PT_LK], dst[PT_LK], m[PT_LK];
@@ -666,24 +717,24 @@ template <bool WAVE_TILES, bool BAGS> __global__ __launch_bounds__(PT_THREADS, 8
                     r[k] = dst[k] = -1;
                     if (i >= total)
                         continue;
-                    const int c = part_owner(s_pre + c0, nb, i);
+                    const int c = tab.owner(s_pre + c0, nb, i);
                     const int *o = s_off + c * (T + 1);
-                    const int j = o[0] + (i - s_pre[c0 + c]);
+                    const int j = o[0] + (i - (ONE ? 0 : s_pre[c0 + c]));
                     const int s = part_owner(o, ns, j);
                     if (s_hot[s] >= 0) {
                         tables[k / 4] |= (uint32_t)(c0 + c) << (k % 4 * 8);
                         dst[k] = s_dst[c * (T + 1) + s] + (j - o[s]);
-                        r[k] = s_tab.row(c0 + c, j, a.wide);
+                        r[k] = tab.row(c0 + c, j, a.wide);
                     }
                 }
 #pragma unroll
                 for (int k = 0; k < PT_LK; ++k)
-                    m[k] = r[k] >= 0 ? s_tab.remap[tables[k / 4] >> (k % 4 * 8) & 0xff][r[k]] : -1;
+                    m[k] = r[k] >= 0 ? tab.map(tables[k / 4] >> (k % 4 * 8) & 0xff)[r[k]] : -1;
 #pragma unroll
                 for (int k = 0; k < PT_LK; ++k) {
                     const int z = tables[k / 4] >> (k % 4 * 8) & 0xff;
-                    if (r[k] >= 0 && dst[k] >= 0 && dst[k] < s_tab.lookups[z])
-                        s_tab.slots[z][dst[k]] = m[k];
+                    if (r[k] >= 0 && dst[k] >= 0 && dst[k] < tab.lookup(z))
+                        tab.slot(z)[dst[k]] = m[k];
                 }
             }
             __syncthreads(); // s_off and s_dst are filled again for the next tables
@@ -813,12 +864,16 @@ extern "C" int32_t fae_partition_batch(fae_ctx *ctx, const fae_tables *tables, c
     a.status = ctx->d_block;
     a.scalars = ctx->d_block + FAE_BLK_SCALARS;
     const dim3 grid((unsigned)tiles), block(PT_THREADS);
-    const bool wave_tiles = log >= 6;
+    const bool wave_tiles = log >= 6, one_bag = a.n_csr == 1;
     for (bool again = false;; again = true) {
         const dim3 spread_grid((unsigned)std::min<int64_t>(rounds, 8LL * ctx->n_cu)), emit_grid(grid.x + (spread ? spread_grid.x : 0u));
         if (!again || a.scanned) { // the counts are still there, or have become running totals
             fae_ktimer kt(ctx, FAE_K_PARTITION);
-            if (bags && wave_tiles)
+            if (one_bag && wave_tiles)
+                FAE_LAUNCH(ctx, (part_classify_kernel<true, true, true>), grid, block, 0, ctx->stream, a);
+            else if (one_bag)
+                FAE_LAUNCH(ctx, (part_classify_kernel<false, true, true>), grid, block, 0, ctx->stream, a);
+            else if (bags && wave_tiles)
                 FAE_LAUNCH(ctx, (part_classify_kernel<true, true>), grid, block, 0, ctx->stream, a);
             else if (bags)
                 FAE_LAUNCH(ctx, (part_classify_kernel<false, true>), grid, block, 0, ctx->stream, a);
@@ -840,14 +895,23 @@ extern "C" int32_t fae_partition_batch(fae_ctx *ctx, const fae_tables *tables, c
         }
         {
             fae_ktimer kt(ctx, FAE_K_PARTITION);
-            if (bags && wave_tiles)
-                FAE_LAUNCH(ctx, (part_emit_kernel<true, true>), emit_grid, block, 0, ctx->stream, a);
+            // the spread part costs the tiles registers (five spilled): only where it is launched
+            if (spread && wave_tiles)
+                FAE_LAUNCH(ctx, (part_emit_kernel<true, true, false, true>), emit_grid, block, 0, ctx->stream, a);
+            else if (spread)
+                FAE_LAUNCH(ctx, (part_emit_kernel<false, true, false, true>), emit_grid, block, 0, ctx->stream, a);
+            else if (one_bag && wave_tiles)
+                FAE_LAUNCH(ctx, (part_emit_kernel<true, true, true, false>), grid, block, 0, ctx->stream, a);
+            else if (one_bag)
+                FAE_LAUNCH(ctx, (part_emit_kernel<false, true, true, false>), grid, block, 0, ctx->stream, a);
+            else if (bags && wave_tiles)
+                FAE_LAUNCH(ctx, (part_emit_kernel<true, true, false, false>), grid, block, 0, ctx->stream, a);
             else if (bags)
-                FAE_LAUNCH(ctx, (part_emit_kernel<false, true>), emit_grid, block, 0, ctx->stream, a);
+                FAE_LAUNCH(ctx, (part_emit_kernel<false, true, false, false>), grid, block, 0, ctx->stream, a);
             else if (wave_tiles)
-                FAE_LAUNCH(ctx, (part_emit_kernel<true, false>), emit_grid, block, 0, ctx->stream, a);
+                FAE_LAUNCH(ctx, (part_emit_kernel<true, false, false, false>), grid, block, 0, ctx->stream, a);
             else
-                FAE_LAUNCH(ctx, (part_emit_kernel<false, false>), emit_grid, block, 0, ctx->stream, a);
+                FAE_LAUNCH(ctx, (part_emit_kernel<false, false, false, false>), grid, block, 0, ctx->stream, a);
             FAE_LAUNCH_CHECK(ctx);
         }
         const int32_t now = fae_readback_status(ctx, nt + 1);

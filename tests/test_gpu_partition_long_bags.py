@@ -114,6 +114,62 @@ def test_a_bad_long_bag_is_refused(what):
         run()
 
 
+@pytest.mark.parametrize("over", [0, 1])  # lookups above the most that a tile walks itself
+@pytest.mark.parametrize("S,bits", [(5, 32), (2047, 64), (40_000, 32), (131_073, 64)])
+def test_a_lone_table_of_bags(S, bits, over):
+    rng = np.random.default_rng(S)
+    n_cu, log = torch.cuda.get_device_properties(0).multi_processor_count, 4
+    while (S + (1 << log) - 1) >> log > 8 * n_cu:
+        log += 1
+    tiles, tile = (S + (1 << log) - 1) >> log, (S // 2) >> log << log
+    ln = rng.integers(0, 7, S)
+
+    def above(n):  # lookups of the tile beyond its limit, with a bag of n in it
+        ln[tile] = n
+        share = int(ln.sum()) // tiles
+        limit = max(int(ln.sum()) // (2 * n_cu), 4096)
+        return int(ln[tile:tile + (1 << log)].sum()) - (limit if share > limit else limit + 2 * share)
+    lo, hi = 0, 100_000
+    if above(hi) > over:
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            lo, hi = (mid, hi) if above(mid) <= over else (lo, mid)
+    above(lo)
+    idx, remap = [rng.integers(0, 5000, int(ln.sum()))], [np.where(rng.random(5000) < 0.01, -1, np.arange(5000)).astype(np.int32)]
+    run, out = _call(S, [ln], idx, remap, bits)
+    owner = np.repeat(np.arange(S), ln)
+    is_hot = np.ones(S, dtype=bool)
+    is_hot[owner[remap[0][idx[0]] < 0]] = False
+    ref = remap[0][idx[0][is_hot[owner]]]
+    for _ in range(2):
+        n_hot, nl = run()
+        assert n_hot == is_hot.sum() and int(nl[0]) == ref.size
+        assert np.array_equal(out[0].cpu().numpy()[:n_hot], np.flatnonzero(is_hot))
+        assert np.array_equal(out[1].cpu().numpy()[:S - n_hot], np.flatnonzero(~is_hot))
+        assert np.array_equal(out[2][0].cpu().numpy()[:ref.size], ref)
+        assert np.array_equal(out[3][0].cpu().numpy()[:n_hot + 1], np.concatenate([[0], np.cumsum(ln[is_hot])]))
+
+
+@pytest.mark.parametrize("what", ["id", "falls", "first", "past", "last"])
+def test_a_bad_short_bag_of_a_lone_table_is_refused(what):
+    S, rows = 3000, 1000
+    ln = np.full(S, 3)
+    idx, off = np.zeros(3 * S, dtype=np.int64), np.arange(S + 1) * 3
+    if what == "id":
+        idx[4321] = -1
+    elif what == "falls":
+        off[1600] = off[1602]
+    elif what == "first":
+        off[0] = -1
+    elif what == "past":
+        off[1601] = 3 * S + 1
+    else:
+        off[S] = 3 * S - 1
+    run, _ = _call(S, [ln], [idx], [np.arange(rows, dtype=np.int32)], 32, [off])
+    with pytest.raises(B.FaeError, match="out of range or a malformed CSR"):
+        run()
+
+
 def test_time_goes_by_the_lookups_and_not_by_who_owns_them():
     """Four million lookups: in equal bags, in sixteen bags, and nearly all in one bag.  A workgroup that
     walks a long bag by itself takes a hundred times as long."""
