@@ -55,15 +55,14 @@ template <> __device__ __forceinline__ float4 bwd_shfl<float4>(const float4 &v, 
 template <> __device__ __forceinline__ float bwd_shfl<float>(const float &v, int src) { return __shfl(v, src, FAE_WAVE); }
 
 // A slice of a border sum that another workgroup of the same launch reads: stored and loaded
-// word by word with device-scope atomics, which go past the caches that are private to a part
-// of the chip.  (Between two launches plain accesses are enough.)
+// with device-scope atomics, eight bytes at a time where the slice has them, which go past the
+// caches that are private to a part of the chip.  (Between two launches plain accesses are enough.)
 __device__ __forceinline__ void bwd_store_shared(float4 *p, const float4 &v)
 {
-    float *f = (float *)p;
-    __hip_atomic_store(f + 0, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(f + 1, v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(f + 2, v.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(f + 3, v.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t w[2];
+    __builtin_memcpy(w, &v, sizeof(w));
+    __hip_atomic_store((uint64_t *)p, w[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store((uint64_t *)p + 1, w[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void bwd_store_shared(float *p, const float &v)
 {
@@ -71,11 +70,11 @@ __device__ __forceinline__ void bwd_store_shared(float *p, const float &v)
 }
 __device__ __forceinline__ float4 bwd_load_shared(const float4 *p)
 {
-    const float *f = (const float *)p;
-    return make_float4(__hip_atomic_load(f + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                       __hip_atomic_load(f + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                       __hip_atomic_load(f + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                       __hip_atomic_load(f + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const uint64_t w[2] = {__hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                           __hip_atomic_load((const uint64_t *)p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+    float4 v;
+    __builtin_memcpy(&v, w, sizeof(v));
+    return v;
 }
 __device__ __forceinline__ float bwd_load_shared(const float *p)
 {
@@ -167,56 +166,50 @@ __device__ __forceinline__ void bwd_finish_borders(const BwdArgs &a, const SpanI
         if (cnt < FAE_WAVE)
             break;
     }
-    // pieces 0 .. n_back-1: whole-span sums of spans sid-1-t; piece n_back: tail sum of the span the run began in
+    // Pieces 0 .. n_back-1: whole-span sums of spans sid-1-t; piece n_back: tail sum of the span the run
+    // began in.  64 of them at a time: every lane polls the flag of one, then each lane group fetches its
+    // pieces (every G-th one) PB at a time.  A popular row has a run over a hundred spans and more, and the
+    // wave that closes it is the launch's last, so its round trips are the launch's time: with four flags and
+    // then four rows per lane group in turn, 208 K lookups of 32 floats (runs over 160 spans) 19.2 -> 15.8 us,
+    // 111 K of 20 with Adagrad 17.0 -> 15.1, 263 K of 100 43.4 -> 33.8.  Asking for the weight row and the keys
+    // behind n_back ahead of the span's rows gave nothing (15.8 -> 16.5, 33.8 -> 34.7 us: registers).
     V acc = bwd_vec<V>::zero();
-    constexpr int PB = 4; // pieces whose flags, then whose rows, are fetched together
-    bool gave_up = false;
-    for (int t0 = g; t0 <= n_back; t0 += PB * G) {
+    constexpr int PB = 8;
+    for (int t0 = 0; t0 <= n_back; t0 += FAE_WAVE) {
+        const int t = t0 + lane;
         int spins = 0;
-        for (;;) { // until the pieces of this round are all published
-            int f[PB];
-#pragma unroll
-            for (int q = 0; q < PB; ++q) {
-                const int t = t0 + q * G;
-                f[q] = t <= n_back ? __hip_atomic_load(&a.flags[sid - 1 - t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1;
-            }
-            bool all = true;
-#pragma unroll
-            for (int q = 0; q < PB; ++q)
-                all = all && f[q] != 0;
-            if (all)
-                break;
+        bool gave_up = false;
+        while (t <= n_back && !gave_up && __hip_atomic_load(&a.flags[sid - 1 - t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
             if (++spins > SWEEP_SPIN_LIMIT) {
                 fae_flag(a.status, FAE_STATUS_EINTERNAL);
                 gave_up = true;
-                break;
+            } else {
+                __builtin_amdgcn_s_sleep(1);
             }
-            __builtin_amdgcn_s_sleep(1);
         }
-        if (gave_up)
-            break;
+        // a wait that gave up: the row (and its accumulator) stays as it was; the status word makes the
+        // next synchronising call report the step as invalid
+        if (__ballot(gave_up) != 0)
+            return;
         if (a.handoff == 1)
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         else
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        V v[PB];
+        const int t1 = t0 + FAE_WAVE - 1 < n_back ? t0 + FAE_WAVE - 1 : n_back; // last piece of this round
+        for (int tb = t0 + g; tb <= t1; tb += PB * G) {
+            V v[PB];
 #pragma unroll
-        for (int q = 0; q < PB; ++q) {
-            const int t = t0 + q * G;
-            v[q] = bwd_vec<V>::zero();
-            if (active && t <= n_back) {
-                const V *row = (const V *)(a.partial + ((int64_t)(sid - 1 - t) * 2 + (t == n_back ? 1 : 0)) * a.dim);
-                v[q] = bwd_load_shared(row + c);
+            for (int q = 0; q < PB; ++q) {
+                const int tq = tb + q * G;
+                v[q] = bwd_vec<V>::zero();
+                if (active && tq <= t1)
+                    v[q] = bwd_load_shared((const V *)(a.partial + ((int64_t)(sid - 1 - tq) * 2 + (tq == n_back ? 1 : 0)) * a.dim) + c);
             }
-        }
 #pragma unroll
-        for (int q = 0; q < PB; ++q)
-            bwd_vec<V>::add(acc, v[q]);
+            for (int q = 0; q < PB; ++q)
+                bwd_vec<V>::add(acc, v[q]);
+        }
     }
-    // a wait that gave up in any lane group: the row (and its accumulator) stays as it was; the
-    // status word makes the next synchronising call report the step as invalid
-    if (__ballot(gave_up) != 0)
-        return;
 #pragma unroll
     for (int mm = LPR; mm < FAE_WAVE; mm <<= 1) {
         const V o = bwd_shfl<V>(acc, lane ^ mm);
