@@ -243,8 +243,8 @@ template <typename V, int UN, bool VAR> struct BwdBatch {
 // UN = steps per batch; the loads of a batch are issued before the batch in front of it is summed
 // (two batches alternate), so a wave always has rows on their way while it works.  VAR = mean
 // pooling or Adagrad may be asked for (the plain kernel carries neither their registers nor
-// their branches).
-template <typename V, int LPR, int UNMAX, bool VAR> __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdArgs a)
+// their branches).  ROLL = the batches of a tile as a loop: fewer registers, a little more to do (see launch_scan).
+template <typename V, int LPR, int UNMAX, bool VAR, bool ROLL = false> __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdArgs a)
 {
     constexpr int G = FAE_WAVE / LPR;              // lane groups = gradient rows per step
     constexpr int VW = sizeof(V) / sizeof(float);
@@ -406,10 +406,7 @@ template <typename V, int LPR, int UNMAX, bool VAR> __global__ __launch_bounds__
             const int n_batch = (sp.pos1 - t0 >= FAE_WAVE) ? NBATCH : ((sp.pos1 - t0) + UN * G - 1) / (UN * G);
             Batch b0, b1;
             issue(b0, 0);
-#pragma unroll
-            for (int ib = 0; ib < NBATCH; ib += 2) {
-                if (ib >= n_batch)
-                    break;
+            auto two = [&](int ib) {
                 if (ib + 1 < NBATCH && ib + 1 < n_batch)
                     issue(b1, (ib + 1) * UN);
                 sum(b0);
@@ -417,6 +414,18 @@ template <typename V, int LPR, int UNMAX, bool VAR> __global__ __launch_bounds__
                     if (ib + 2 < NBATCH && ib + 2 < n_batch)
                         issue(b0, (ib + 2) * UN);
                     sum(b1);
+                }
+            };
+            if constexpr (ROLL) {
+#pragma unroll 1
+                for (int ib = 0; ib < n_batch; ib += 2)
+                    two(ib);
+            } else {
+#pragma unroll
+                for (int ib = 0; ib < NBATCH; ib += 2) {
+                    if (ib >= n_batch)
+                        break;
+                    two(ib);
                 }
             }
         }
@@ -767,6 +776,25 @@ template <typename V, int LPR> void launch_walk(fae_ctx *ctx, const BwdArgs &a, 
     }
 }
 
+// With sixteen float4 lanes per row the loop takes 90 registers instead of 104: five waves per SIMD instead of
+// four.  That is worth it where the spans then take fewer rounds (the chip's full of waves): 5096 spans of 256
+// lookups 129 -> 119 us, 41 000 (zipf 1.2) 398 -> 377; with as many rounds it is not: 3328 spans 27.1 / 27.8,
+// 6682 spans 153 / 159.  With 32 lanes (115 / 85 registers, many rounds) 1109 / 1114, with eight 63 / 69: not there.
+template <typename V, int LPR> void launch_scan(fae_ctx *ctx, const BwdArgs &a, dim3 grid, dim3 block)
+{
+    if constexpr (sizeof(V) == sizeof(float4) && LPR == 16)
+        if (const int at_once = 4 * 4 * ctx->n_cu, rolled = 5 * 4 * ctx->n_cu;
+            ctx->opt_unroll != 4 && (a.n_spans + rolled - 1) / rolled < (a.n_spans + at_once - 1) / at_once) {
+            FAE_LAUNCH(ctx, (bwd_reduce_kernel<V, LPR, 2, false, true>), grid, block, 0, ctx->stream, a);
+            return;
+        }
+    // steps per batch: two; reduce_unroll 4 forces four
+    if (ctx->opt_unroll == 4)
+        FAE_LAUNCH(ctx, (bwd_reduce_kernel<V, LPR, 4, false>), grid, block, 0, ctx->stream, a);
+    else
+        FAE_LAUNCH(ctx, (bwd_reduce_kernel<V, LPR, 2, false>), grid, block, 0, ctx->stream, a);
+}
+
 template <typename V, int LPR> void launch_reduce(fae_ctx *ctx, const BwdArgs &a)
 {
     {
@@ -774,19 +802,10 @@ template <typename V, int LPR> void launch_reduce(fae_ctx *ctx, const BwdArgs &a
         const dim3 grid((a.n_spans + a.wg_waves - 1) / a.wg_waves), block(a.wg_waves * FAE_WAVE);
         if (a.form == 1)
             launch_walk<V, LPR>(ctx, a, grid, block);
+        else if (a.mean || a.adagrad)
+            FAE_LAUNCH(ctx, (bwd_reduce_kernel<V, LPR, 2, true>), grid, block, 0, ctx->stream, a);
         else
-        {
-            // steps per batch: two where a step moves whole rows with few lanes to spare (long rows),
-            // four otherwise; reduce_unroll 2 / 4 forces one
-            const bool var = a.mean || a.adagrad;
-            const int un = ctx->opt_unroll == 2 ? 2 : (ctx->opt_unroll == 4 ? 4 : 2);
-            if (var)
-                FAE_LAUNCH(ctx, (bwd_reduce_kernel<V, LPR, 2, true>), grid, block, 0, ctx->stream, a);
-            else if (un == 2)
-                FAE_LAUNCH(ctx, (bwd_reduce_kernel<V, LPR, 2, false>), grid, block, 0, ctx->stream, a);
-            else
-                FAE_LAUNCH(ctx, (bwd_reduce_kernel<V, LPR, 4, false>), grid, block, 0, ctx->stream, a);
-        }
+            launch_scan<V, LPR>(ctx, a, grid, block);
     }
     if (a.fused_fixup)
         return;

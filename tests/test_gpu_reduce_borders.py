@@ -1,6 +1,7 @@
 """Runs that cross span borders, at the counts of spans where the wave that closes a run changes what
-it does (64 pieces at a time, fetched eight per lane group).  Gradients and weights are whole numbers and lr is
-a power of two, so every sum is exact in fp32 whatever its order."""
+it does (64 pieces at a time, fetched eight per lane group), and launches of more spans than the chip
+holds at once, where the reduce kernel's tiles run as a loop (rows of 36 to 64 floats).  Gradients and
+weights are whole numbers and lr is a power of two, so every sum is exact in fp32 whatever its order."""
 import numpy as np
 import pytest
 import torch
@@ -40,3 +41,12 @@ def test_runs_over_many_spans(dim, pieces):
         s = np.concatenate([rng.integers(0, 50, lead), np.full(n, 50), rng.integers(51, 300, tail)])
         lists.append(rng.permutation(s))
     _step(dim, lists, [300] * len(lists), 64)
+
+
+@pytest.mark.parametrize("dim", [36, 64])
+@pytest.mark.parametrize("spans", [4096, 4097, 5120, 5121, 9000])
+def test_more_spans_than_the_chip_holds(dim, spans):
+    rng = np.random.default_rng(spans)
+    n = spans * 64 // 2
+    lists = [np.where(rng.random(n) < 0.1, 17, rng.integers(0, 4000, n)), rng.integers(0, 100_000, n)]
+    _step(dim, lists, [4000, 100_000], 64)
