@@ -282,41 +282,42 @@ __device__ __forceinline__ int fae_load_row(const void *idx, int64_t j, int wide
     return (unsigned)v < (unsigned)rows ? v : -1;
 }
 
-// inclusive scan across the 64 lanes of a wave
+// Inclusive scan across the 64 lanes of a wave, all of them active: inside the rows of sixteen lanes, then from
+// row to row, by the data-parallel primitives of the vector unit (a shuffle goes through the LDS, six of them in a row).
+__device__ __forceinline__ int fae_row_incl_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false); // from the lane 1, 2, 4, 8 below in the row, zero where there is none
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    return v;
+}
 __device__ __forceinline__ int fae_wave_incl_scan(int v)
 {
-    int lane = fae_lane();
-#pragma unroll
-    for (int d = 1; d < FAE_WAVE; d <<= 1) {
-        int n = __shfl_up(v, d, FAE_WAVE);
-        if (lane >= d)
-            v += n;
-    }
+    v = fae_row_incl_scan(v);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false); // the last lane of rows 0 and 2 to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false); // lane 31 to rows 2 and 3
     return v;
 }
 
 // exclusive scan across a block of BLOCK threads (BLOCK multiple of 64, <= 1024).
 // lds must hold BLOCK/64 + 1 ints.  Returns the exclusive prefix; *total = block sum.
-// Every thread adds up the wave totals itself (at most sixteen LDS reads of the same addresses,
-// issued together): no thread does it for the others while they wait at a third barrier.
+// Every wave adds up the wave totals itself (one LDS read, a total per lane): no thread does it for the
+// others while they wait at a third barrier.
 template <int BLOCK> __device__ __forceinline__ int fae_block_excl_scan(int v, int *lds, int *total)
 {
     constexpr int NW = BLOCK / FAE_WAVE;
-    int lane = fae_lane(), w = threadIdx.x / FAE_WAVE;
-    int inc = fae_wave_incl_scan(v);
+    static_assert(NW <= 16, "the totals fit a row of lanes");
+    const int lane = fae_lane(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / FAE_WAVE);
+    const int inc = fae_wave_incl_scan(v);
     __syncthreads(); // lds may still be read from a previous call
     if (lane == FAE_WAVE - 1)
         lds[w] = inc;
     __syncthreads();
-    int before = 0, all = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        const int t = lds[i];
-        all += t;
-        before += i < w ? t : 0;
-    }
-    *total = all;
-    return before + inc - v;
+    const int own = lds[lane % NW];
+    const int all = fae_row_incl_scan(own);
+    *total = __builtin_amdgcn_readlane(all, NW - 1);
+    return __builtin_amdgcn_readlane(all, w) - __builtin_amdgcn_readlane(own, w) + inc - v;
 }
 
 // first position in sorted a[lo,hi) whose value is > key (upper bound)
