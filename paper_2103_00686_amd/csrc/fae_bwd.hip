@@ -3,7 +3,7 @@
 //
 //   1. keys    key = hot slot, value = sample id, per table segment
 //   2. sort    stable sort of (key, value), segmented by table: inside LDS for tables of up
-//              to 16 K lookups, else LSD radix passes over only the bits a hot slot can
+//              to 16 K lookups, mostly up to 128 K, else LSD radix passes over only the bits a hot slot can
 //              occupy (one chained kernel per pass for short lists, three kernels per pass
 //              for long ones)
 //   3. reduce  one wave owns a span of the sorted lookups.  Its 64/LPR lane groups
@@ -17,7 +17,7 @@
 //              run ends adds them in span order and applies the update (inside the
 //              reduce kernel; as a kernel of its own for very wide rows or on request).
 // No float atomics: every row has exactly one writer, and the summation order is fixed by the
-// stable sort (the optional counting sort, sort_order=1, leaves the order inside a run open).
+// stable sort.
 // Bandwidth bound: per lookup one gradient row is read, per distinct row one weight
 // row is read and written; the sort moves 16 B per lookup and pass.
 //

@@ -1,7 +1,7 @@
 // Backward, steps 1 + 2: (hot slot, sample) pairs of a hot mini-batch sorted by slot, per table
 // (Sec. 2.2, Sec. 6.2: the embedding update of hot mini-batches runs on the GPU).
 //   keys     key = hot slot, value = sample id, per table segment
-//   sort     inside LDS for tables of up to 16 K lookups (split over workgroups by key range),
+//   sort     inside LDS for lists of up to 16 K lookups, mostly up to 128 K (split over workgroups by key range),
 //            else stable LSD radix passes over only the bits a hot slot can occupy: one kernel per
 //            pass for short lists, whose tiles add up their table's digit counts themselves (direct:
 //            few tiles, most of them in a few tables) or are chained through published counts;
@@ -9,6 +9,7 @@
 // Also here: the sort started ahead of the backward (side stream), and the launch that carries
 // the forward's row copies and the LDS sort together.
 #include "fae_bwd.h"
+#include "fae_lsort.h"
 
 // ---------------------------------------------------------------------------------
 // 1. keys
@@ -458,57 +459,77 @@ template <int MODE, int ITEMS> __global__ __launch_bounds__(SORT_THREADS, MODE =
 }
 
 // ---------------------------------------------------------------------------------
-// 2b. small tables: a table's list is sorted inside LDS by a few workgroups.
-// Each workgroup loads all keys of its table (64 KiB of LDS, left in place), takes the
-// keys whose top bits equal its part number (an ordered selection, so the input order
-// survives), and LSD-sorts that subset on the remaining low bits.  What moves is a
-// 16-bit permutation (position -> original lookup), ping-ponged between two 32 KiB
-// arrays.  A radix pass makes two sweeps over the permutation: a per-wave digit
-// histogram, then the same stable ranking as the global pass (wave-level match on
-// the digit, running per-wave offsets).  The parts of a table are disjoint key ranges,
-// so their outputs are laid end to end: part p starts after all keys of parts < p.
+// 2b. tables of up to LSORT_MAX lookups: sorted inside LDS by a few workgroups per table (fae_lsort.h)
 // ---------------------------------------------------------------------------------
-
-__global__ __launch_bounds__(LSORT_THREADS) void lds_sort_kernel(LsortArgs a)
+__global__ __launch_bounds__(LSORT_THREADS, 8) void lds_sort_kernel(LsortArgs a)
 {
     bwd_clear_flags(a.flags, a.n_flags, a.flag_slice, LSORT_THREADS);
     const int z = fae_find_table(a.blk_start, a.n_tables, blockIdx.x);
-    lds_sort_block(a.slots[z], a.offsets[z], a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z],
-                   blockIdx.x - a.blk_start[z], a.part_shift[z], a.n_samples, a.keys_out + a.seg_start[z],
-                   a.vals_out + a.seg_start[z], a.status, a.unordered != 0);
+    lds_sort_block(a.slots[z], a.offsets[z], a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z], blockIdx.x - a.blk_start[z],
+                   a.blk_start[z + 1] - a.blk_start[z], a.part_shift[z], a.n_samples, a.keys_out + a.seg_start[z],
+                   a.vals_out + a.seg_start[z], a.status);
 }
 
 // ---------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------
-// Workgroups per small table for the LDS sort: enough parts to occupy the chip, never lists
-// below ~64 lookups (a part of up to 256 is sorted by counting, whose time goes by its length; a step of
-// 8 x 1024 lookups, parts down to 512, 256, 128, 64, 32: 19.3, 17.6, 17.6, 17.5, 17.4 us; of 1 x 512: 15.8, 14.6,
-// 14.8, 14.7, 14.1 us).  part_shift[z]: part of a key = key >> shift; blk_start: prefix of workgroups per
-// table (tables not sorted in LDS get none).  Returns the number of workgroups.
+// Lists beyond LSORT_SHORT lookups in LDS, instead of a keys kernel and radix passes: up to 100 000 lookups, and up to
+// LSORT_MAX where the batch has no more than a million (what every part's way over the whole list costs grows with the square of the
+// list), and, by itself, only where some slot needs three passes.  Sort kernels, us, passes / LDS:
+//   1 x 17 000 28-34 / 17.6, 1 x 131 000 33.4 / 28.9, 3 x 100 000 43.3 / 33.5, 7 x 65 536 44.6 / 28.9, 13 x 100 000 67.8 / 52.7
+//   26 x 17 000 40.9 / 26.7, 26 x 65 536 68.6 / 51.5, 26 x 100 000 81.1 / 76.4, 13 x 131 000 70.5 / 80.1, 26 x 131 000 97.8 / 106.9
+//   bags of 20: 1 x 65 536 30.2 / 23.0, 3 x 100 000 45.3 / 45.7, 13 x 65 536 55.7 / 41.3, 13 x 131 000 72.6 / 72.3
+//   slots of 13 bits (two passes): 7 x 18 432 26.3 / 17.6, 13 x 60 000 34.6 / 29.9, 2 x 110 000 28.1 / 34.0; 40 rows (one
+//   pass): 7 x 18 432 18.1 / 18.0, 13 x 60 000 20.8 / 29.5, 2 x 110 000 13.0 / 35.6.  So two passes or one are left as they are.
+#define LSORT_SHORT 16384
+#define FUSED_ALONE_LANES 32 // lanes per row from which on a workgroup of the fused launch has a compute unit to itself
+#define LSORT_LONG_ROWS 65536
+static bool lsort_takes(int64_t lookups, int64_t all)
+{
+    return lookups <= 100000 || (lookups <= LSORT_MAX && all <= 1 << 20);
+}
+
+// Workgroups per table for the LDS sort.  Lists that are split by the top bits of the slot: enough parts to
+// occupy the chip, never below ~64 lookups (a part of up to 256 is sorted by counting; a step of 8 x 1024 lookups,
+// parts down to 512, 256, 128, 64, 32: 19.3, 17.6, 17.6, 17.5, 17.4 us; of 1 x 512: 15.8, 14.6, 14.8, 14.7, 14.1 us).
+// Longer ones: one sorting workgroup per compute unit over all tables, two for three beside row copies, parts of 512 to
+// 5000 lookups (every part goes over its table's whole list, so more of them cost more than shorter ones save; 5000
+// leaves room for the sample's error below LSORT_CAP).  Steps of 26 x 16 384, dim 64, parts of 1664, 2500, 4096, 5000: 56.6,
+// 55.0, 59.0, 59.3 us; 26 x 50 001, parts of 2048, 4096, 5000: 217, 210.1, 209.2; 5 lists of 111 K in all, parts of 512,
+// 1024: 43.4, 45.3.  Beside more copies of wide rows than there are compute units, where a sorting workgroup
+// keeps one to itself (see fwd_sort_kernel), no less than 3300 (26 x 16 384, dim 128, 2500: 138, 3300: 130).
+// part_shift[z]: part of a key = key >> shift; blk_start: prefix of workgroups per table (tables not
+// sorted in LDS get none).  Returns the number of workgroups.
 static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fae_batch *hot_batch, const bool *in_lds,
-               int n_lds, int32_t *blk_start, int32_t *part_shift, int64_t other_blocks)
+               int n_lds, int32_t *blk_start, int32_t *part_shift, int copy_lanes, int64_t copy_blocks)
 {
     const int nt = hot_tables->n_tables;
     int want = 1;
     while (want < 16 && n_lds * want * 2 <= ctx->n_cu)
         want <<= 1;
-    // In the launch that also copies rows (other_blocks workgroups of them, one workgroup per
-    // compute unit), every sorting workgroup keeps a unit from copying: when the copies alone are
-    // more than the chip holds at once, fewer and larger parts win although the largest part ends
-    // later (workload 3: 35.5 us with 4 parts per table, 38.9 us with 8, 43.5 us with 2).
-    while (want > 4 && (int64_t)n_lds * want + other_blocks > (int64_t)ctx->n_cu * 3 / 2)
-        want >>= 1;
+    int64_t long_lookups = 0;
+    for (int z = 0; z < nt; ++z)
+        if (in_lds[z] && hot_batch->h_n_lookups[z] > LSORT_SPLIT_MAX)
+            long_lookups += hot_batch->h_n_lookups[z];
+    int64_t share = long_lookups * (copy_blocks > 0 ? 3 : 2) / (2 * ctx->n_cu);
+    const int64_t least = copy_lanes >= FUSED_ALONE_LANES && copy_blocks > ctx->n_cu ? 3300 : 512;
+    share = share < least ? least : (share > 5000 ? 5000 : share);
     int nb = 0;
     for (int z = 0; z < nt; ++z) {
         blk_start[z] = nb;
+        part_shift[z] = 0;
         if (!in_lds[z])
             continue;
+        const int64_t n = hot_batch->h_n_lookups[z];
+        if (n > LSORT_SPLIT_MAX) {
+            nb += (int)((n + share - 1) / share);
+            continue;
+        }
         int kbits = 1; // bits of the largest key (n_hot itself marks an invalid slot)
         while ((hot_tables->h_rows[z] >> kbits) != 0)
             ++kbits;
         int parts = want;
-        while (parts > 1 && hot_batch->h_n_lookups[z] / parts < 64)
+        while (parts > 1 && n / parts < 64)
             parts >>= 1;
         int pbits = 0;
         while ((1 << pbits) < parts)
@@ -530,15 +551,20 @@ int32_t bwd_sort_stage(fae_ctx *ctx, hipStream_t st, const fae_tables *hot_table
     BwdArgs &a = su.a;
     const BwdWs &w = su.w;
     const int nt = hot_tables->n_tables;
-    // Tables whose lookups fit one workgroup are sorted in LDS; they take no part in the
-    // global passes (zero tiles, zero key blocks).
+    // Tables that are sorted in LDS take no part in the global passes (zero tiles, zero key blocks).
     bool in_lds[FAE_MAX_TABLES];
     int n_lds = 0;
     int64_t max_hot_global = 0;
     int64_t tiles = 0;
+    int64_t max_hot_long = 0; // of the lists beyond LSORT_SHORT
+    for (int z = 0; z < nt; ++z)
+        if (hot_batch->h_n_lookups[z] > LSORT_SHORT && hot_tables->h_rows[z] > max_hot_long)
+            max_hot_long = hot_tables->h_rows[z];
     for (int z = 0; z < nt; ++z) {
         const int64_t nl = hot_batch->h_n_lookups[z];
-        in_lds[z] = ctx->opt_sort != 1 && nl > 0 && nl <= LSORT_MAX;
+        in_lds[z] = ctx->opt_sort != 1 && nl > 0 && nl <= LSORT_MAX && (!a.offsets[z] || a.n_samples <= LSORT_MAX);
+        if (in_lds[z] && nl > LSORT_SHORT && ctx->opt_sort != 2)
+            in_lds[z] = ctx->opt_sort == 0 && max_hot_long >= LSORT_LONG_ROWS && lsort_takes(nl, su.plan.N);
         if (!in_lds[z] && nl > 0 && hot_tables->h_rows[z] > max_hot_global)
             max_hot_global = hot_tables->h_rows[z];
     }
@@ -714,14 +740,13 @@ int32_t bwd_sort_stage(fae_ctx *ctx, hipStream_t st, const fae_tables *hot_table
             la.n_hot[z] = a.n_hot[z];
             la.seg_start[z] = a.seg_start[z];
         }
-        const int nb = lsort_plan(ctx, hot_tables, hot_batch, in_lds, n_lds, la.blk_start, la.part_shift, 0);
+        const int nb = lsort_plan(ctx, hot_tables, hot_batch, in_lds, n_lds, la.blk_start, la.part_shift, 0, 0);
         la.seg_start[nt] = a.seg_start[nt];
         la.n_tables = nt;
         la.n_samples = a.n_samples;
         la.keys_out = w.keys[cur];
         la.vals_out = w.vals[cur];
         la.status = ctx->d_block;
-        la.unordered = ctx->opt_sort_order == 1;
         la.flags = a.flags;
         la.n_flags = a.n_flags;
         la.flag_slice = bwd_flag_slice(a.n_flags, nb);
@@ -782,7 +807,6 @@ struct FusedArgs {
     int32_t part_shift[FAE_MAX_TABLES];
     int32_t n_tables, dim, n_samples;
     int32_t n_sort_blocks, fwd_blocks_per_table;
-    int32_t unordered;
     int64_t out_stride;
     float *out;
     int32_t *keys_out, *vals_out;
@@ -792,20 +816,24 @@ struct FusedArgs {
     int32_t n_flags, flag_slice;
 };
 
-template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS) void fwd_sort_kernel(FusedArgs a)
+// Rows of up to 16 lanes: two workgroups share a compute unit, eight rows per lane group in flight.  Wider ones: with as few
+// registers only four rows fit (eight spill: 128 -> 151 us), and 16 rows in one workgroup move more.  Steps of 26 tables, before
+// (one workgroup, more LDS) / two with four rows / one with sixteen, us: 16 384 samples, dim 128 128.1 / 132.7 / 130.1, 12 000 90.6
+// / 96.7 / 90.6, 50 001 452 / 420 / 411; dim 100, 16 384 105.9 / 111.4 / 107.1, 50 001 452 / 407 / 415, 4000 39.2 / 36.2 / 38.3.
+template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS, (LPR < FUSED_ALONE_LANES ? 8 : 4)) void fwd_sort_kernel(FusedArgs a)
 {
     bwd_clear_flags(a.flags, a.n_flags, a.flag_slice, LSORT_THREADS);
     if ((int)blockIdx.x < a.n_sort_blocks) {
         const int z = fae_find_table(a.sort_blk_start, a.n_tables, blockIdx.x);
-        lds_sort_block(a.slots[z], nullptr, a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z],
-                       blockIdx.x - a.sort_blk_start[z], a.part_shift[z], a.n_samples, a.keys_out + a.seg_start[z],
-                       a.vals_out + a.seg_start[z], a.status, a.unordered != 0);
+        lds_sort_block(a.slots[z], nullptr, a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z], blockIdx.x - a.sort_blk_start[z],
+                       a.sort_blk_start[z + 1] - a.sort_blk_start[z], a.part_shift[z], a.n_samples, a.keys_out + a.seg_start[z],
+                       a.vals_out + a.seg_start[z], a.status);
     } else {
         const int b = blockIdx.x - a.n_sort_blocks;
         const int z = b / a.fwd_blocks_per_table, bl = b % a.fwd_blocks_per_table;
         const int64_t s0 = ((int64_t)bl * LSORT_WAVES + threadIdx.x / FAE_WAVE) * FAE_WAVE;
-        fwd_onehot_wave<V, LPR, 16>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, a.n_samples, a.out + (int64_t)z * a.dim,
-                                a.out_stride, a.dim, a.status, a.stream_out != 0);
+        fwd_onehot_wave<V, LPR, (LPR < FUSED_ALONE_LANES ? 8 : 16)>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, a.n_samples, a.out + (int64_t)z * a.dim,
+                               a.out_stride, a.dim, a.status, a.stream_out != 0);
     }
 }
 
@@ -828,7 +856,7 @@ extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_ta
     // batch within the LDS sort's reach, 16-byte aligned rows); anything else: plain forward
     bool fused = !su.empty && ctx->opt_sort != 1 && ctx->opt_fwd == 0 && h_hotW && out && dim % 4 == 0 &&
                  out_row_stride % 4 == 0 && out_row_stride >= (int64_t)nt * dim && ((uintptr_t)out) % 16 == 0 &&
-                 S <= LSORT_MAX;
+                 (S <= LSORT_SHORT || ((ctx->opt_sort == 0 || ctx->opt_sort == 2) && lsort_takes(S, su.plan.N)));
     for (int z = 0; fused && z < nt; ++z)
         fused = su.a.offsets[z] == nullptr && h_hotW[z] && ((uintptr_t)h_hotW[z]) % 16 == 0;
     if (!fused)
@@ -849,8 +877,11 @@ extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_ta
         in_lds[z] = true;
     }
     f.seg_start[nt] = su.a.seg_start[nt];
-    f.n_sort_blocks = lsort_plan(ctx, hot_tables, hot_batch, in_lds, nt, f.sort_blk_start, f.part_shift,
-                                (int64_t)nt * ((S + LSORT_THREADS - 1) / LSORT_THREADS));
+    int lpr = 1;
+    while (lpr < dim / 4 && lpr < 64)
+        lpr <<= 1;
+    f.n_sort_blocks = lsort_plan(ctx, hot_tables, hot_batch, in_lds, nt, f.sort_blk_start, f.part_shift, lpr,
+                                 (int64_t)nt * ((S + LSORT_THREADS - 1) / LSORT_THREADS));
     f.n_tables = nt;
     f.dim = dim;
     f.n_samples = (int32_t)S;
@@ -860,15 +891,11 @@ extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_ta
     f.keys_out = su.w.keys[0];
     f.vals_out = su.w.vals[0];
     f.status = ctx->d_block;
-    f.unordered = ctx->opt_sort_order == 1;
     f.stream_out = ctx->opt_fwd_stream != 0;
     f.flags = su.a.flags;
     f.n_flags = su.a.n_flags;
     const int blocks = f.n_sort_blocks + f.fwd_blocks_per_table * nt;
     f.flag_slice = bwd_flag_slice(f.n_flags, blocks);
-    int lpr = 1;
-    while (lpr < dim / 4 && lpr < 64)
-        lpr <<= 1;
     {
         fae_ktimer kt(ctx, FAE_K_FWD_SORT);
         switch (lpr) {

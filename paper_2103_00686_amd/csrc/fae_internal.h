@@ -40,7 +40,6 @@ struct fae_ctx {
     int64_t opt_profile = 0; // 0 auto, 1 global atomics, 2 LDS-privatised
     int64_t opt_fwd = 0;     // 0 auto, 1 group-per-bag, 2 wave-per-bag
     int64_t opt_sort = 0;    // 0 auto, 1 global radix, 2 LDS per table
-    int64_t opt_sort_order = 0; // LDS sort: 0 stable (lookups of a slot in batch order), 1 counting sort (any order)
     int64_t opt_fwd_stream = 1; // non-temporal stores for the pooled output
     int64_t opt_span = 0;       // lookups per wave in the reduce kernel (0 = auto)
     int64_t opt_fixup = 0;      // runs that cross span borders: 0 auto (inside the reduce kernel), 1 separate kernel
@@ -303,14 +302,15 @@ __device__ __forceinline__ int fae_wave_incl_scan(int v)
 // exclusive scan across a block of BLOCK threads (BLOCK multiple of 64, <= 1024).
 // lds must hold BLOCK/64 + 1 ints.  Returns the exclusive prefix; *total = block sum.
 // Every wave adds up the wave totals itself (one LDS read, a total per lane): no thread does it for the
-// others while they wait at a third barrier.
-template <int BLOCK> __device__ __forceinline__ int fae_block_excl_scan(int v, int *lds, int *total)
+// others while they wait at a third barrier.  FREE: a barrier lies between the last use of lds and this call.
+template <int BLOCK, bool FREE = false> __device__ __forceinline__ int fae_block_excl_scan(int v, int *lds, int *total)
 {
     constexpr int NW = BLOCK / FAE_WAVE;
     static_assert(NW <= 16, "the totals fit a row of lanes");
     const int lane = fae_lane(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / FAE_WAVE);
     const int inc = fae_wave_incl_scan(v);
-    __syncthreads(); // lds may still be read from a previous call
+    if (!FREE)
+        __syncthreads(); // lds may still be read from a previous call
     if (lane == FAE_WAVE - 1)
         lds[w] = inc;
     __syncthreads();
