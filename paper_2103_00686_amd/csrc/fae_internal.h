@@ -36,6 +36,7 @@ struct fae_ctx {
     uint32_t *d_block = nullptr; // device, FAE_BLK_WORDS words
     uint32_t part_calls = 0;     // calls of the partition so far
     uint32_t *h_block = nullptr; // pinned host mirror
+    uint32_t *h_block_dev = nullptr; // the same memory as the device addresses it
     int n_cu = 256;
     int64_t opt_profile = 0; // 0 auto, 1 global atomics, 2 LDS-privatised
     int64_t opt_fwd = 0;     // 0 auto, 1 group-per-bag, 2 wave-per-bag
@@ -172,10 +173,14 @@ int32_t fae_fail(fae_ctx *ctx, int32_t code, const char *fmt, ...);
 int32_t fae_bwd_scratch_resolve(fae_ctx *ctx, int device, void **out);
 // copy n words of the device block (from word `first`) to the pinned block and wait
 int32_t fae_readback(fae_ctx *ctx, int first, int n);
+// copy n words from device memory to the pinned memory from word `at` of its mirror on, and wait
+int32_t fae_publish(fae_ctx *ctx, const uint32_t *p, int at, int n);
 // wait for the stream, fetch + clear the sticky status; maps it to an error code
 int32_t fae_sync_status(fae_ctx *ctx);
 // the same together with the first n scalars of the device block (fetched whatever the status says)
 int32_t fae_readback_status(fae_ctx *ctx, int n);
+// the same after a kernel that has written status and scalars to the pinned block itself
+int32_t fae_wait_status(fae_ctx *ctx);
 int32_t fae_check_tables(fae_ctx *ctx, const fae_tables *t, const char *who);
 int32_t fae_check_batch(fae_ctx *ctx, const fae_tables *t, const fae_batch *b, const char *who);
 // data[0..n) -> exclusive prefix sums in place, data[n] = total (one workgroup; n+1 entries)

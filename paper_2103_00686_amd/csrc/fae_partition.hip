@@ -47,7 +47,7 @@ struct PartArgs {
     int32_t *hot_samples;
     int32_t *cold_samples;
     uint32_t *status;
-    uint32_t *scalars;    // device scalars: [0] = n_hot_samples, [1+z] = hot lookups of table z
+    uint32_t *host;       // the pinned block: from FAE_BLK_SCALARS on n_hot_samples, then the hot lookups of every table
 };
 static_assert(sizeof(PartArgs) <= 4096, "kernel arguments are passed by value");
 
@@ -568,6 +568,14 @@ template <bool WAVE_TILES, bool BAGS, bool ONE, bool SPREAD> __global__ __launch
     const bool hot = t < ns && a.cold[s0 + t] == 0u;
     const int state = BAGS ? a.tile_state[tile] : PT_LIGHT;
     const bool leave = BAGS && a.leave && *a.any_heavy == a.stamp;
+    // The results go straight to pinned memory (the kernels before this one have reported what they had to), so neither a
+    // copy nor a kernel of its own stands between the last tile and the host: 1 table, 3004 samples 26.9 -> 24.3 us a call,
+    // 16 tables, 14 059 samples 41.6 -> 39.1, 26 tables, 262 144 samples 88.0 -> 86.9.
+    const bool last = tile == a.n_tiles - 1;
+    if (last && t == 0) {
+        a.host[FAE_BLK_STATUS] = a.status[FAE_BLK_STATUS];
+        a.host[FAE_BLK_HEAVY] = *a.any_heavy;
+    }
     const int nb_max = PT_OFF_WORDS / (T + 1);
     if (BAGS && !ONE)
         s_tab.fill(a);
@@ -626,13 +634,13 @@ template <bool WAVE_TILES, bool BAGS, bool ONE, bool SPREAD> __global__ __launch
             a.cold_samples[s0 + t - h0 - pos] = s0 + t;
     }
     __syncthreads();
-    const bool last = tile == a.n_tiles - 1; // it also writes the closing offsets and the totals
+    uint32_t *const totals = a.host + FAE_BLK_SCALARS; // the last tile also writes the closing offsets and the totals
     if (last && t == 0)
-        a.scalars[0] = (uint32_t)(h0 + n_here);
+        totals[0] = (uint32_t)(h0 + n_here);
     if (last && t < a.n_one) {
         const int z = a.n_csr + t;
         a.hoffsets[z][h0 + n_here] = h0 + n_here;
-        a.scalars[1 + a.number[z]] = (uint32_t)(h0 + n_here);
+        totals[1 + a.number[z]] = (uint32_t)(h0 + n_here);
     }
     const int items = n_here > 0 ? a.n_one << a.tile_log : 0;
     for (int i0 = t; i0 < items; i0 += PT_ROUND) {
@@ -701,7 +709,7 @@ template <bool WAVE_TILES, bool BAGS, bool ONE, bool SPREAD> __global__ __launch
                 }
                 if (last && l == lanes - 1) {
                     tab.hoffset(z)[h0 + n_here] = at;
-                    a.scalars[1 + a.number[z]] = (uint32_t)at;
+                    totals[1 + a.number[z]] = (uint32_t)at;
                 }
             }
             __syncthreads();
@@ -862,7 +870,7 @@ extern "C" int32_t fae_partition_batch(fae_ctx *ctx, const fae_tables *tables, c
     a.hot_samples = hot_samples;
     a.cold_samples = cold_samples;
     a.status = ctx->d_block;
-    a.scalars = ctx->d_block + FAE_BLK_SCALARS;
+    a.host = ctx->h_block_dev;
     const dim3 grid((unsigned)tiles), block(PT_THREADS);
     const bool wave_tiles = log >= 6, one_bag = a.n_csr == 1;
     for (bool again = false;; again = true) {
@@ -914,7 +922,7 @@ extern "C" int32_t fae_partition_batch(fae_ctx *ctx, const fae_tables *tables, c
                 FAE_LAUNCH(ctx, (part_emit_kernel<false, false, false, false>), grid, block, 0, ctx->stream, a);
             FAE_LAUNCH_CHECK(ctx);
         }
-        const int32_t now = fae_readback_status(ctx, nt + 1);
+        const int32_t now = fae_wait_status(ctx);
         if (now == FAE_EHIP)
             return now;
         rc = rc != FAE_OK ? rc : now; // what the first half reported is not reported again

@@ -332,9 +332,9 @@ struct Window {
             FAE_LAUNCH(ctx, count_window_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a);
             FAE_LAUNCH_CHECK(ctx);
         }
-        FAE_HIP(ctx, hipMemcpyAsync(host, d_hist, (size_t)nt * CW_STRIDE * sizeof(uint32_t), hipMemcpyDeviceToHost,
-                                    ctx->stream));
-        FAE_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        rc = fae_publish(ctx, d_hist, FAE_BLK_WORDS, nt * CW_STRIDE);
+        if (rc != FAE_OK)
+            return rc;
         for (int z = 0; z < nt; ++z) { // rows with count >= lo_z
             const uint32_t *h = host + (size_t)z * CW_STRIDE;
             uint32_t all = 0;
