@@ -1,0 +1,64 @@
+"""Classifier at the edges of its tiles (2048 rows, eight per thread): remap, hot ids and counts against the
+definition in numpy, with remaps and counters that do not start on 16 bytes, empty tables, no and only hot rows,
+and a capacity that is too small."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2103_00686_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _build(rows, counts, cutoff, caps, shift):
+    dim = 4
+    ctx, tables = B.Context(0, None), B.Tables(rows, dim)
+    view = lambda n: torch.full((max(n, 1) + shift,), -7, dtype=torch.int32, device="cuda")[shift:]  # noqa: E731
+    cnt = []
+    for c in counts:
+        v = view(len(c))
+        v[:len(c)] = torch.from_numpy(c.astype(np.int32)).cuda()
+        cnt.append(v)
+    remap, ids = [view(r) for r in rows], [view(c) for c in caps]
+    hotW = [torch.zeros((max(c, 1), dim), dtype=torch.float32, device="cuda") for c in caps]
+    ws = torch.empty(B.fae_build_workspace_bytes(tables), dtype=torch.uint8, device="cuda")
+    got = B.fae_build_hot_tables(ctx, tables, cnt, cutoff, B.FAE_SRC_PROCEDURAL, None, 1, remap, ids, hotW, caps, ws)
+    return [int(g) for g in got], remap, ids
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("rows", [[1, 0, 7], [8, 9, 63], [2047, 2048, 2049], [4096, 4097, 1], [100_001, 6143, 0, 33]])
+@pytest.mark.parametrize("share", [0.0, 0.3, 1.0])
+def test_build_at_tile_edges(rows, shift, share):
+    rng = np.random.default_rng(sum(rows) + shift)
+    counts = [np.where(rng.random(r) < share, 5, 4) for r in rows]
+    got, remap, ids = _build(rows, counts, [5] * len(rows), rows, shift)
+    for z, c in enumerate(counts):
+        hot = np.flatnonzero(c >= 5)
+        want = np.full(len(c), -1)
+        want[hot] = np.arange(hot.size)
+        assert got[z] == hot.size
+        assert np.array_equal(remap[z].cpu().numpy()[:len(c)], want)
+        assert np.array_equal(ids[z].cpu().numpy()[:hot.size], hot)
+
+
+def test_remap_over_its_counters():
+    rows, dim = [10_007], 4
+    c = np.random.default_rng(3).integers(0, 9, rows[0]).astype(np.int32)
+    ctx, tables, both = B.Context(0, None), B.Tables(rows, dim), torch.from_numpy(c.copy()).cuda()
+    ids = torch.empty(rows[0], dtype=torch.int32, device="cuda")
+    hotW = torch.empty((rows[0], dim), dtype=torch.float32, device="cuda")
+    ws = torch.empty(B.fae_build_workspace_bytes(tables), dtype=torch.uint8, device="cuda")
+    got = B.fae_build_hot_tables(ctx, tables, [both], [5], B.FAE_SRC_PROCEDURAL, None, 1, [both], [ids], [hotW], rows, ws)
+    hot = np.flatnonzero(c >= 5)
+    want = np.full(rows[0], -1)
+    want[hot] = np.arange(hot.size)
+    assert got[0] == hot.size
+    assert np.array_equal(both.cpu().numpy(), want)
+
+
+def test_capacity_is_reported():
+    counts = [np.full(5000, 5)]
+    with pytest.raises(B.FaeError) as e:
+        _build([5000], counts, [5], [4999], 0)
+    assert e.value.code == B.FAE_ENOSPC
