@@ -483,6 +483,10 @@ __global__ __launch_bounds__(LSORT_THREADS, 8) void lds_sort_kernel(LsortArgs a)
 //   pass): 7 x 18 432 18.1 / 18.0, 13 x 60 000 20.8 / 29.5, 2 x 110 000 13.0 / 35.6.  So two passes or one are left as they are.
 #define LSORT_SHORT 16384
 #define FUSED_ALONE_LANES 32 // lanes per row from which on a workgroup of the fused launch has a compute unit to itself
+// Samples per copying wave of the fused launch: its workgroups fill what the sorting ones leave of the chip, and pieces of 64
+// left a nearly empty last round.  26 tables, three batches' inputs in turn, 64 / 32 / 16 samples, us a step: 16 384 samples, dim 64
+// 77.6 / 72.8 / 73.4, dim 128 143.6 / 138.9 / 142.6; 50 001 samples, dim 64 218 / 210 / 215; 4096, dim 16 22.9 / 23.0 / 23.0.
+#define FUSED_SAMPLES 32
 #define LSORT_LONG_ROWS 65536
 static bool lsort_takes(int64_t lookups, int64_t all)
 {
@@ -492,12 +496,13 @@ static bool lsort_takes(int64_t lookups, int64_t all)
 // Workgroups per table for the LDS sort.  Lists that are split by the top bits of the slot: enough parts to
 // occupy the chip, never below ~64 lookups (a part of up to 256 is sorted by counting; a step of 8 x 1024 lookups,
 // parts down to 512, 256, 128, 64, 32: 19.3, 17.6, 17.6, 17.5, 17.4 us; of 1 x 512: 15.8, 14.6, 14.8, 14.7, 14.1 us).
-// Longer ones: one sorting workgroup per compute unit over all tables, two for three beside row copies, parts of 512 to
-// 5000 lookups (every part goes over its table's whole list, so more of them cost more than shorter ones save; 5000
-// leaves room for the sample's error below LSORT_CAP).  Steps of 26 x 16 384, dim 64, parts of 1664, 2500, 4096, 5000: 56.6,
-// 55.0, 59.0, 59.3 us; 26 x 50 001, parts of 2048, 4096, 5000: 217, 210.1, 209.2; 5 lists of 111 K in all, parts of 512,
-// 1024: 43.4, 45.3.  Beside more copies of wide rows than there are compute units, where a sorting workgroup
-// keeps one to itself (see fwd_sort_kernel), no less than 3300 (26 x 16 384, dim 128, 2500: 138, 3300: 130).
+// Longer ones: one sorting workgroup per compute unit over all tables, parts of 512 to 5000 lookups (every part goes over its
+// table's whole list, so more of them cost more than shorter ones save; 5000 leaves room for the sample's error below
+// LSORT_CAP); 5 lists of 111 K in all, parts of 512, 1024: 43.4, 45.3 us.  Beside row copies two for three compute units, and
+// one for two where more workgroups copy rows of 16 lanes on than there are compute units, since those need the memory's
+// rate from all of them.  Steps, three batches' inputs in turn, two for three / one for two: 26 x 16 384, dim 64 73.9 /
+// 72.8 us, 12 000 60.5 / 59.3; 26 x 11 000, dim 16 34.5 / 35.1; 3 x 65 536, dim 8 36.4 / 37.9.  Where a sorting workgroup
+// has a compute unit to itself (see fwd_sort_kernel), no less than 3300: 13 x 16 384, dim 128, without / with 79.3 / 76.0.
 // part_shift[z]: part of a key = key >> shift; blk_start: prefix of workgroups per table (tables not
 // sorted in LDS get none).  Returns the number of workgroups.
 static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fae_batch *hot_batch, const bool *in_lds,
@@ -511,8 +516,9 @@ static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fa
     for (int z = 0; z < nt; ++z)
         if (in_lds[z] && hot_batch->h_n_lookups[z] > LSORT_SPLIT_MAX)
             long_lookups += hot_batch->h_n_lookups[z];
-    int64_t share = long_lookups * (copy_blocks > 0 ? 3 : 2) / (2 * ctx->n_cu);
-    const int64_t least = copy_lanes >= FUSED_ALONE_LANES && copy_blocks > ctx->n_cu ? 3300 : 512;
+    const bool many = copy_blocks > ctx->n_cu;
+    int64_t share = long_lookups * (many && copy_lanes >= 16 ? 4 : copy_blocks > 0 ? 3 : 2) / (2 * ctx->n_cu);
+    const int64_t least = many && copy_lanes >= FUSED_ALONE_LANES ? 3300 : 512;
     share = share < least ? least : (share > 5000 ? 5000 : share);
     int nb = 0;
     for (int z = 0; z < nt; ++z) {
@@ -831,8 +837,9 @@ template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS, (LPR 
     } else {
         const int b = blockIdx.x - a.n_sort_blocks;
         const int z = b / a.fwd_blocks_per_table, bl = b % a.fwd_blocks_per_table;
-        const int64_t s0 = ((int64_t)bl * LSORT_WAVES + threadIdx.x / FAE_WAVE) * FAE_WAVE;
-        fwd_onehot_wave<V, LPR, (LPR < FUSED_ALONE_LANES ? 8 : 16)>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, a.n_samples, a.out + (int64_t)z * a.dim,
+        const int64_t s0 = ((int64_t)bl * LSORT_WAVES + threadIdx.x / FAE_WAVE) * FUSED_SAMPLES;
+        const int s1 = s0 + FUSED_SAMPLES < a.n_samples ? (int)s0 + FUSED_SAMPLES : a.n_samples;
+        fwd_onehot_wave<V, LPR, (LPR < FUSED_ALONE_LANES ? 8 : 16)>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, s1, a.out + (int64_t)z * a.dim,
                                a.out_stride, a.dim, a.status, a.stream_out != 0);
     }
 }
@@ -880,12 +887,12 @@ extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_ta
     int lpr = 1;
     while (lpr < dim / 4 && lpr < 64)
         lpr <<= 1;
+    f.fwd_blocks_per_table = (int32_t)((S + LSORT_WAVES * FUSED_SAMPLES - 1) / (LSORT_WAVES * FUSED_SAMPLES));
     f.n_sort_blocks = lsort_plan(ctx, hot_tables, hot_batch, in_lds, nt, f.sort_blk_start, f.part_shift, lpr,
-                                 (int64_t)nt * ((S + LSORT_THREADS - 1) / LSORT_THREADS));
+                                 (int64_t)nt * f.fwd_blocks_per_table);
     f.n_tables = nt;
     f.dim = dim;
     f.n_samples = (int32_t)S;
-    f.fwd_blocks_per_table = (int32_t)((S + LSORT_THREADS - 1) / LSORT_THREADS);
     f.out_stride = out_row_stride;
     f.out = out;
     f.keys_out = su.w.keys[0];

@@ -92,3 +92,14 @@ def test_many_samples_with_empty_bags():
     offs = [torch.from_numpy(np.concatenate([[0], np.sort(rng.integers(0, n + 1, S - 1)), [n]]).astype(np.int32)).cuda()]
     want, got = (_step(v, slots, offs, S, [n])[1] for v in (1, 0))
     assert all(torch.equal(a, b) for a, b in zip(want, got))
+
+
+@pytest.mark.parametrize("nt,n", [(1, 1), (1, 31), (1, 33), (2, 511), (2, 513), (26, 5120), (26, 5121), (26, 10_753)])
+@pytest.mark.parametrize("dim", [4, 60, 64, 128, 260])
+def test_row_copies_beside_the_sort(nt, n, dim):
+    """Pieces of 32 samples per wave, and both sides of the rule on how many copies run beside the sorts."""
+    rng = np.random.default_rng(n + dim)
+    one = [torch.from_numpy(rng.integers(0, 999, n).astype(np.int32)).cuda() for _ in range(nt)]
+    want = _step(1, one, [None] * nt, n, [n] * nt, fused=True, rows=999, dim=dim)[1]
+    got = _step(0, one, [None] * nt, n, [n] * nt, fused=True, rows=999, dim=dim)[1]
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
