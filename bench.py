@@ -68,7 +68,7 @@ def main():
                     help="capture each step into a HIP graph and time the replays (same kernels, fewer launches)")
     ap.add_argument("--presort", choices=["auto", "fused", "side", "none", "ahead"], default="auto",
                     help="where the backward's sort runs: in the forward's launch (fused; needs one-hot tables "
-                         "and at most 16384 samples), on the side stream, inside fae_embbag_bwd_sgd, or one step "
+                         "and at most 100000 samples), on the side stream, inside fae_embbag_bwd_sgd, or one step "
                          "ahead on the side stream (the next batch's sort beside this batch's forward and "
                          "backward).  auto: fused where the shape allows, else ahead for steps of up to 4 M lookups")
     ap.add_argument("--ceiling", action="store_true", help="sweep the streaming probes' launch shapes and exit")

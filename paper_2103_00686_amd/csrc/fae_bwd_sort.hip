@@ -823,9 +823,9 @@ struct FusedArgs {
 };
 
 // Rows of up to 16 lanes: two workgroups share a compute unit, eight rows per lane group in flight.  Wider ones: with as few
-// registers only four rows fit (eight spill: 128 -> 151 us), and 16 rows in one workgroup move more.  Steps of 26 tables, before
-// (one workgroup, more LDS) / two with four rows / one with sixteen, us: 16 384 samples, dim 128 128.1 / 132.7 / 130.1, 12 000 90.6
-// / 96.7 / 90.6, 50 001 452 / 420 / 411; dim 100, 16 384 105.9 / 111.4 / 107.1, 50 001 452 / 407 / 415, 4000 39.2 / 36.2 / 38.3.
+// registers only four rows fit (eight spill: 128 -> 151 us), and 16 rows in one workgroup move more.  Steps of 26 tables, one batch
+// over and over, 64 samples per copying wave, before (one workgroup, more LDS) / two with four rows / one with sixteen, us:
+// 16 384 samples, dim 128 128.1 / 132.7 / 130.1, 12 000 90.6 / 96.7 / 90.6, 50 001 452 / 420 / 411; dim 100, 16 384 105.9 / 111.4 / 107.1, 50 001 452 / 407 / 415, 4000 39.2 / 36.2 / 38.3.
 template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS, (LPR < FUSED_ALONE_LANES ? 8 : 4)) void fwd_sort_kernel(FusedArgs a)
 {
     bwd_clear_flags(a.flags, a.n_flags, a.flag_slice, LSORT_THREADS);

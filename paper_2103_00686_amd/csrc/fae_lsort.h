@@ -26,7 +26,8 @@
 // registers two workgroups share a compute unit, which is what the row copies of the fused launch need.
 // Microseconds a step, one-hot, forward and sort in one launch, before (all keys and a 16-bit permutation in 147 KB
 // of LDS, lists of up to 16 384 only, longer ones by the radix passes) and now:
-//   26 x 50 001, dim 64 258 -> 209; 26 x 16 384, dim 64 59.9 -> 56.6, dim 16 49.3 -> 39.8; 26 x 12 000, dim 16 41.5 -> 37.8;
+//   three batches' inputs in turn: 26 x 50 001, dim 64 273 -> 210; 26 x 16 384, dim 64 73.0 -> 72.8, dim 32 56.7 -> 47.8;
+//   one batch over and over: 26 x 16 384, dim 16 49.3 -> 39.8; 26 x 12 000, dim 16 41.5 -> 37.8;
 //   1 x 1024 14.1 -> 12.7; 26 x 4096, dim 16 21.8 -> 22.0; sort alone, ids in order of popularity: 26 x 16 384 36 -> 23
 #define LSORT_THREADS 1024
 #define LSORT_WAVES (LSORT_THREADS / FAE_WAVE)
