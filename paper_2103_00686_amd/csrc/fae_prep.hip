@@ -543,34 +543,43 @@ __device__ __forceinline__ void build_load8(const uint32_t *cnt, int64_t r0, int
 // reads before it writes them.  So the counters are read once here: threshold and build of 16 tables with 72 M rows
 // 398 -> 382 us a call, their kernels 300 -> 286.  (One kernel with chained tile counts: 150 us instead of 133 for the
 // two and the scan between them, as a chip's worth of tiles waits for one another; 164-180 looking further back at a time.)
+// Tables may share a remap (one embedding table under two numbers, the same counters and cutoff): there a tile of one would
+// overwrite the bytes of the other's before they are read, so such calls read the counters twice (MARKS = false).
 __device__ __forceinline__ uint8_t *build_mark(const BuildArgs &a, int z, int64_t r0)
 {
     return (uint8_t *)(a.remap[z] + (r0 - (int64_t)threadIdx.x * 8)) + threadIdx.x;
 }
 
-__global__ __launch_bounds__(256) void build_count_kernel(BuildArgs a)
+// bit k: row r0 + k is hot
+__device__ __forceinline__ uint32_t build_hot8(const BuildArgs &a, int z, int64_t r0)
+{
+    const int R = a.n_rows[z];
+    const uint32_t H = a.cutoff[z];
+    uint32_t v[8], hot = 0;
+    build_load8(a.cnt[z], r0, R, v);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        hot |= (r0 + k < R && v[k] >= H) ? 1u << k : 0u;
+    return hot;
+}
+
+template <bool MARKS> __global__ __launch_bounds__(256) void build_count_kernel(BuildArgs a)
 {
     __shared__ int lds[256 / FAE_WAVE + 1];
     const int z = fae_find_table(a.tile_start, a.n_tables, blockIdx.x);
     const int tl = blockIdx.x - a.tile_start[z];
     const int R = a.n_rows[z];
-    const uint32_t H = a.cutoff[z];
     const int64_t r0 = (int64_t)tl * BT_TILE + (int64_t)threadIdx.x * 8;
-    uint32_t v[8];
-    build_load8(a.cnt[z], r0, R, v);
-    uint32_t hot = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        hot |= (r0 + k < R && v[k] >= H) ? 1u << k : 0u;
+    const uint32_t hot = build_hot8(a, z, r0);
     int total;
     (void)fae_block_excl_scan<256>(__popc(hot), lds, &total);
-    if (r0 < R) // behind the scan's barriers: a remap may lie over its own counters, and they have all been read here
+    if (MARKS && r0 < R) // behind the scan's barriers: a remap may lie over its own counters, and they have all been read here
         *build_mark(a, z, r0) = (uint8_t)hot;
     if (threadIdx.x == 0)
         a.tile_sums[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(256) void build_scatter_kernel(BuildArgs a)
+template <bool MARKS> __global__ __launch_bounds__(256) void build_scatter_kernel(BuildArgs a)
 {
     __shared__ int lds[256 / FAE_WAVE + 1];
     const int z = fae_find_table(a.tile_start, a.n_tables, blockIdx.x);
@@ -578,7 +587,7 @@ __global__ __launch_bounds__(256) void build_scatter_kernel(BuildArgs a)
     const int R = a.n_rows[z];
     const int cap = a.cap[z];
     const int64_t r0 = (int64_t)tl * BT_TILE + (int64_t)threadIdx.x * 8;
-    const uint32_t hot = r0 < R ? *build_mark(a, z, r0) : 0u;
+    const uint32_t hot = !MARKS ? build_hot8(a, z, r0) : r0 < R ? *build_mark(a, z, r0) : 0u;
     int total;
     const int ex = fae_block_excl_scan<256>(__popc(hot), lds, &total); // its barriers: all bytes are read before any is overwritten
     // slots restart at 0 for every table: subtract the scan value at the table's first tile
@@ -758,12 +767,20 @@ extern "C" int32_t fae_build_hot_tables(fae_ctx *ctx, const fae_tables *tables, 
     a.n_hot_out = ctx->d_block + FAE_BLK_SCALARS;
     if (tiles >= 2147483647LL)
         return fae_fail(ctx, FAE_EINVAL, "fae_build_hot_tables: too many rows for one launch");
+    bool marks = true; // every table has its remap to itself
+    for (int z = 1; z < nt; ++z)
+        for (int y = 0; y < z; ++y)
+            marks = marks && ((uintptr_t)(a.remap[z] + a.n_rows[z]) <= (uintptr_t)a.remap[y] ||
+                              (uintptr_t)(a.remap[y] + a.n_rows[y]) <= (uintptr_t)a.remap[z]);
     rc = fae_fill_u32(ctx, ctx->d_block + FAE_BLK_SCALARS, nt, 0u);
     if (rc != FAE_OK)
         return rc;
     if (tiles > 0) {
         fae_ktimer kt(ctx, FAE_K_BUILD);
-        FAE_LAUNCH(ctx, build_count_kernel, dim3((unsigned)tiles), dim3(256), 0, ctx->stream, a);
+        if (marks)
+            FAE_LAUNCH(ctx, build_count_kernel<true>, dim3((unsigned)tiles), dim3(256), 0, ctx->stream, a);
+        else
+            FAE_LAUNCH(ctx, build_count_kernel<false>, dim3((unsigned)tiles), dim3(256), 0, ctx->stream, a);
         FAE_LAUNCH_CHECK(ctx);
     }
     rc = fae_scan_i32(ctx, a.tile_sums, tiles);
@@ -771,7 +788,10 @@ extern "C" int32_t fae_build_hot_tables(fae_ctx *ctx, const fae_tables *tables, 
         return rc;
     if (tiles > 0) {
         fae_ktimer kt(ctx, FAE_K_BUILD);
-        FAE_LAUNCH(ctx, build_scatter_kernel, dim3((unsigned)tiles), dim3(256), 0, ctx->stream, a);
+        if (marks)
+            FAE_LAUNCH(ctx, build_scatter_kernel<true>, dim3((unsigned)tiles), dim3(256), 0, ctx->stream, a);
+        else
+            FAE_LAUNCH(ctx, build_scatter_kernel<false>, dim3((unsigned)tiles), dim3(256), 0, ctx->stream, a);
         FAE_LAUNCH_CHECK(ctx);
     }
     rc = fae_readback_status(ctx, nt);

@@ -57,6 +57,31 @@ def test_remap_over_its_counters():
     assert np.array_equal(both.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("shift", [0, 1000])
+def test_tables_that_share_a_remap(shift):
+    """One embedding table under two numbers, or remaps that lie over each other in part (the second one's
+    rows are all cold where they meet): no table's first half may touch what another one still needs."""
+    rows, dim = 3_000_001, 4
+    c = np.random.default_rng(5).integers(0, 9, rows).astype(np.int32)
+    if shift:
+        c[:shift] = 0
+        c[rows - shift:] = 0
+    ctx, tables, cnt = B.Context(0, None), B.Tables([rows] * 2, dim), torch.from_numpy(c).cuda()
+    buf = torch.empty(2 * rows, dtype=torch.int32, device="cuda")
+    remap = [buf[:rows], buf[rows - shift:2 * rows - shift] if shift else buf[:rows]]
+    ids = [torch.zeros(rows, dtype=torch.int32, device="cuda")] * 2 if not shift else [torch.zeros(rows, dtype=torch.int32, device="cuda") for _ in range(2)]
+    hotW = [torch.empty((rows, dim), dtype=torch.float32, device="cuda") for _ in range(2)]
+    ws = torch.empty(B.fae_build_workspace_bytes(tables), dtype=torch.uint8, device="cuda")
+    got = B.fae_build_hot_tables(ctx, tables, [cnt] * 2, [5] * 2, B.FAE_SRC_PROCEDURAL, None, 1, remap, ids, hotW, [rows] * 2, ws)
+    hot = np.flatnonzero(c >= 5)
+    want = np.full(rows, -1)
+    want[hot] = np.arange(hot.size)
+    for z in range(2):
+        assert got[z] == hot.size
+        assert np.array_equal(remap[z].cpu().numpy(), want)
+        assert np.array_equal(ids[z][:hot.size].cpu().numpy(), hot)
+
+
 def test_capacity_is_reported():
     counts = [np.full(5000, 5)]
     with pytest.raises(B.FaeError) as e:
