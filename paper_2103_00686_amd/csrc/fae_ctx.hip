@@ -353,6 +353,7 @@ extern "C" int32_t fae_sync(fae_ctx *ctx)
 {
     if (!ctx)
         return FAE_EINVAL;
+    FAE_HIP(ctx, hipSetDevice(ctx->device)); // the status goes out with a kernel, and the caller's thread may be on another device
     return fae_sync_status(ctx);
 }
 
