@@ -10,7 +10,7 @@
 //   2. goes over the bits and takes the lookups of its range in batch order into LDS;
 //   3. sorts them there (LSD radix passes, or, where they are few, by counting the keys in front of each).
 // Lists of up to LSORT_SPLIT_MAX lookups are split by the top bits of the slot.  Longer ones are split by the ranks of
-// a sample of 1024 lookups, taken at even distances (lsort_bounds): to single slots where many lookups
+// a sample of 1024 lookups, one out of every 1024th of the list (lsort_bounds): to single slots where many lookups
 // crowd on few, so that popular slots next to each other (ids in order of popularity) end up in different parts.  A slot that
 // owns much of the batch is the last one of its part then: its lookups go straight to their places (their order is
 // right as it is) and take no part in the sort, and where it fills several parts the workgroups of
@@ -58,6 +58,17 @@ struct LsortLds {
 };
 static_assert(2 * LSORT_SAMPLES <= LSORT_WORDS, "two histograms of a digit of ten bits");
 
+// The number of sample t of n >= LSORT_SAMPLES lookups: one out of every n / LSORT_SAMPLES, its place among these from a Weyl
+// sequence.  (At even distances all samples are the same entry of a bag where bags have one length that divides
+// the distance: 2048 bags of 50 on one table, sorted inside or with a first entry out of ten, put 100 K lookups into one part, sort alone
+// 30 us without such bags, 1040 to 1120 with them, 29 now.)  The same for all workgroups of a table.
+__device__ __forceinline__ int lsort_sample(int t, int n)
+{
+    const uint32_t at = (uint32_t)t * (uint32_t)n / LSORT_SAMPLES, next = (uint32_t)(t + 1) * (uint32_t)n / LSORT_SAMPLES;
+    static_assert((uint64_t)LSORT_SAMPLES * LSORT_MAX < 1ull << 32, "in 32 bits");
+    return (int)(at + __umulhi((uint32_t)t * 0x9E3779B1u, next - at)); // 2^32 times the golden ratio's fraction
+}
+
 // Lower and upper bound of a part: bound(t) = the lowest slot with at least t samples below it, for t = part / parts and
 // (part + 1) / parts of the samples; found ten bits at a time, from the top, among the samples that agree in
 // the bits above.  A bin with few samples is not looked into (its end is taken), which depends on t and the samples
@@ -70,7 +81,7 @@ __device__ __forceinline__ bool lsort_bounds(LsortLds &s, const int32_t *slots, 
     constexpr int BITS = 10;
     static_assert(LSORT_SAMPLES == LSORT_THREADS && 1 << BITS == LSORT_THREADS, "a sample and a bin per thread");
     const int t = threadIdx.x;
-    uint32_t k = (uint32_t)slots[(int64_t)t * n / LSORT_SAMPLES];
+    uint32_t k = (uint32_t)slots[lsort_sample(t, n)];
     k = k < n_hot ? k : n_hot;
     const int few = LSORT_SAMPLES / (4 * parts);
     int want[2] = {part * LSORT_SAMPLES / parts, (part + 1) * LSORT_SAMPLES / parts};

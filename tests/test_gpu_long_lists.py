@@ -13,6 +13,13 @@ pytestmark = pytest.mark.gpu
 ROWS = 300_000  # three radix passes: beyond 16 384 lookups the LDS sort takes only these by itself
 
 
+def _sampled(n):
+    """The lookups that split a list: one out of every 1024th of it, placed by a Weyl sequence."""
+    t = np.arange(1024, dtype=np.uint64)
+    at, nxt = t * np.uint64(n) // np.uint64(1024), (t + np.uint64(1)) * np.uint64(n) // np.uint64(1024)
+    return (at + ((t * np.uint64(0x9E3779B1) % np.uint64(1 << 32)) * (nxt - at) >> np.uint64(32))).astype(np.int64)
+
+
 def _slots(kind, n, rng):
     if kind == "uniform":
         return rng.integers(0, ROWS, n)
@@ -28,7 +35,7 @@ def _slots(kind, n, rng):
         return s
     if kind == "misled":  # every sampled lookup is on slot 7, hardly any other
         s = rng.integers(1000, ROWS, n)
-        s[np.arange(1024, dtype=np.int64) * n // 1024] = 7
+        s[_sampled(n)] = 7
         return s
     return np.where(rng.random(n) < 0.5, rng.integers(0, 3, n), rng.integers(0, ROWS, n))  # "few": three own half
 
@@ -103,3 +110,50 @@ def test_row_copies_beside_the_sort(nt, n, dim):
     want = _step(1, one, [None] * nt, n, [n] * nt, fused=True, rows=999, dim=dim)[1]
     got = _step(0, one, [None] * nt, n, [n] * nt, fused=True, rows=999, dim=dim)[1]
     assert all(torch.equal(a, b) for a, b in zip(want, got))
+
+
+def _sort_us(slots, off, S):
+    """Time of the LDS sort's kernel for one table (the shortest of several)."""
+    hp = HotPath([ROWS], 4)
+    hp.alloc_counts()
+    hp.build([0], [ROWS], seed=3)
+    hb = HotBatch(S, [torch.from_numpy(slots.astype(np.int32)).cuda()], [off], [slots.size])
+    gout = torch.zeros((S, 1, 4), device="cuda")
+    kernel = [B.fae_kernel_name(k) for k in range(B.FAE_K_COUNT)].index("lds_sort")
+    times = []
+    for _ in range(8):
+        B.fae_timing_enable(hp.ctx, True)
+        B.fae_timing_reset(hp.ctx)
+        hp.backward_sgd(hb, gout, 0.0)
+        hp.sync()
+        ms, launches = B.fae_timing_read(hp.ctx, kernel)
+        assert launches == 1
+        times.append(ms * 1e3)
+    return min(times)
+
+
+def _bags_of_one_length(kind, S, L, rng):
+    s = (rng.random((S, L)) ** 4 * ROWS).astype(np.int64) * 7 % ROWS
+    if kind == "typed":  # the first entry is one of ten types
+        s[:, 0] = 100 + 7 * rng.integers(0, 10, S)
+    elif kind == "sorted":
+        s.sort(axis=1)
+    else:  # histories padded with slot 0
+        pad, place = rng.integers(0, L, S)[:, None], np.arange(L)[None, :]
+        s[place < pad if kind == "left" else place >= L - pad] = 0
+    return s.reshape(-1)
+
+
+@pytest.mark.parametrize("S,L", [(2048, 50), (1024, 100), (2048, 32), (4096, 24), (16384, 6)])
+@pytest.mark.parametrize("kind", ["typed", "sorted", "left", "right"])
+def test_bags_of_one_length(S, L, kind):
+    """The sort's time does not depend on where in the list the lookups of a slot are: not twice that of the same
+    lookups in any order (it was 4 to 40 times that where all samples met one position of a bag)."""
+    rng = np.random.default_rng(S + L)
+    s = _bags_of_one_length(kind, S, L, rng)
+    off = torch.arange(0, S * L + 1, L, dtype=torch.int32, device="cuda")
+    slots = [torch.from_numpy(s.astype(np.int32)).cuda()]
+    want, got = (_step(v, slots, [off], S, [S * L])[1] for v in (1, 0))
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    us, mixed = _sort_us(s, off, S), _sort_us(rng.permutation(s), off, S)
+    assert us <= 2 * mixed, f"{us:.1f} us, in any order {mixed:.1f}"
