@@ -6,16 +6,18 @@
 
 // A table's keys are split into parts, ranges of slots, a workgroup each.  The parts' outputs are laid end
 // to end: a part starts behind all lookups with lower slots.  A workgroup
-//   1. goes over all keys of its table and leaves two bits per lookup in registers: below its range, below its end;
+//   1. goes over all keys of its table and leaves a bit per lookup in registers, in its range or not (a second one for the range's
+//      last slot where that is left out of the sort, see below), and adds up the lookups below its range;
 //   2. goes over the bits and takes the lookups of its range in batch order into LDS;
 //   3. sorts them there (LSD radix passes, or, where they are few, by counting the keys in front of each).
-// Lists of up to LSORT_SPLIT_MAX lookups are split by the top bits of the slot.  Longer ones are split by the ranks of
+// Lists of up to LSORT_CAP lookups are split by the top bits of the slot, those of up to LSORT_SPLIT_MAX too unless that
+// would leave a part with far more than its share (lsort_uneven).  Others are split by the ranks of
 // a sample of 1024 lookups, one out of every 1024th of the list (lsort_bounds): to single slots where many lookups
 // crowd on few, so that popular slots next to each other (ids in order of popularity) end up in different parts.  A slot that
 // owns much of the batch is the last one of its part then: its lookups go straight to their places (their order is
 // right as it is) and take no part in the sort, and where it fills several parts the workgroups of
-// these share them.  Should a part hold more than LSORT_CAP lookups all the same, it is worked off in pieces, lower half
-// first, until each fits; a piece of one slot always does, since nothing of it is sorted.
+// these share them.  Should a part hold more than LSORT_CAP lookups all the same, it is worked off in pieces whose ends
+// are the ranks of other samples (lsort_piece).
 //
 // Bound by instructions and by the chain of its phases, not by memory (the keys come from the L2): every workgroup
 // of a table goes over all its keys, so a key costs five vector instructions there (the sign of a difference,
@@ -39,6 +41,9 @@
 #define LSORT_STEP (FAE_WAVE * LSORT_KEYS)
 #define LSORT_STEPS ((LSORT_MAX + LSORT_WAVES * LSORT_STEP) / (LSORT_WAVES * LSORT_STEP)) // of a wave, at most
 #define LSORT_SAMPLES 1024
+#define LSORT_PARTS 16    // of a list that is split by the top bits of the slot, at most
+#define LSORT_UNEVEN 2048 // lookups beyond an even share that take a part longer than bounds by rank would (1.4 us per 1024 / 2.5 us)
+#define LSORT_PIECE 5000  // lookups of a piece of a part that does not fit
 #define LSORT_SPLIT_MAX 10240 // lookups up to which the top bits of the slot split a list: the sample costs 2 us (1 x 9000 18.9 -> 20.3, 1 x 11 642 28.6 either way, 26 x 12 000 43.8 -> 37.1 a step)
 #define LSORT_BITS 9 // of a digit, at most
 #define LSORT_DIGITS (1 << LSORT_BITS)
@@ -58,53 +63,60 @@ struct LsortLds {
 };
 static_assert(2 * LSORT_SAMPLES <= LSORT_WORDS, "two histograms of a digit of ten bits");
 
-// The number of sample t of n >= LSORT_SAMPLES lookups: one out of every n / LSORT_SAMPLES, its place among these from a Weyl
-// sequence.  (At even distances all samples are the same entry of a bag where bags have one length that divides
-// the distance: 2048 bags of 50 on one table, sorted inside or with a first entry out of ten, put 100 K lookups into one part, sort alone
-// 30 us without such bags, 1040 to 1120 with them, 29 now.)  The same for all workgroups of a table.
-__device__ __forceinline__ int lsort_sample(int t, int n)
+// The number of sample t out of SAMPLES of n >= SAMPLES lookups: one of every n / SAMPLES, its place among these from a Weyl
+// sequence, another part of it for other tries; the same for all workgroups of a table.  (At even distances all samples are the
+// same entry of a bag where bags have one length that divides the distance: 2048 bags of 50 on one table, sorted inside or with
+// a first entry out of ten, put 100 K lookups into one part, sort alone 30 us without such bags, 1040 to 1120 with them, 29 now.)
+template <int SAMPLES> __device__ __forceinline__ int lsort_sample(int t, int n, int tries)
 {
-    const uint32_t at = (uint32_t)t * (uint32_t)n / LSORT_SAMPLES, next = (uint32_t)(t + 1) * (uint32_t)n / LSORT_SAMPLES;
-    static_assert((uint64_t)LSORT_SAMPLES * LSORT_MAX < 1ull << 32, "in 32 bits");
-    return (int)(at + __umulhi((uint32_t)t * 0x9E3779B1u, next - at)); // 2^32 times the golden ratio's fraction
+    const uint32_t at = (uint32_t)t * (uint32_t)n / SAMPLES, next = (uint32_t)(t + 1) * (uint32_t)n / SAMPLES;
+    static_assert((uint64_t)SAMPLES * LSORT_MAX < 1ull << 32, "in 32 bits");
+    return (int)(at + __umulhi((uint32_t)(t + tries * SAMPLES) * 0x9E3779B1u, next - at)); // 2^32 times the golden ratio's fraction
 }
 
-// Lower and upper bound of a part: bound(t) = the lowest slot with at least t samples below it, for t = part / parts and
-// (part + 1) / parts of the samples; found ten bits at a time, from the top, among the samples that agree in
-// the bits above.  A bin with few samples is not looked into (its end is taken), which depends on t and the samples
-// alone, so neighbours agree on the bound between them.  A slot that owns many lookups (crowd) may
-// fill several parts: the first one ends with it, the others are left empty and take a share of its lookups instead
-// (share of shares; slots from hi - 1 on then, without sorting anything).
-__device__ __forceinline__ bool lsort_bounds(LsortLds &s, const int32_t *slots, int n, uint32_t n_hot, int part, int parts, uint32_t *lo, uint32_t *hi,
-                                             int *share, int *shares)
+// For each open b: bound[b] = the lowest slot with at least want[b] (>= 1) of the samples below it, the samples being the threads'
+// keys k; found ten bits at a time, from the top, among the samples that agree in the bits above.  A bin with at most `few`
+// samples is not looked into (its end is taken), which depends on want[b] and the samples alone, so neighbours agree on the
+// bound between them.  crowd[b] = samples of the slot in front of the bound where these are more than `few`, want[b] =
+// how many of them are wanted; else crowd[b] = 0.
+template <int NB>
+__device__ __forceinline__ void lsort_find(LsortLds &s, uint32_t k, uint32_t n_hot, int few, bool (&open)[NB], int (&want)[NB], uint32_t (&bound)[NB],
+                                           int (&crowd)[NB])
 {
     constexpr int BITS = 10;
     static_assert(LSORT_SAMPLES == LSORT_THREADS && 1 << BITS == LSORT_THREADS, "a sample and a bin per thread");
     const int t = threadIdx.x;
-    uint32_t k = (uint32_t)slots[lsort_sample(t, n)];
-    k = k < n_hot ? k : n_hot;
-    const int few = LSORT_SAMPLES / (4 * parts);
-    int want[2] = {part * LSORT_SAMPLES / parts, (part + 1) * LSORT_SAMPLES / parts};
-    uint32_t pre[2] = {0u, 0u}, bound[2] = {0u, n_hot + 1u};
-    bool open[2] = {part > 0, part + 1 < parts}, crowd = false;
-    for (int sh = 32 - __builtin_clz(n_hot | 1u); (open[0] || open[1]) && sh > 0;) {
+    uint32_t pre[NB];
+    bool any = false;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        pre[b] = 0u;
+        crowd[b] = 0;
+        any = any || open[b];
+    }
+    for (int sh = 32 - __builtin_clz(n_hot | 1u); any && sh > 0;) {
         const int bits = sh < BITS ? sh : BITS;
         const int up = sh;
         sh -= bits;
-        s.word[t] = 0;
-        s.word[LSORT_SAMPLES + t] = 0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            s.word[b * LSORT_SAMPLES + t] = 0;
         __syncthreads();
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < NB; ++b)
             if (open[b] && k >> up == pre[b])
                 atomicAdd(&s.word[b * LSORT_SAMPLES + ((k >> sh) & ((1u << bits) - 1u))], 1);
         __syncthreads();
-        const int own[2] = {s.word[t], s.word[LSORT_SAMPLES + t]};
-        int all;
-        const int ex = fae_block_excl_scan<LSORT_THREADS, true>(own[1] << 16 | own[0], s.scan, &all);
+        int own[NB], sum = 0, all;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int before = b == 0 ? ex & 0xffff : ex >> 16;
+        for (int b = 0; b < NB; ++b) {
+            own[b] = s.word[b * LSORT_SAMPLES + t];
+            sum += own[b] << 16 * b;
+        }
+        const int ex = fae_block_excl_scan<LSORT_THREADS, true>(sum, s.scan, &all);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int before = ex >> 16 * b & 0xffff;
             if (open[b] && want[b] > before && want[b] <= before + own[b]) { // one thread
                 s.misc[b] = t;
                 s.misc[2 + b] = want[b] - before;
@@ -112,8 +124,9 @@ __device__ __forceinline__ bool lsort_bounds(LsortLds &s, const int32_t *slots, 
             }
         }
         __syncthreads();
+        any = false;
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < NB; ++b) {
             if (open[b]) {
                 pre[b] = pre[b] << bits | (uint32_t)__builtin_amdgcn_readfirstlane(s.misc[b]);
                 want[b] = __builtin_amdgcn_readfirstlane(s.misc[2 + b]);
@@ -121,23 +134,74 @@ __device__ __forceinline__ bool lsort_bounds(LsortLds &s, const int32_t *slots, 
                 if (sh == 0 || here <= few) {
                     bound[b] = (pre[b] + 1u) << sh;
                     open[b] = false;
-                    if (b == 1 && sh == 0 && here > few) {
-                        crowd = true;
-                        // the parts whose upper bound lies among the samples of this slot: under + 1 .. under + here
-                        const int under = (part + 1) * LSORT_SAMPLES / parts - want[1];
-                        const int first = ((under + 1) * parts + LSORT_SAMPLES - 1) / LSORT_SAMPLES - 1;
-                        const int end = ((under + here + 1) * parts + LSORT_SAMPLES - 1) / LSORT_SAMPLES - 1;
-                        *share = part - first;
-                        *shares = (end < parts - 1 ? end : parts - 1) - first;
-                    }
+                    crowd[b] = sh == 0 && here > few ? here : 0;
                 }
             }
+            any = any || open[b];
+        }
     }
+}
+
+// Bounds of a part: lsort_find's for part / parts and (part + 1) / parts of the samples.  A slot that owns many lookups may
+// fill several parts: the first one ends with it, the others are left empty and take a share of its lookups instead
+// (share of shares; slots from hi - 1 on then, without sorting anything).  Returns whether the last slot is to be left out of the sort.
+__device__ __forceinline__ bool lsort_bounds(LsortLds &s, const int32_t *slots, int n, uint32_t n_hot, int part, int parts, uint32_t *lo, uint32_t *hi,
+                                             int *share, int *shares)
+{
+    uint32_t k = (uint32_t)slots[lsort_sample<LSORT_SAMPLES>(threadIdx.x, n, 0)];
+    k = k < n_hot ? k : n_hot;
+    const int upto = (part + 1) * LSORT_SAMPLES / parts;
+    int want[2] = {part * LSORT_SAMPLES / parts, upto}, here[2];
+    uint32_t bound[2] = {0u, n_hot + 1u};
+    bool open[2] = {part > 0, part + 1 < parts};
+    lsort_find<2>(s, k, n_hot, LSORT_SAMPLES / (4 * parts), open, want, bound, here);
     *lo = bound[0] < n_hot + 1u ? bound[0] : n_hot + 1u;
     *hi = bound[1] < n_hot + 1u ? bound[1] : n_hot + 1u;
-    if (crowd && *share > 0)
+    if (here[1] == 0)
+        return false;
+    // the parts whose upper bound lies among the samples of this slot: under + 1 .. under + here
+    const int under = upto - want[1];
+    const int first = ((under + 1) * parts + LSORT_SAMPLES - 1) / LSORT_SAMPLES - 1;
+    const int end = ((under + here[1] + 1) * parts + LSORT_SAMPLES - 1) / LSORT_SAMPLES - 1;
+    *share = part - first;
+    *shares = (end < parts - 1 ? end : parts - 1) - first;
+    if (*share > 0)
         *lo = *hi - 1u;
-    return crowd;
+    return true;
+}
+
+// Where slots lo .. top - 1 hold `over` lookups, more than fit: the end of a first piece of about LSORT_PIECE, by other samples of the
+// list for each try; by halves, which end with a single slot, if these do not help.  *crowd: as lsort_bounds returns.
+__device__ __forceinline__ uint32_t lsort_piece(LsortLds &s, const int32_t *slots, int n, uint32_t n_hot, uint32_t lo, uint32_t top, int over, int tries,
+                                                bool *crowd)
+{
+    uint32_t k = (uint32_t)slots[lsort_sample<LSORT_SAMPLES>(threadIdx.x, n, tries)];
+    k = k < n_hot ? k : n_hot;
+    int both; // samples below lo, and in the range
+    (void)fae_block_excl_scan<LSORT_THREADS>((k >= lo && k < top ? 1 << 16 : 0) + (k < lo ? 1 : 0), s.scan, &both);
+    const int in = both >> 16, pieces = (over + LSORT_PIECE - 1) / LSORT_PIECE; // at least two
+    int want[1] = {(both & 0xffff) + in / pieces}, here[1];
+    uint32_t bound[1] = {top - lo > 1u ? lo + (top - lo) / 2u : top};
+    bool open[1] = {tries <= 3 && in >= 2 * pieces};
+    lsort_find<1>(s, k, n_hot, in / (8 * pieces), open, want, bound, here);
+    const uint32_t end = bound[0] < top ? bound[0] : top;
+    *crowd = here[0] > 0 || end - lo == 1u;
+    return end;
+}
+
+// Whether equal ranges of slots (the top bits) make a part of a list of up to LSORT_SPLIT_MAX lookups too large: by 64 samples, the same for
+// every wave of every workgroup of a table.
+__device__ __forceinline__ bool lsort_uneven(const int32_t *slots, int n, uint32_t n_hot, int part_shift, int parts)
+{
+    uint32_t k = (uint32_t)slots[lsort_sample<FAE_WAVE>(fae_lane(), n, 0)];
+    k = (k < n_hot ? k : n_hot) >> part_shift;
+    int most = 0;
+#pragma unroll
+    for (int p = 0; p < LSORT_PARTS; ++p) {
+        const int c = __popcll(__ballot(k == (uint32_t)p));
+        most = c > most ? c : most;
+    }
+    return most * n / FAE_WAVE > n / parts + LSORT_UNEVEN;
 }
 
 // The wave's lookups beg .. end - 1, in steps of which a lane has `per` consecutive ones: LSORT_KEYS, or four where
@@ -355,22 +419,23 @@ struct LsortBags {
 };
 
 // Part `part` of `parts` of a table's n lookups; part_shift: part of a slot = slot >> part_shift, for
-// lists of up to LSORT_CAP.  keys_out / vals_out: the table's segment of the sorted pairs.
+// lists that the top bits split.  keys_out / vals_out: the table's segment of the sorted pairs.
 __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32_t *off, int n, int n_hot_z, int part, int parts, int part_shift,
                                                int n_samples, int32_t *keys_out, int32_t *vals_out, uint32_t *status)
 {
     __shared__ __align__(16) LsortLds s;
     const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / FAE_WAVE), lane = fae_lane();
     const uint32_t n_hot = (uint32_t)n_hot_z;
-    uint32_t lo, hi; // the part's slots
+    uint32_t lo = (uint32_t)part << part_shift, hi = (uint32_t)(part + 1) << part_shift; // the part's slots
+    hi = hi < n_hot + 1u ? hi : n_hot + 1u;
     bool crowd = false; // the last of them is left out of the sort
     int share = 0, shares = 1;
-    if (n <= LSORT_SPLIT_MAX) {
-        lo = (uint32_t)part << part_shift;
-        hi = (uint32_t)(part + 1) << part_shift;
-        hi = hi < n_hot + 1u ? hi : n_hot + 1u;
-    } else {
+    bool by_rank = n > LSORT_SPLIT_MAX;
+    if (n > LSORT_CAP && !by_rank)
+        by_rank = lsort_uneven(slots, n, n_hot, part_shift, parts);
+    if (by_rank) {
         crowd = lsort_bounds(s, slots, n, n_hot, part, parts, &lo, &hi, &share, &shares);
+        __syncthreads(); // its counts are read
     }
     LsortList l;
     l.slots = slots;
@@ -382,10 +447,17 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
     l.per = per_wave > 256 ? LSORT_KEYS : 4;
     LsortBags bags = {off, n_samples, (n_samples + LSORT_WORDS) / LSORT_WORDS, 0};
     bags.m = (n_samples + bags.step) / bags.step;
-    if (n > LSORT_SPLIT_MAX)
-        __syncthreads(); // the split's counts are read
     bool bad = false;
+    int left = 0;             // lookups on slots lo .. hi - 1, once they are counted
+    int over = 0, tries = 1;  // lookups on slots lo .. top - 1 where these are known not to fit
     for (uint32_t top = hi; lo < hi;) { // slots lo .. top - 1; more than once only if a part does not fit
+        if (over > 0) {
+            top = lsort_piece(s, slots, n, n_hot, lo, top, over, tries++, &crowd);
+            share = 0;
+            shares = 1;
+            over = 0;
+            __syncthreads(); // its counts are read
+        }
         if (off)
             bags.stage(s);
         LsortMask in, last;
@@ -407,13 +479,10 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
         const int n_part = __builtin_amdgcn_readlane(in_upto, LSORT_WAVES - 1);
         const int all_last = __builtin_amdgcn_readlane(last_upto, LSORT_WAVES - 1);
         const int all_below = __builtin_amdgcn_readlane(below_upto, LSORT_WAVES - 1);
+        if (top == hi)
+            left = n_part + all_last;
         if (n_part > LSORT_CAP) { // then of at least two slots, or of one that is not left out
-            if (top - lo > 1u)
-                top = lo + (top - lo) / 2u;
-            crowd = top - lo == 1u;
-            share = 0;
-            shares = 1;
-            __syncthreads(); // the counts are written again
+            over = n_part + all_last;
             continue;
         }
         const bool few = n_part <= LSORT_RANK_MAX;
@@ -478,11 +547,14 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
             if (n_part > 0 && s.key[n_part - 1] == n_hot_z)
                 bad = true;
         }
+        left -= n_part + all_last;
         lo = top;
         top = hi;
         crowd = false;
         share = 0;
         shares = 1;
+        tries = 1;
+        over = left > LSORT_CAP ? left : 0;
         if (lo < hi)
             __syncthreads(); // LDS is filled again
     }

@@ -1,4 +1,4 @@
-"""The LDS sort of lists that are split by a sample of their lookups (beyond 10 240, up to 128 K): the same bytes
+"""The LDS sort of lists that do not fit one part (beyond 7168 lookups, up to 128 K): the same bytes
 as from the radix passes (sort_variant 1) at the edges of its rules, with slots that own several parts,
 neighbouring popular slots, samples that mislead, offsets beyond what LDS holds, slots out of range and a
 list that does not start on 16 bytes."""
@@ -13,11 +13,12 @@ pytestmark = pytest.mark.gpu
 ROWS = 300_000  # three radix passes: beyond 16 384 lookups the LDS sort takes only these by itself
 
 
-def _sampled(n):
+def _sampled(n, tries=0, samples=1024):
     """The lookups that split a list: one out of every 1024th of it, placed by a Weyl sequence."""
-    t = np.arange(1024, dtype=np.uint64)
-    at, nxt = t * np.uint64(n) // np.uint64(1024), (t + np.uint64(1)) * np.uint64(n) // np.uint64(1024)
-    return (at + ((t * np.uint64(0x9E3779B1) % np.uint64(1 << 32)) * (nxt - at) >> np.uint64(32))).astype(np.int64)
+    u64 = np.uint64
+    t = np.arange(samples, dtype=u64)
+    at, nxt = t * u64(n) // u64(samples), (t + u64(1)) * u64(n) // u64(samples)
+    return (at + (((t + u64(tries * samples)) * u64(0x9E3779B1) % u64(1 << 32)) * (nxt - at) >> u64(32))).astype(np.int64)
 
 
 def _slots(kind, n, rng):
@@ -37,6 +38,14 @@ def _slots(kind, n, rng):
         s = rng.integers(1000, ROWS, n)
         s[_sampled(n)] = 7
         return s
+    if kind == "misled often":  # and so are the samples that split what did not fit, and the few that look for uneven parts
+        s = rng.integers(1000, 1000 + ROWS // 16, n)
+        for tries in range(4):
+            s[_sampled(n, tries)] = 7
+        s[_sampled(n, 0, 64)] = np.arange(64) * ROWS // 64
+        return s
+    if kind in ("default", "ordered few"):  # one slot owns nine tenths; all lookups on a few slots next to each other
+        return np.where(rng.random(n) < 0.9, 191_001, rng.integers(0, ROWS, n)) if kind == "default" else (rng.random(n) ** 3 * 40).astype(np.int64)
     return np.where(rng.random(n) < 0.5, rng.integers(0, 3, n), rng.integers(0, ROWS, n))  # "few": three own half
 
 
@@ -53,7 +62,7 @@ def _step(variant, slots, offs, S, lengths, fused=False, rows=ROWS, dim=4):
     return hp, list(uniq) + list(runs) + [w.clone() for w in hp.hotW] + ([out.clone()] if fused else [])
 
 
-KINDS = ["uniform", "one", "ordered", "heavy", "misled", "few"]
+KINDS = ["uniform", "one", "ordered", "heavy", "misled", "misled often", "default", "ordered few", "few"]
 
 
 @pytest.mark.parametrize("n", [7168, 7169, 10_240, 10_241, 16384, 16385, 40_003, 100_000, 131_071])
@@ -157,3 +166,13 @@ def test_bags_of_one_length(S, L, kind):
     assert all(torch.equal(a, b) for a, b in zip(want, got))
     us, mixed = _sort_us(s, off, S), _sort_us(rng.permutation(s), off, S)
     assert us <= 2 * mixed, f"{us:.1f} us, in any order {mixed:.1f}"
+
+
+@pytest.mark.parametrize("n", [7169, 8192, 10_000, 12_000, 16_384])
+@pytest.mark.parametrize("share", [0.75, 0.9, 0.97])
+def test_one_slot_owns_most_of_a_list(n, share):
+    """Not three times the time of a list without such a slot (it was twelve times that up to 10 240 lookups)."""
+    rng = np.random.default_rng(n)
+    even = rng.integers(0, ROWS, n)
+    us, without = _sort_us(np.where(rng.random(n) < share, 191_001, even), None, n), _sort_us(even, None, n)
+    assert us <= 3 * without, f"{us:.1f} us, without {without:.1f}"
