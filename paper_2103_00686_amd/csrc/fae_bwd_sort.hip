@@ -486,7 +486,9 @@ __global__ __launch_bounds__(LSORT_THREADS, 8) void lds_sort_kernel(LsortArgs a)
 // Samples per copying wave of the fused launch: its workgroups fill what the sorting ones leave of the chip, and pieces of 64
 // left a nearly empty last round.  26 tables, three batches' inputs in turn, 64 / 32 / 16 samples, us a step: 16 384 samples, dim 64
 // 77.6 / 72.8 / 73.4, dim 128 143.6 / 138.9 / 142.6; 50 001 samples, dim 64 218 / 210 / 215; 4096, dim 16 22.9 / 23.0 / 23.0.
-#define FUSED_SAMPLES 32
+// (A loop of no more steps than 32 samples need, against one made for 64: 26 x 8192, dim 256 197 -> 187, 26 x 16 384, dim 64 87.3 -> 82.9,
+// 1 x 1024, dim 256 41 -> 34.)  A row of one lane: a slot for each.
+#define FUSED_SAMPLES(lanes) ((lanes) == 1 ? FAE_WAVE : 32)
 #define LSORT_LONG_ROWS 65536
 static bool lsort_takes(int64_t lookups, int64_t all)
 {
@@ -837,10 +839,11 @@ template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS, (LPR 
     } else {
         const int b = blockIdx.x - a.n_sort_blocks;
         const int z = b / a.fwd_blocks_per_table, bl = b % a.fwd_blocks_per_table;
-        const int64_t s0 = ((int64_t)bl * LSORT_WAVES + threadIdx.x / FAE_WAVE) * FUSED_SAMPLES;
-        const int s1 = s0 + FUSED_SAMPLES < a.n_samples ? (int)s0 + FUSED_SAMPLES : a.n_samples;
-        fwd_onehot_wave<V, LPR, (LPR < FUSED_ALONE_LANES ? 8 : 16)>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, s1, a.out + (int64_t)z * a.dim,
-                               a.out_stride, a.dim, a.status, a.stream_out != 0);
+        constexpr int SAMPLES = FUSED_SAMPLES(LPR);
+        const int64_t s0 = ((int64_t)bl * LSORT_WAVES + threadIdx.x / FAE_WAVE) * SAMPLES;
+        const int s1 = s0 + SAMPLES < a.n_samples ? (int)s0 + SAMPLES : a.n_samples;
+        fwd_onehot_wave<V, LPR, (LPR < FUSED_ALONE_LANES ? 8 : 16), SAMPLES>((const V *)a.W[z], a.slots[z], a.n_hot[z], s0, s1, a.out + (int64_t)z * a.dim,
+                                                                              a.out_stride, a.dim, a.status, a.stream_out != 0);
     }
 }
 
@@ -887,7 +890,8 @@ extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_ta
     int lpr = 1;
     while (lpr < dim / 4 && lpr < 64)
         lpr <<= 1;
-    f.fwd_blocks_per_table = (int32_t)((S + LSORT_WAVES * FUSED_SAMPLES - 1) / (LSORT_WAVES * FUSED_SAMPLES));
+    const int64_t piece = LSORT_WAVES * FUSED_SAMPLES(lpr);
+    f.fwd_blocks_per_table = (int32_t)((S + piece - 1) / piece);
     f.n_sort_blocks = lsort_plan(ctx, hot_tables, hot_batch, in_lds, nt, f.sort_blk_start, f.part_shift, lpr,
                                  (int64_t)nt * f.fwd_blocks_per_table);
     f.n_tables = nt;

@@ -76,23 +76,24 @@ __device__ __forceinline__ void fwd_store(float *p, const float &v, bool stream)
         *p = v;
 }
 
-// One-hot tables (one lookup per sample): a wave takes 64 consecutive samples starting at s0,
-// reads their 64 slots with one coalesced load and then copies rows, 64/LPR rows per step, with
+// One-hot tables (one lookup per sample): a wave takes SAMPLES consecutive samples from s0 on (those in front of s_end),
+// reads their slots with one coalesced load and then copies rows, 64/LPR rows per step, with
 // the loads of up to UNMAX steps in flight before the first store.  obase points at the table's
 // first output column of sample 0.
-template <typename V, int LPR, int UNMAX>
-__device__ __forceinline__ void fwd_onehot_wave(const V *W, const int32_t *slots, int n_hot, int64_t s0, int n_samples,
+template <typename V, int LPR, int UNMAX, int SAMPLES = FAE_WAVE>
+__device__ __forceinline__ void fwd_onehot_wave(const V *W, const int32_t *slots, int n_hot, int64_t s0, int s_end,
                                                 float *obase, int64_t out_stride, int dim, uint32_t *status,
                                                 bool stream_out)
 {
     constexpr int G = FAE_WAVE / LPR;
-    constexpr int STEPS = FAE_WAVE / G;
+    constexpr int STEPS = SAMPLES / G;
+    static_assert(SAMPLES <= FAE_WAVE && SAMPLES % G == 0, "a slot per lane, whole steps");
     constexpr int UN = STEPS < UNMAX ? STEPS : UNMAX;
     const int lane = fae_lane(), g = lane / LPR, l = lane % LPR;
-    if (s0 >= n_samples)
+    if (s0 >= s_end)
         return;
     int sreg = -1;
-    if (s0 + lane < n_samples) {
+    if (lane < SAMPLES && s0 + lane < s_end) {
         sreg = slots[s0 + lane];
         if ((unsigned)sreg >= (unsigned)n_hot) {
             fae_flag(status, FAE_STATUS_ERANGE);
@@ -114,7 +115,7 @@ __device__ __forceinline__ void fwd_onehot_wave(const V *W, const int32_t *slots
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 const int64_t s = s0 + (i0 + u) * G + g;
-                if (active && s < n_samples)
+                if (active && s < s_end)
                     fwd_store((V *)(obase + s * out_stride) + c, v[u], stream_out);
             }
         }

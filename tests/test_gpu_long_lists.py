@@ -111,9 +111,9 @@ def test_many_samples_with_empty_bags():
 
 
 @pytest.mark.parametrize("nt,n", [(1, 1), (1, 31), (1, 33), (2, 511), (2, 513), (26, 5120), (26, 5121), (26, 10_753)])
-@pytest.mark.parametrize("dim", [4, 60, 64, 128, 260])
+@pytest.mark.parametrize("dim", [4, 8, 60, 64, 128, 256, 260, 512])
 def test_row_copies_beside_the_sort(nt, n, dim):
-    """Pieces of 32 samples per wave, and both sides of the rule on how many copies run beside the sorts."""
+    """Pieces of 32 samples per wave (64 where a row is one lane), in rows of 1 to 64 lanes and of several rounds of these, and both sides of the rule on how many copies run beside the sorts."""
     rng = np.random.default_rng(n + dim)
     one = [torch.from_numpy(rng.integers(0, 999, n).astype(np.int32)).cuda() for _ in range(nt)]
     want = _step(1, one, [None] * nt, n, [n] * nt, fused=True, rows=999, dim=dim)[1]
