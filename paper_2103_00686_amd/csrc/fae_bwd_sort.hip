@@ -498,6 +498,9 @@ static bool lsort_takes(int64_t lookups, int64_t all)
 // Workgroups per table for the LDS sort.  Lists that are split by the top bits of the slot: enough parts to
 // occupy the chip, never below ~64 lookups (a part of up to 256 is sorted by counting; a step of 8 x 1024 lookups,
 // parts down to 512, 256, 128, 64, 32: 19.3, 17.6, 17.6, 17.5, 17.4 us; of 1 x 512: 15.8, 14.6, 14.8, 14.7, 14.1 us).
+// Beside more copies than there are compute units of rows of 32 lanes on (there a sorting workgroup has a unit to itself), or than twice as many of
+// rows of 16, no more than four a table: steps with up to sixteen / four, 26 x 8192, dim 128 90.8 / 88.2, dim 256 187 / 185; 26 x 10 000, dim 64
+// 59.8 / 59.2, dim 128 111 / 106; 13 x 10 200, dim 128 60.0 / 58.9; with fewer copies of 16 lanes 13 x 16 384 49 / 56, 20 x 12 000 55 / 57.
 // Longer ones: one sorting workgroup per compute unit over all tables, parts of 512 to 5000 lookups (every part goes over its
 // table's whole list, so more of them cost more than shorter ones save; 5000 leaves room for the sample's error below
 // LSORT_CAP); 5 lists of 111 K in all, parts of 512, 1024: 43.4, 45.3 us.  Beside row copies two for three compute units, and
@@ -514,11 +517,13 @@ static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fa
     int want = 1;
     while (want < 16 && n_lds * want * 2 <= ctx->n_cu)
         want <<= 1;
+    const bool many = copy_blocks > ctx->n_cu;
+    if (want > 4 && (copy_lanes >= FUSED_ALONE_LANES ? many : copy_lanes >= 16 && copy_blocks > 2LL * ctx->n_cu))
+        want = 4;
     int64_t long_lookups = 0;
     for (int z = 0; z < nt; ++z)
         if (in_lds[z] && hot_batch->h_n_lookups[z] > LSORT_SPLIT_MAX)
             long_lookups += hot_batch->h_n_lookups[z];
-    const bool many = copy_blocks > ctx->n_cu;
     int64_t share = long_lookups * (many && copy_lanes >= 16 ? 4 : copy_blocks > 0 ? 3 : 2) / (2 * ctx->n_cu);
     const int64_t least = many && copy_lanes >= FUSED_ALONE_LANES ? 3300 : 512;
     share = share < least ? least : (share > 5000 ? 5000 : share);

@@ -110,7 +110,7 @@ def test_many_samples_with_empty_bags():
     assert all(torch.equal(a, b) for a, b in zip(want, got))
 
 
-@pytest.mark.parametrize("nt,n", [(1, 1), (1, 31), (1, 33), (2, 511), (2, 513), (26, 5120), (26, 5121), (26, 10_753)])
+@pytest.mark.parametrize("nt,n", [(1, 1), (1, 31), (1, 33), (2, 511), (2, 513), (26, 5120), (26, 5121), (26, 9000), (26, 10_753)])
 @pytest.mark.parametrize("dim", [4, 8, 60, 64, 128, 256, 260, 512])
 def test_row_copies_beside_the_sort(nt, n, dim):
     """Pieces of 32 samples per wave (64 where a row is one lane), in rows of 1 to 64 lanes and of several rounds of these, and both sides of the rule on how many copies run beside the sorts."""
