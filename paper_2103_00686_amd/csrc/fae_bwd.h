@@ -88,7 +88,7 @@ struct LsortArgs {
     int32_t n_hot[FAE_MAX_TABLES];
     int32_t seg_start[FAE_MAX_TABLES + 1];
     int32_t blk_start[FAE_MAX_TABLES + 1]; // workgroups per table (0 for tables sorted elsewhere)
-    int32_t part_shift[FAE_MAX_TABLES];    // part of a key = key >> part_shift
+    uint32_t part_slots[FAE_MAX_TABLES];   // slots of a part where ranges of slots split a list
     int32_t n_tables;
     int32_t n_samples;
     int32_t *keys_out, *vals_out;

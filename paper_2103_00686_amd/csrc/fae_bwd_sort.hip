@@ -466,7 +466,7 @@ __global__ __launch_bounds__(LSORT_THREADS, 8) void lds_sort_kernel(LsortArgs a)
     bwd_clear_flags(a.flags, a.n_flags, a.flag_slice, LSORT_THREADS);
     const int z = fae_find_table(a.blk_start, a.n_tables, blockIdx.x);
     lds_sort_block(a.slots[z], a.offsets[z], a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z], blockIdx.x - a.blk_start[z],
-                   a.blk_start[z + 1] - a.blk_start[z], a.part_shift[z], a.n_samples, a.keys_out + a.seg_start[z],
+                   a.blk_start[z + 1] - a.blk_start[z], a.part_slots[z], a.n_samples, a.keys_out + a.seg_start[z],
                    a.vals_out + a.seg_start[z], a.status);
 }
 
@@ -495,62 +495,75 @@ static bool lsort_takes(int64_t lookups, int64_t all)
     return lookups <= 100000 || (lookups <= LSORT_MAX && all <= 1 << 20);
 }
 
-// Workgroups per table for the LDS sort.  Lists that are split by the top bits of the slot: enough parts to
+// Workgroups per table for the LDS sort.  Lists that are split into ranges of slots: enough parts to
 // occupy the chip, never below ~64 lookups (a part of up to 256 is sorted by counting; a step of 8 x 1024 lookups,
-// parts down to 512, 256, 128, 64, 32: 19.3, 17.6, 17.6, 17.5, 17.4 us; of 1 x 512: 15.8, 14.6, 14.8, 14.7, 14.1 us).
+// parts down to 512, 256, 128, 64, 32: 19.3, 17.6, 17.6, 17.5, 17.4 us; of 1 x 512: 15.8, 14.6, 14.8, 14.7, 14.1 us).  The ranges are
+// equal, not the slot's top bits, which make half as many parts twice as large just above a power of two (70 000 slots, steps, top bits / equal:
+// 40 x 11 000 49.9 / 45.5, 13 x 16 384 31.6 / 29.0, 1 x 1024 13.3 / 12.4; 130 000 slots the same either way).
 // Beside more copies than there are compute units of rows of 32 lanes on (there a sorting workgroup has a unit to itself), or than twice as many of
 // rows of 16, no more than four a table: steps with up to sixteen / four, 26 x 8192, dim 128 90.8 / 88.2, dim 256 187 / 185; 26 x 10 000, dim 64
 // 59.8 / 59.2, dim 128 111 / 106; 13 x 10 200, dim 128 60.0 / 58.9; with fewer copies of 16 lanes 13 x 16 384 49 / 56, 20 x 12 000 55 / 57.
-// Longer ones: one sorting workgroup per compute unit over all tables, parts of 512 to 5000 lookups (every part goes over its
+// Longer ones: one sorting workgroup per compute unit over all tables (no more, where no copies run beside them: two that share one
+// end later; sort alone, 3 x 100 000 with 258 / 256 workgroups 37.5 / 28.4, 3 lists of 207 K with 272 / 256 35.7 / 32.8, 5 x 102 400 45 / 35), parts
+// of 512 to 5000 lookups (every part goes over its
 // table's whole list, so more of them cost more than shorter ones save; 5000 leaves room for the sample's error below
 // LSORT_CAP); 5 lists of 111 K in all, parts of 512, 1024: 43.4, 45.3 us.  Beside row copies two for three compute units, and
 // one for two where more workgroups copy rows of 16 lanes on than there are compute units, since those need the memory's
 // rate from all of them.  Steps, three batches' inputs in turn, two for three / one for two: 26 x 16 384, dim 64 73.9 /
 // 72.8 us, 12 000 60.5 / 59.3; 26 x 11 000, dim 16 34.5 / 35.1; 3 x 65 536, dim 8 36.4 / 37.9.  Where a sorting workgroup
 // has a compute unit to itself (see fwd_sort_kernel), no less than 3300: 13 x 16 384, dim 128, without / with 79.3 / 76.0.
-// part_shift[z]: part of a key = key >> shift; blk_start: prefix of workgroups per table (tables not
+// part_slots[z]: slots of a part that is a range; blk_start: prefix of workgroups per table (tables not
 // sorted in LDS get none).  Returns the number of workgroups.
 static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fae_batch *hot_batch, const bool *in_lds,
-               int n_lds, int32_t *blk_start, int32_t *part_shift, int copy_lanes, int64_t copy_blocks)
+               int n_lds, int32_t *blk_start, uint32_t *part_slots, int copy_lanes, int64_t copy_blocks)
 {
     const int nt = hot_tables->n_tables;
+    const bool many = copy_blocks > ctx->n_cu;
     int want = 1;
     while (want < 16 && n_lds * want * 2 <= ctx->n_cu)
         want <<= 1;
-    const bool many = copy_blocks > ctx->n_cu;
     if (want > 4 && (copy_lanes >= FUSED_ALONE_LANES ? many : copy_lanes >= 16 && copy_blocks > 2LL * ctx->n_cu))
         want = 4;
     int64_t long_lookups = 0;
-    for (int z = 0; z < nt; ++z)
-        if (in_lds[z] && hot_batch->h_n_lookups[z] > LSORT_SPLIT_MAX)
-            long_lookups += hot_batch->h_n_lookups[z];
-    int64_t share = long_lookups * (many && copy_lanes >= 16 ? 4 : copy_blocks > 0 ? 3 : 2) / (2 * ctx->n_cu);
-    const int64_t least = many && copy_lanes >= FUSED_ALONE_LANES ? 3300 : 512;
-    share = share < least ? least : (share > 5000 ? 5000 : share);
     int nb = 0;
     for (int z = 0; z < nt; ++z) {
-        blk_start[z] = nb;
-        part_shift[z] = 0;
+        part_slots[z] = 1;
+        blk_start[z] = 0;
         if (!in_lds[z])
             continue;
         const int64_t n = hot_batch->h_n_lookups[z];
         if (n > LSORT_SPLIT_MAX) {
-            nb += (int)((n + share - 1) / share);
+            long_lookups += n;
             continue;
         }
-        int kbits = 1; // bits of the largest key (n_hot itself marks an invalid slot)
-        while ((hot_tables->h_rows[z] >> kbits) != 0)
-            ++kbits;
         int parts = want;
         while (parts > 1 && n / parts < 64)
             parts >>= 1;
-        int pbits = 0;
-        while ((1 << pbits) < parts)
-            ++pbits;
-        if (pbits > kbits)
-            pbits = kbits;
-        part_shift[z] = kbits - pbits;
-        nb += (int)(hot_tables->h_rows[z] >> part_shift[z]) + 1; // parts that can hold a key: 0 .. (n_hot >> shift)
+        const int64_t keys = hot_tables->h_rows[z] + 1; // n_hot itself marks an invalid slot
+        part_slots[z] = (uint32_t)((keys + parts - 1) / parts);
+        blk_start[z] = (int)((keys + part_slots[z] - 1) / part_slots[z]);
+        nb += blk_start[z];
+    }
+    int64_t share = long_lookups * (many && copy_lanes >= 16 ? 4 : copy_blocks > 0 ? 3 : 2) / (2 * ctx->n_cu);
+    const int64_t least = many && copy_lanes >= FUSED_ALONE_LANES ? 3300 : 512;
+    share = share < least ? least : (share > 5000 ? 5000 : share);
+    if (copy_blocks == 0 && long_lookups > 0) { // rounding up may not take them beyond one per compute unit
+        const auto parts_of = [&](int64_t per) {
+            int64_t p = nb;
+            for (int z = 0; z < nt; ++z)
+                if (in_lds[z] && hot_batch->h_n_lookups[z] > LSORT_SPLIT_MAX)
+                    p += (hot_batch->h_n_lookups[z] + per - 1) / per;
+            return p;
+        };
+        while (share < 5000 && parts_of(share) > ctx->n_cu)
+            share += share / 32 + 1;
+        share = share > 5000 ? 5000 : share;
+    }
+    nb = 0;
+    for (int z = 0; z < nt; ++z) {
+        const int parts = !in_lds[z] ? 0 : hot_batch->h_n_lookups[z] > LSORT_SPLIT_MAX ? (int)((hot_batch->h_n_lookups[z] + share - 1) / share) : blk_start[z];
+        blk_start[z] = nb;
+        nb += parts;
     }
     blk_start[nt] = nb;
     return nb;
@@ -753,7 +766,7 @@ int32_t bwd_sort_stage(fae_ctx *ctx, hipStream_t st, const fae_tables *hot_table
             la.n_hot[z] = a.n_hot[z];
             la.seg_start[z] = a.seg_start[z];
         }
-        const int nb = lsort_plan(ctx, hot_tables, hot_batch, in_lds, n_lds, la.blk_start, la.part_shift, 0, 0);
+        const int nb = lsort_plan(ctx, hot_tables, hot_batch, in_lds, n_lds, la.blk_start, la.part_slots, 0, 0);
         la.seg_start[nt] = a.seg_start[nt];
         la.n_tables = nt;
         la.n_samples = a.n_samples;
@@ -817,7 +830,7 @@ struct FusedArgs {
     int32_t n_hot[FAE_MAX_TABLES];
     int32_t seg_start[FAE_MAX_TABLES + 1];
     int32_t sort_blk_start[FAE_MAX_TABLES + 1];
-    int32_t part_shift[FAE_MAX_TABLES];
+    uint32_t part_slots[FAE_MAX_TABLES];
     int32_t n_tables, dim, n_samples;
     int32_t n_sort_blocks, fwd_blocks_per_table;
     int64_t out_stride;
@@ -839,7 +852,7 @@ template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS, (LPR 
     if ((int)blockIdx.x < a.n_sort_blocks) {
         const int z = fae_find_table(a.sort_blk_start, a.n_tables, blockIdx.x);
         lds_sort_block(a.slots[z], nullptr, a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z], blockIdx.x - a.sort_blk_start[z],
-                       a.sort_blk_start[z + 1] - a.sort_blk_start[z], a.part_shift[z], a.n_samples, a.keys_out + a.seg_start[z],
+                       a.sort_blk_start[z + 1] - a.sort_blk_start[z], a.part_slots[z], a.n_samples, a.keys_out + a.seg_start[z],
                        a.vals_out + a.seg_start[z], a.status);
     } else {
         const int b = blockIdx.x - a.n_sort_blocks;
@@ -897,7 +910,7 @@ extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_ta
         lpr <<= 1;
     const int64_t piece = LSORT_WAVES * FUSED_SAMPLES(lpr);
     f.fwd_blocks_per_table = (int32_t)((S + piece - 1) / piece);
-    f.n_sort_blocks = lsort_plan(ctx, hot_tables, hot_batch, in_lds, nt, f.sort_blk_start, f.part_shift, lpr,
+    f.n_sort_blocks = lsort_plan(ctx, hot_tables, hot_batch, in_lds, nt, f.sort_blk_start, f.part_slots, lpr,
                                  (int64_t)nt * f.fwd_blocks_per_table);
     f.n_tables = nt;
     f.dim = dim;

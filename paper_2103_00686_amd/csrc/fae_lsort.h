@@ -10,7 +10,7 @@
 //      last slot where that is left out of the sort, see below), and adds up the lookups below its range;
 //   2. goes over the bits and takes the lookups of its range in batch order into LDS;
 //   3. sorts them there (LSD radix passes, or, where they are few, by counting the keys in front of each).
-// Lists of up to LSORT_CAP lookups are split by the top bits of the slot, those of up to LSORT_SPLIT_MAX too unless that
+// Lists of up to LSORT_CAP lookups are split into equal ranges of slots, those of up to LSORT_SPLIT_MAX too unless that
 // would leave a part with far more than its share (lsort_uneven).  Others are split by the ranks of
 // a sample of 1024 lookups, one out of every 1024th of the list (lsort_bounds): to single slots where many lookups
 // crowd on few, so that popular slots next to each other (ids in order of popularity) end up in different parts.  A slot that
@@ -41,10 +41,14 @@
 #define LSORT_STEP (FAE_WAVE * LSORT_KEYS)
 #define LSORT_STEPS ((LSORT_MAX + LSORT_WAVES * LSORT_STEP) / (LSORT_WAVES * LSORT_STEP)) // of a wave, at most
 #define LSORT_SAMPLES 1024
-#define LSORT_PARTS 16    // of a list that is split by the top bits of the slot, at most
-#define LSORT_UNEVEN 2048 // lookups beyond an even share that take a part longer than bounds by rank would (1.4 us per 1024 / 2.5 us)
+#define LSORT_PARTS 16    // of a list that is split by ranges of slots, at most
+#define LSORT_UNEVEN 3072 // lookups beyond an even share that take a part longer than bounds by rank would (1.4 us per 1024 / 2.5 us), and what 64 samples may err by
 #define LSORT_PIECE 5000  // lookups of a piece of a part that does not fit
-#define LSORT_SPLIT_MAX 10240 // lookups up to which the top bits of the slot split a list: the sample costs 2 us (1 x 9000 18.9 -> 20.3, 1 x 11 642 28.6 either way, 26 x 12 000 43.8 -> 37.1 a step)
+// Lookups up to which ranges of slots split a list where they do so evenly: finding the parts by rank takes 2.5 us more, and longer
+// lists gain more from even parts.  Steps, us, by rank / by ranges: 1 x 12 000 20.9 / 18.9, 8 x 12 000 26.0 / 23.9, 1 x 16 384 21.2 / 19.7,
+// 26 x 16 384 43.4 / 42.4, sort alone 22 / 17.5; three quarters on one slot (uneven: the 64 samples that see it come on top): 1 x 16 384 24 / 27,
+// 26 x 16 384 41.9 / 41.6.
+#define LSORT_SPLIT_MAX 16384
 #define LSORT_BITS 9 // of a digit, at most
 #define LSORT_DIGITS (1 << LSORT_BITS)
 #define LSORT_WORDS (LSORT_WAVES * LSORT_DIGITS / 2) // of the counters, as 32-bit words
@@ -189,19 +193,20 @@ __device__ __forceinline__ uint32_t lsort_piece(LsortLds &s, const int32_t *slot
     return end;
 }
 
-// Whether equal ranges of slots (the top bits) make a part of a list of up to LSORT_SPLIT_MAX lookups too large: by 64 samples, the same for
+// Whether equal ranges of slots make a part of a list of up to LSORT_SPLIT_MAX lookups too large: by 64 samples, the same for
 // every wave of every workgroup of a table.
-__device__ __forceinline__ bool lsort_uneven(const int32_t *slots, int n, uint32_t n_hot, int part_shift, int parts)
+__device__ __forceinline__ bool lsort_uneven(const int32_t *slots, int n, uint32_t n_hot, uint32_t part_slots, int parts)
 {
     uint32_t k = (uint32_t)slots[lsort_sample<FAE_WAVE>(fae_lane(), n, 0)];
-    k = (k < n_hot ? k : n_hot) >> part_shift;
+    k = (k < n_hot ? k : n_hot) / part_slots;
     int most = 0;
 #pragma unroll
     for (int p = 0; p < LSORT_PARTS; ++p) {
         const int c = __popcll(__ballot(k == (uint32_t)p));
         most = c > most ? c : most;
     }
-    return most * n / FAE_WAVE > n / parts + LSORT_UNEVEN;
+    const int limit = n / parts + LSORT_UNEVEN;
+    return most * n / FAE_WAVE > (limit < LSORT_CAP - 1024 ? limit : LSORT_CAP - 1024);
 }
 
 // The wave's lookups beg .. end - 1, in steps of which a lane has `per` consecutive ones: LSORT_KEYS, or four where
@@ -418,21 +423,21 @@ struct LsortBags {
     }
 };
 
-// Part `part` of `parts` of a table's n lookups; part_shift: part of a slot = slot >> part_shift, for
-// lists that the top bits split.  keys_out / vals_out: the table's segment of the sorted pairs.
-__device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32_t *off, int n, int n_hot_z, int part, int parts, int part_shift,
+// Part `part` of `parts` of a table's n lookups; part_slots: slots of a part of a list that is split
+// by ranges.  keys_out / vals_out: the table's segment of the sorted pairs.
+__device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32_t *off, int n, int n_hot_z, int part, int parts, uint32_t part_slots,
                                                int n_samples, int32_t *keys_out, int32_t *vals_out, uint32_t *status)
 {
     __shared__ __align__(16) LsortLds s;
     const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / FAE_WAVE), lane = fae_lane();
     const uint32_t n_hot = (uint32_t)n_hot_z;
-    uint32_t lo = (uint32_t)part << part_shift, hi = (uint32_t)(part + 1) << part_shift; // the part's slots
-    hi = hi < n_hot + 1u ? hi : n_hot + 1u;
+    uint32_t lo = (uint32_t)part * part_slots; // the part's slots
+    uint32_t hi = n_hot + 1u - lo < part_slots ? n_hot + 1u : lo + part_slots;
     bool crowd = false; // the last of them is left out of the sort
     int share = 0, shares = 1;
     bool by_rank = n > LSORT_SPLIT_MAX;
     if (n > LSORT_CAP && !by_rank)
-        by_rank = lsort_uneven(slots, n, n_hot, part_shift, parts);
+        by_rank = lsort_uneven(slots, n, n_hot, part_slots, parts);
     if (by_rank) {
         crowd = lsort_bounds(s, slots, n, n_hot, part, parts, &lo, &hi, &share, &shares);
         __syncthreads(); // its counts are read

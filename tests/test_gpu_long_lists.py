@@ -176,3 +176,40 @@ def test_one_slot_owns_most_of_a_list(n, share):
     even = rng.integers(0, ROWS, n)
     us, without = _sort_us(np.where(rng.random(n) < share, 191_001, even), None, n), _sort_us(even, None, n)
     assert us <= 3 * without, f"{us:.1f} us, without {without:.1f}"
+
+
+@pytest.mark.parametrize("rows", [1, 2, 3, 5, 63, 64, 65, 999, 32_767, 32_768, 70_000])
+@pytest.mark.parametrize("nt,n", [(1, 700), (40, 900), (2, 7169), (40, 16_384), (13, 12_001)])
+def test_ranges_of_slots(nt, n, rows):
+    """Parts that are equal ranges of slots: fewer slots than parts, a last part that is shorter, lists of one or two parts."""
+    rng = np.random.default_rng(n + rows)
+    slots = [torch.from_numpy((rng.random(n) ** (1 + z % 3) * rows).astype(np.int32)).cuda() for z in range(nt)]
+    want, got = (_step(v, slots, [None] * nt, n, [n] * nt, rows=rows)[1] for v in (1, 0))
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+
+
+def _workgroups_per_unit(nt, n):
+    """Sort alone: time for nt tables over that for a quarter of them."""
+    times = []
+    for k in (nt, (nt + 3) // 4):
+        rng = np.random.default_rng(5)
+        hp = HotPath([ROWS] * k, 4)
+        hp.alloc_counts()
+        hp.build([0] * k, [ROWS] * k, seed=3)
+        hb = HotBatch(n, [torch.from_numpy(rng.integers(0, ROWS, n).astype(np.int32)).cuda() for _ in range(k)], [None] * k, [n] * k)
+        gout = torch.zeros((n, k, 4), device="cuda")
+        kernel = [B.fae_kernel_name(i) for i in range(B.FAE_K_COUNT)].index("lds_sort")
+        best = 1e9
+        for _ in range(12):
+            B.fae_timing_enable(hp.ctx, True)
+            B.fae_timing_reset(hp.ctx)
+            hp.backward_sgd(hb, gout, 0.0)
+            hp.sync()
+            best = min(best, B.fae_timing_read(hp.ctx, kernel)[0])
+        times.append(best)
+    return times[0] / times[1]
+
+
+def test_sorting_workgroups_fit_the_chip():
+    """13 lists of 12 000 sort in about the time of 4 of them (a few workgroups more than compute units made it 1.4 times that)."""
+    assert _workgroups_per_unit(13, 12_000) < 1.25
