@@ -588,7 +588,7 @@ int32_t bwd_sort_stage(fae_ctx *ctx, hipStream_t st, const fae_tables *hot_table
             max_hot_long = hot_tables->h_rows[z];
     for (int z = 0; z < nt; ++z) {
         const int64_t nl = hot_batch->h_n_lookups[z];
-        in_lds[z] = ctx->opt_sort != 1 && nl > 0 && nl <= LSORT_MAX && (!a.offsets[z] || a.n_samples <= LSORT_MAX);
+        in_lds[z] = ctx->opt_sort != 1 && nl > 0 && nl <= LSORT_MAX && (nl <= LSORT_SHORT || !a.offsets[z] || a.n_samples <= LSORT_MAX);
         if (in_lds[z] && nl > LSORT_SHORT && ctx->opt_sort != 2)
             in_lds[z] = ctx->opt_sort == 0 && max_hot_long >= LSORT_LONG_ROWS && lsort_takes(nl, su.plan.N);
         if (!in_lds[z] && nl > 0 && hot_tables->h_rows[z] > max_hot_global)

@@ -35,7 +35,7 @@
 #define LSORT_WAVES (LSORT_THREADS / FAE_WAVE)
 #define LSORT_ITEMS 7 // keys per thread in the sort
 #define LSORT_CAP (LSORT_THREADS * LSORT_ITEMS)
-#define LSORT_POS_BITS 17                 // of a lookup's or a sample's number
+#define LSORT_POS_BITS 17                 // of a lookup's number, or of a sample's where there are no more of these
 #define LSORT_MAX ((1 << LSORT_POS_BITS) - 1) // lookups of a table
 #define LSORT_KEYS 16                     // consecutive lookups of a lane in a step: a bit of half a word each
 #define LSORT_STEP (FAE_WAVE * LSORT_KEYS)
@@ -398,6 +398,11 @@ __device__ __forceinline__ void lsort_passes(LsortLds &s, int n, uint32_t lo, in
 struct LsortBags {
     const int32_t *off;
     int n_samples, step, m;
+    __device__ __forceinline__ LsortBags(const int32_t *offsets, int samples) : off(offsets), n_samples(samples)
+    {
+        step = n_samples / LSORT_WORDS + 1;
+        m = n_samples / step + 1;
+    }
     __device__ __forceinline__ void stage(LsortLds &s) const // into the counters' room
     {
         for (int i = threadIdx.x; i < m; i += LSORT_THREADS)
@@ -418,7 +423,7 @@ struct LsortBags {
             at += at + d < m && s.word[at + d < m ? at + d : 0] <= e ? d : 0;
         at *= step;
         for (int d = step > 1 ? 1 << (31 - __builtin_clz(step - 1)) : 0; d > 0; d >>= 1)
-            at += at + d <= n_samples && off[at + d <= n_samples ? at + d : 0] <= e ? d : 0;
+            at += d <= n_samples - at && off[d <= n_samples - at ? at + d : 0] <= e ? d : 0;
         return at;
     }
 };
@@ -450,8 +455,8 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
     l.beg = w * per_wave < n ? w * per_wave : n;
     l.end = l.beg + per_wave < n ? l.beg + per_wave : n;
     l.per = per_wave > 256 ? LSORT_KEYS : 4;
-    LsortBags bags = {off, n_samples, (n_samples + LSORT_WORDS) / LSORT_WORDS, 0};
-    bags.m = (n_samples + bags.step) / bags.step;
+    const LsortBags bags(off, n_samples);
+    const bool many_samples = n_samples > LSORT_MAX; // the passes have no room for a sample's number beside a key's rank: found behind them
     bool bad = false;
     int left = 0;             // lookups on slots lo .. hi - 1, once they are counted
     int over = 0, tries = 1;  // lookups on slots lo .. top - 1 where these are known not to fit
@@ -463,7 +468,7 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
             over = 0;
             __syncthreads(); // its counts are read
         }
-        if (off)
+        if (off && !many_samples)
             bags.stage(s);
         LsortMask in, last;
         in.clear();
@@ -490,7 +495,9 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
             over = n_part + all_last;
             continue;
         }
-        const bool few = n_part <= LSORT_RANK_MAX;
+        const bool few = n_part <= LSORT_RANK_MAX, late = many_samples && !few;
+        if (off && many_samples && (few || crowd))
+            bags.stage(s);
         if (crowd) { // this part's share of the lookups on the last slot, as many at a time as LDS holds
             const int end = (int)((int64_t)all_last * (share + 1) / shares);
             for (int from = (int)((int64_t)all_last * share / shares); from < end; from += LSORT_CAP) {
@@ -513,7 +520,7 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
         for (int i = t; i < n_part; i += LSORT_THREADS) {
             const int e = s.pos[i];
             s.key[i] = (int)lsort_key(l, e);
-            if (off)
+            if (off && !late)
                 s.pos[i] = bags.check(s, bags.search(s, e), e, &bad);
         }
         __syncthreads();
@@ -535,6 +542,14 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
                 rank += __shfl_xor(rank, m, FAE_WAVE);
         } else {
             lsort_passes(s, n_part, lo, 32 - __builtin_clz((top - 1u - lo) | 1u));
+            if (off && late) {
+                bags.stage(s);
+                __syncthreads();
+                for (int i = t; i < n_part; i += LSORT_THREADS) {
+                    const int e = s.pos[i];
+                    s.pos[i] = bags.check(s, bags.search(s, e), e, &bad);
+                }
+            }
         }
         if (few) {
             const int i = t / LSORT_RANK_LANES;

@@ -100,14 +100,24 @@ def test_slots_out_of_range_and_unaligned_lists(n, kind):
     assert torch.equal(*weights)
 
 
-def test_many_samples_with_empty_bags():
-    """More samples than the LDS sort numbers: the passes take the list, whatever its length."""
-    rng = np.random.default_rng(3)
-    n, S = 9000, 140_000
-    slots = [torch.from_numpy(_slots("few", n, rng).astype(np.int32)).cuda()]
+@pytest.mark.parametrize("kind", ["uniform", "few", "one", "default"])
+@pytest.mark.parametrize("n", [1, 200, 2000, 9000, 16_384])
+@pytest.mark.parametrize("S", [131_071, 131_072, 140_000, 700_001])
+def test_many_samples_with_empty_bags(S, n, kind):
+    """More samples than a key's rank leaves room for in the sort's words: lists of up to 16 384 lookups are sorted in LDS all the same
+    (the passes took 80 us for 2000 lookups of 140 000 samples, the LDS sort 13)."""
+    rng = np.random.default_rng(n)
+    slots = [torch.from_numpy(_slots(kind, n, rng).astype(np.int32)).cuda()]
     offs = [torch.from_numpy(np.concatenate([[0], np.sort(rng.integers(0, n + 1, S - 1)), [n]]).astype(np.int32)).cuda()]
     want, got = (_step(v, slots, offs, S, [n])[1] for v in (1, 0))
     assert all(torch.equal(a, b) for a, b in zip(want, got))
+    hp = HotPath([ROWS], 4)
+    hp.alloc_counts()
+    hp.build([0], [ROWS], seed=3)
+    B.fae_timing_enable(hp.ctx, True)
+    hp.backward_sgd(HotBatch(S, slots, offs, [n]), torch.zeros((S, 1, 4), device="cuda"), 0.05)
+    hp.sync()
+    assert {B.fae_kernel_name(k): B.fae_timing_read(hp.ctx, k)[1] for k in range(B.FAE_K_COUNT)}["lds_sort"] == 1
 
 
 @pytest.mark.parametrize("nt,n", [(1, 1), (1, 31), (1, 33), (2, 511), (2, 513), (26, 5120), (26, 5121), (26, 9000), (26, 10_753)])
