@@ -252,9 +252,12 @@ size_t fae_bwd_workspace_bytes(const fae_tables *hot_tables, int64_t n_samples,
 int32_t fae_embbag_bwd_presort(fae_ctx *ctx, const fae_tables *hot_tables, const fae_batch *hot_batch,
                                void *ws, size_t ws_bytes);
 /* fae_embbag_fwd that also carries the sort of the backward for the same batch: when every
- * table is one-hot and the batch is small enough for the in-LDS sort (100 000 samples and more),
- * one launch holds both, the sorting workgroups running beside the row copies; the sorted
- * pairs stay in ws for the fae_embbag_bwd_sgd call with the same batch and workspace.
+ * table is one-hot, dim and out_row_stride are multiples of four, the rows lie on 16 bytes and the
+ * batch is within the in-LDS sort's reach, one launch holds both, the sorting workgroups running beside
+ * the row copies; the sorted pairs stay in ws for the fae_embbag_bwd_sgd call with the same batch and
+ * workspace.  That reach is 16 384 samples, and with sort_variant 0 or 2 100 000, or 131 071 where
+ * all tables together have no more than 2^20 lookups; with sort_variant 0 batches of more than 40 000
+ * samples whose tables all have fewer than 256 rows are left out where the separate calls are faster.
  * For any other shape it is exactly fae_embbag_fwd.  Same results as the separate calls.
  * Asynchronous. */
 int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_tables, const float *const *h_hotW,

@@ -495,6 +495,19 @@ static bool lsort_takes(int64_t lookups, int64_t all)
     return lookups <= 100000 || (lookups <= LSORT_MAX && all <= 1 << 20);
 }
 
+// Whether one launch for forward and sort is the shorter way beyond LSORT_SHORT samples.  It is, whatever the slots' bits, since the
+// copies hide most of the sort, except where the sort would be a single pass over at most 255 slots and the copies are too few to
+// hide what every part's way over the whole list costs.  Steps of 40 slots, three batches' inputs in turn, us, one launch / apart:
+//   dim 16: 1 x 30 000 22.1 / 23.5, 50 000 27 / 25, 100 000 37 / 29; 2 x 40 000 26 / 24, 100 000 41 / 33; 4 x 65 536 34 / 31
+//   8 x 60 000 40 / 42, 8 x 100 000 67 / 60, 10 x 100 000 80 / 80, 13 x 100 000 84 / 98; dim 64: 1 x 100 000 46 / 40, 8 x 100 000 143 / 148
+// 1000 slots (two passes): dim 16 1 x 100 000 35 / 38, 4 x 100 000 44 / 53, 8 x 100 000 70 / 78, dim 128 1 x 100 000 54.5 / 64.
+static bool lsort_fuses(int64_t samples, int64_t all, int64_t most_slots, int lanes)
+{
+    if (samples <= LSORT_SHORT || most_slots >= RADIX)
+        return true;
+    return !((samples > 40000 && all <= 1 << 18) || (samples > 90000 && all <= 900000 && lanes <= 8));
+}
+
 // Workgroups per table for the LDS sort.  Lists that are split into ranges of slots: enough parts to
 // occupy the chip, never below ~64 lookups (a part of up to 256 is sorted by counting; a step of 8 x 1024 lookups,
 // parts down to 512, 256, 128, 64, 32: 19.3, 17.6, 17.6, 17.5, 17.4 us; of 1 x 512: 15.8, 14.6, 14.8, 14.7, 14.1 us).  The ranges are
@@ -885,8 +898,16 @@ extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_ta
     bool fused = !su.empty && ctx->opt_sort != 1 && ctx->opt_fwd == 0 && h_hotW && out && dim % 4 == 0 &&
                  out_row_stride % 4 == 0 && out_row_stride >= (int64_t)nt * dim && ((uintptr_t)out) % 16 == 0 &&
                  (S <= LSORT_SHORT || ((ctx->opt_sort == 0 || ctx->opt_sort == 2) && lsort_takes(S, su.plan.N)));
-    for (int z = 0; fused && z < nt; ++z)
+    int64_t most_slots = 0;
+    for (int z = 0; fused && z < nt; ++z) {
         fused = su.a.offsets[z] == nullptr && h_hotW[z] && ((uintptr_t)h_hotW[z]) % 16 == 0;
+        most_slots = hot_tables->h_rows[z] > most_slots ? hot_tables->h_rows[z] : most_slots;
+    }
+    int lpr = 1;
+    while (lpr < dim / 4 && lpr < 64)
+        lpr <<= 1;
+    if (ctx->opt_sort == 0)
+        fused = fused && lsort_fuses(S, su.plan.N, most_slots, lpr);
     if (!fused)
         return fae_embbag_fwd(ctx, hot_tables, h_hotW, hot_batch, out, out_row_stride);
     FAE_HIP(ctx, hipSetDevice(ctx->device));
@@ -905,9 +926,6 @@ extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_ta
         in_lds[z] = true;
     }
     f.seg_start[nt] = su.a.seg_start[nt];
-    int lpr = 1;
-    while (lpr < dim / 4 && lpr < 64)
-        lpr <<= 1;
     const int64_t piece = LSORT_WAVES * FUSED_SAMPLES(lpr);
     f.fwd_blocks_per_table = (int32_t)((S + piece - 1) / piece);
     f.n_sort_blocks = lsort_plan(ctx, hot_tables, hot_batch, in_lds, nt, f.sort_blk_start, f.part_slots, lpr,

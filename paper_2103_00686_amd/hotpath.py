@@ -43,6 +43,30 @@ class HotBatch:
         return HotBatch(count, slots, offs, nl)
 
 
+def step_sequence(rows: Sequence[int], dim: int, one_hot: bool, n_samples: int, n_lookups: int, single_stream: bool = False) -> str:
+    """The call sequence of a step: "fused" (forward and the backward's sort in one launch, which is the plain
+    forward and a sort of its own for shapes that it does not take) or "ahead" (the next batch's sort on the side
+    stream beside this batch's forward and backward).  "fused" for one-hot batches of up to 100 000 samples, unless
+    rows are short and slots few (one or two radix passes) and the lists long: there the copies do not hide the sort.
+    "ahead" for other steps of up to 4 M lookups, whose sort is a string of short launches.
+    Three batches' inputs in turn, us a step, fused / ahead:
+      40 slots, dim 16: 8 x 60 000 40 / 44, 8 x 80 000 50 / 43, 8 x 100 000 67 / 50, 13 x 65 536 64 / 55, 20 x 50 000 70 / 60, 26 x 30 000
+      54 / 49, 16 x 100 000 113 / 101; dim 32: 8 x 100 000 85 / 67, 13 x 65 536 79 / 70; dim 64: 8 x 100 000 143 / 147
+      8000 slots, dim 16: 8 x 65 536 50 / 49, 8 x 100 000 71 / 60, 10 x 100 000 86 / 74, 13 x 50 000 55 / 56, 13 x 60 000 67 / 62,
+      13 x 65 536 74 / 69, 16 x 65 536 78 / 83, 16 x 100 000 123 / 114, 20 x 100 000 131 / 138
+      65 000 slots, dim 16: 8 x 100 000 82 / 78, 8 x 80 000 61 / 64, 13 x 65 536 78 / 87, 13 x 100 000 121 / 110; a million: 8 x 60 000 59 / 58
+    """
+    most = max(rows, default=0)
+    if one_hot and n_samples <= 100_000:
+        long_lists = n_samples > 16384 and dim <= 32 and (
+            (most < 256 and 500_000 <= n_lookups <= 1 << 21) or
+            (256 <= most < 16384 and n_samples >= 55_000 and 600_000 <= n_lookups < 1 << 20) or
+            (256 <= most < 65536 and n_samples >= 90_000 and 600_000 <= n_lookups <= 1_700_000))
+        if not long_lists:
+            return "fused"
+    return "ahead" if n_lookups <= 1 << 22 and not single_stream else "fused"
+
+
 class HotPath:
     def __init__(self, rows: Sequence[int], dim: int, device: int = 0, stream: Optional[int] = None):
         """stream: a hipStream_t handle (e.g. ``torch.cuda.Stream().cuda_stream``); default is
@@ -150,16 +174,11 @@ class HotPath:
     def prepare_steps(self, hbs: Sequence[HotBatch], gouts: Sequence[torch.Tensor], outs: Sequence[torch.Tensor],
                       lr: float, presort: str = "auto", single_stream: bool = False):
         """The training steps of a cycle of hot batches as zero-argument callables (to be called in
-        cyclic order), and the name of the call sequence they use.  presort "auto" picks, from the
-        shapes alone: "fused" (forward and the backward's sort in one launch) when every table is
-        one-hot and the batches have at most 100000 samples; "ahead" (the next batch's sort on the
-        side stream beside this batch's forward and backward) for other steps of up to 4 M lookups,
-        whose sort is a string of short launches; else the calls one after the other ("fused", which
-        is the plain forward for such shapes).  single_stream rules "ahead" out (graph capture)."""
+        cyclic order), and the name of the call sequence they use.  presort "auto" picks from the
+        shapes alone (``step_sequence``).  single_stream rules "ahead" out (graph capture)."""
         if presort == "auto":
-            fusable = all(o is None for hb in hbs for o in hb.offsets) and max(hb.n_samples for hb in hbs) <= 100_000
-            short_sort = max(sum(hb.n_lookups) for hb in hbs) <= (1 << 22)
-            presort = "ahead" if (not fusable and short_sort and not single_stream) else "fused"
+            presort = step_sequence(self.n_hot, self.dim, all(o is None for hb in hbs for o in hb.offsets),
+                                    max(hb.n_samples for hb in hbs), max(sum(hb.n_lookups) for hb in hbs), single_stream)
         if presort == "ahead":
             return self.prepare_pipeline(hbs, gouts, outs, lr), presort
         return [self.prepare_step(hb, g, o, lr, presort=presort) for hb, g, o in zip(hbs, gouts, outs)], presort

@@ -223,3 +223,25 @@ def _workgroups_per_unit(nt, n):
 def test_sorting_workgroups_fit_the_chip():
     """13 lists of 12 000 sort in about the time of 4 of them (a few workgroups more than compute units made it 1.4 times that)."""
     assert _workgroups_per_unit(13, 12_000) < 1.25
+
+
+def _launches(hp):
+    return {B.fae_kernel_name(k): B.fae_timing_read(hp.ctx, k)[1] for k in range(B.FAE_K_COUNT)}
+
+
+@pytest.mark.parametrize("nt,n,rows,dim,one", [(1, 40_000, 255, 16, True), (1, 40_001, 255, 16, False), (1, 40_001, 256, 16, True), (2, 100_000, 40, 16, False),
+                                               (8, 32_768, 40, 16, True), (6, 43_690, 40, 4, False), (6, 43_691, 40, 4, True), (8, 100_000, 40, 16, False),
+                                               (8, 100_000, 40, 36, True), (10, 100_000, 40, 16, True), (1, 100_000, 70_000, 16, True), (1, 131_071, 70_000, 4, True),
+                                               (1, 131_072, 70_000, 4, False), (10, 100_001, 999, 4, True), (11, 100_000, 999, 4, True), (11, 100_001, 999, 4, False)])
+def test_one_launch_where_it_is_the_shorter_way(nt, n, rows, dim, one):
+    """Both sides of the rules on forward and sort in one launch: which kernels ran, and the bytes that come out.  (Every list of
+    up to 100 000 lookups went there; 2 x 100 000 lookups of 40 slots took 41 us instead of 36.)"""
+    rng = np.random.default_rng(n + rows)
+    slots = [torch.from_numpy((rng.random(n) ** 3 * rows).astype(np.int32)).cuda() for _ in range(nt)]
+    want = _step(1, slots, [None] * nt, n, [n] * nt, fused=True, rows=rows, dim=dim)[1]
+    hp, got = _step(0, slots, [None] * nt, n, [n] * nt, fused=True, rows=rows, dim=dim)
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    B.fae_timing_enable(hp.ctx, True)
+    hp.forward_presort(HotBatch(n, slots, [None] * nt, [n] * nt))
+    hp.sync()
+    assert _launches(hp)["fwd_sort"] == int(one)
