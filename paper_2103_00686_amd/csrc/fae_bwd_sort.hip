@@ -461,11 +461,11 @@ template <int MODE, int ITEMS> __global__ __launch_bounds__(SORT_THREADS, MODE =
 // ---------------------------------------------------------------------------------
 // 2b. tables of up to LSORT_MAX lookups: sorted inside LDS by a few workgroups per table (fae_lsort.h)
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(LSORT_THREADS, 8) void lds_sort_kernel(LsortArgs a)
+template <bool ANY> __global__ __launch_bounds__(LSORT_THREADS, 8) void lds_sort_kernel(LsortArgs a)
 {
     bwd_clear_flags(a.flags, a.n_flags, a.flag_slice, LSORT_THREADS);
     const int z = fae_find_table(a.blk_start, a.n_tables, blockIdx.x);
-    lds_sort_block(a.slots[z], a.offsets[z], a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z], blockIdx.x - a.blk_start[z],
+    lds_sort_block<ANY>(a.slots[z], a.offsets[z], a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z], blockIdx.x - a.blk_start[z],
                    a.blk_start[z + 1] - a.blk_start[z], a.part_slots[z], a.n_samples, a.keys_out + a.seg_start[z],
                    a.vals_out + a.seg_start[z], a.status);
 }
@@ -790,7 +790,10 @@ int32_t bwd_sort_stage(fae_ctx *ctx, hipStream_t st, const fae_tables *hot_table
         la.n_flags = a.n_flags;
         la.flag_slice = bwd_flag_slice(a.n_flags, nb);
         fae_ktimer kt(ctx, FAE_K_LDS_SORT, st);
-        FAE_LAUNCH(ctx, lds_sort_kernel, dim3(nb), dim3(LSORT_THREADS), 0, st, la);
+        if (ctx->opt_sort_order == 1)
+            FAE_LAUNCH(ctx, (lds_sort_kernel<true>), dim3(nb), dim3(LSORT_THREADS), 0, st, la);
+        else
+            FAE_LAUNCH(ctx, (lds_sort_kernel<false>), dim3(nb), dim3(LSORT_THREADS), 0, st, la);
         FAE_LAUNCH_CHECK(ctx);
     }
     *cur_out = cur;
@@ -859,12 +862,12 @@ struct FusedArgs {
 // registers only four rows fit (eight spill: 128 -> 151 us), and 16 rows in one workgroup move more.  Steps of 26 tables, one batch
 // over and over, 64 samples per copying wave, before (one workgroup, more LDS) / two with four rows / one with sixteen, us:
 // 16 384 samples, dim 128 128.1 / 132.7 / 130.1, 12 000 90.6 / 96.7 / 90.6, 50 001 452 / 420 / 411; dim 100, 16 384 105.9 / 111.4 / 107.1, 50 001 452 / 407 / 415, 4000 39.2 / 36.2 / 38.3.
-template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS, (LPR < FUSED_ALONE_LANES ? 8 : 4)) void fwd_sort_kernel(FusedArgs a)
+template <typename V, int LPR, bool ANY> __global__ __launch_bounds__(LSORT_THREADS, (LPR < FUSED_ALONE_LANES ? 8 : 4)) void fwd_sort_kernel(FusedArgs a)
 {
     bwd_clear_flags(a.flags, a.n_flags, a.flag_slice, LSORT_THREADS);
     if ((int)blockIdx.x < a.n_sort_blocks) {
         const int z = fae_find_table(a.sort_blk_start, a.n_tables, blockIdx.x);
-        lds_sort_block(a.slots[z], nullptr, a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z], blockIdx.x - a.sort_blk_start[z],
+        lds_sort_block<ANY>(a.slots[z], nullptr, a.seg_start[z + 1] - a.seg_start[z], a.n_hot[z], blockIdx.x - a.sort_blk_start[z],
                        a.sort_blk_start[z + 1] - a.sort_blk_start[z], a.part_slots[z], a.n_samples, a.keys_out + a.seg_start[z],
                        a.vals_out + a.seg_start[z], a.status);
     } else {
@@ -880,7 +883,10 @@ template <typename V, int LPR> __global__ __launch_bounds__(LSORT_THREADS, (LPR 
 
 template <int LPR> static void launch_fwd_sort(fae_ctx *ctx, const FusedArgs &a, int blocks)
 {
-    FAE_LAUNCH(ctx, (fwd_sort_kernel<float4, LPR>), dim3(blocks), dim3(LSORT_THREADS), 0, ctx->stream, a);
+    if (ctx->opt_sort_order == 1)
+        FAE_LAUNCH(ctx, (fwd_sort_kernel<float4, LPR, true>), dim3(blocks), dim3(LSORT_THREADS), 0, ctx->stream, a);
+    else
+        FAE_LAUNCH(ctx, (fwd_sort_kernel<float4, LPR, false>), dim3(blocks), dim3(LSORT_THREADS), 0, ctx->stream, a);
 }
 
 extern "C" int32_t fae_embbag_fwd_presort(fae_ctx *ctx, const fae_tables *hot_tables, const float *const *h_hotW,
