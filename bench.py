@@ -187,8 +187,8 @@ def run_workload(args, cfg_id, headline):
 
     # ---- a3 + a4: classify, remap, hot tables (procedural weights) -------------------
     _, dt, kt = timed(lambda: hp.build(H, n_hot, seed=w.seed))
-    stage("build", sum(w.rows), "rows", 2 * 4 * sum(w.rows) + 4 * sum(w.rows) + 4 * sum(n_hot) + 4 * D * sum(n_hot), dt, kt,
-          "counters read by the count and the scatter pass, remap and hot ids written, hot rows written (procedural "
+    stage("build", sum(w.rows), "rows", 4 * sum(w.rows) + 4 * sum(w.rows) + 4 * sum(n_hot) + 4 * D * sum(n_hot), dt, kt,
+          "counters read once, remap and hot ids written, hot rows written (procedural "
           "weights: nothing read, one 64-bit hash per element)")
     log(f"built hot tables in {dt*1e3:.2f} ms")
 

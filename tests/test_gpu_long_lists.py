@@ -293,3 +293,18 @@ def test_any_order_is_the_faster_one():
     s = np.random.default_rng(2).integers(0, 30_000, 8192)
     us, stable = _sort_us(s, None, 8192, 30_000, 1), _sort_us(s, None, 8192, 30_000)
     assert us < 0.9 * stable, f"{us:.1f} us, in batch order {stable:.1f}"
+
+
+@pytest.mark.parametrize("nt,n,rows,lds", [(1, 16_384, 40, 1), (1, 16_385, 65_535, 0), (1, 16_385, 65_536, 1), (1, 131_071, ROWS, 1), (1, 131_072, ROWS, 0),
+                                           (10, 100_001, 70_000, 1), (11, 100_000, 70_000, 1), (11, 100_001, 70_000, 0)])
+def test_lists_that_the_sort_takes_by_itself(nt, n, rows, lds):
+    """Both sides of the rules on the LDS sort in a launch of its own: which kernel ran, and the bytes that come out."""
+    rng = np.random.default_rng(n + rows)
+    slots = [torch.from_numpy((rng.random(n) ** 3 * rows).astype(np.int32)).cuda() for _ in range(nt)]
+    want = _step(1, slots, [None] * nt, n, [n] * nt, rows=rows)[1]
+    hp, got = _step(0, slots, [None] * nt, n, [n] * nt, rows=rows)
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    B.fae_timing_enable(hp.ctx, True)
+    hp.backward_sgd(HotBatch(n, slots, [None] * nt, [n] * nt), torch.zeros((n, nt, 4), device="cuda"), 0.05)
+    hp.sync()
+    assert _launches(hp)["lds_sort"] == lds and (_launches(hp)["sort_scatter"] == 0) == bool(lds)
