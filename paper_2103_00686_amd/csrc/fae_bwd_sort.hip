@@ -516,7 +516,7 @@ static bool lsort_fuses(int64_t samples, int64_t all, int64_t most_slots, int la
 // Beside more copies than there are compute units of rows of 32 lanes on (there a sorting workgroup has a unit to itself), or than twice as many of
 // rows of 16, no more than four a table: steps with up to sixteen / four, 26 x 8192, dim 128 90.8 / 88.2, dim 256 187 / 185; 26 x 10 000, dim 64
 // 59.8 / 59.2, dim 128 111 / 106; 13 x 10 200, dim 128 60.0 / 58.9; with fewer copies of 16 lanes 13 x 16 384 49 / 56, 20 x 12 000 55 / 57.
-// Longer ones: one sorting workgroup per compute unit over all tables (no more, where no copies run beside them: two that share one
+// Those split by rank: one sorting workgroup per compute unit over all tables (no more, where no copies run beside them: two that share one
 // end later; sort alone, 3 x 100 000 with 258 / 256 workgroups 37.5 / 28.4, 3 lists of 207 K with 272 / 256 35.7 / 32.8, 5 x 102 400 45 / 35), parts
 // of 512 to 5000 lookups (every part goes over its
 // table's whole list, so more of them cost more than shorter ones save; 5000 leaves room for the sample's error below
@@ -525,7 +525,7 @@ static bool lsort_fuses(int64_t samples, int64_t all, int64_t most_slots, int la
 // rate from all of them.  Steps, three batches' inputs in turn, two for three / one for two: 26 x 16 384, dim 64 73.9 /
 // 72.8 us, 12 000 60.5 / 59.3; 26 x 11 000, dim 16 34.5 / 35.1; 3 x 65 536, dim 8 36.4 / 37.9.  Where a sorting workgroup
 // has a compute unit to itself (see fwd_sort_kernel), no less than 3300: 13 x 16 384, dim 128, without / with 79.3 / 76.0.
-// part_slots[z]: slots of a part that is a range; blk_start: prefix of workgroups per table (tables not
+// part_slots[z]: slots of a part that is a range, 0 where parts are found by rank; blk_start: prefix of workgroups per table (tables not
 // sorted in LDS get none).  Returns the number of workgroups.
 static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fae_batch *hot_batch, const bool *in_lds,
                int n_lds, int32_t *blk_start, uint32_t *part_slots, int copy_lanes, int64_t copy_blocks)
@@ -537,15 +537,21 @@ static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fa
         want <<= 1;
     if (want > 4 && (copy_lanes >= FUSED_ALONE_LANES ? many : copy_lanes >= 16 && copy_blocks > 2LL * ctx->n_cu))
         want = 4;
+    // Lookups up to which a list is split into ranges of slots: finding the parts by rank takes 2.5 us more, and longer lists gain more from
+    // even parts, the more so the more skewed they are.  Steps, a bounded Zipf law of 0.9 / 1.2, us, ranges then by rank: dim 16 1 x 12 000 19.1,
+    // 20.3 / 21.6, 21.4; 8 x 12 000 23.2, 25.2 / 26.7, 25.7; 1 x 16 384 19.6, 20.8 / 23.2, 21.4; 8 x 16 384 25.2, 26.9 / 28.8, 27.0; sort alone 4 x 16 384
+    // 27.8, 28.9 / 30.6, 28.8, 26 x 16 384 49.5, 50.5 / 49.5, 48.0.  Rows of 16 lanes beside many copies, where the longest part ends last: 26 x 16 384,
+    // dim 64 (workload 3) 76.1, 73.1; 26 x 12 000 60.2, 58.9; of 32 lanes 26 x 16 384 139.1, 140.9 / 132.7, 133.6; 13 x 16 384 70.3, 71.1.
+    const int64_t ranges = copy_lanes >= FUSED_ALONE_LANES || ctx->opt_sort_order == 1 ? LSORT_SPLIT_MAX : many && copy_lanes >= 16 ? 10240 : 13312;
     int64_t long_lookups = 0;
     int nb = 0;
     for (int z = 0; z < nt; ++z) {
-        part_slots[z] = 1;
+        part_slots[z] = 0; // by rank
         blk_start[z] = 0;
         if (!in_lds[z])
             continue;
         const int64_t n = hot_batch->h_n_lookups[z];
-        if (n > LSORT_SPLIT_MAX) {
+        if (n > ranges) {
             long_lookups += n;
             continue;
         }
@@ -564,7 +570,7 @@ static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fa
         const auto parts_of = [&](int64_t per) {
             int64_t p = nb;
             for (int z = 0; z < nt; ++z)
-                if (in_lds[z] && hot_batch->h_n_lookups[z] > LSORT_SPLIT_MAX)
+                if (in_lds[z] && hot_batch->h_n_lookups[z] > ranges)
                     p += (hot_batch->h_n_lookups[z] + per - 1) / per;
             return p;
         };
@@ -574,7 +580,7 @@ static int lsort_plan(const fae_ctx *ctx, const fae_tables *hot_tables, const fa
     }
     nb = 0;
     for (int z = 0; z < nt; ++z) {
-        const int parts = !in_lds[z] ? 0 : hot_batch->h_n_lookups[z] > LSORT_SPLIT_MAX ? (int)((hot_batch->h_n_lookups[z] + share - 1) / share) : blk_start[z];
+        const int parts = !in_lds[z] ? 0 : hot_batch->h_n_lookups[z] > ranges ? (int)((hot_batch->h_n_lookups[z] + share - 1) / share) : blk_start[z];
         blk_start[z] = nb;
         nb += parts;
     }

@@ -10,7 +10,7 @@
 //      last slot where that is left out of the sort, see below), and adds up the lookups below its range;
 //   2. goes over the bits and takes the lookups of its range in batch order into LDS;
 //   3. sorts them there (LSD radix passes, or, where they are few, by counting the keys in front of each).
-// Lists of up to LSORT_CAP lookups are split into equal ranges of slots, those of up to LSORT_SPLIT_MAX too unless that
+// Lists of up to LSORT_CAP lookups are split into equal ranges of slots, those of up to 10 240 to LSORT_SPLIT_MAX (by lsort_plan) too unless that
 // would leave a part with far more than its share (lsort_uneven).  Others are split by the ranks of
 // a sample of 1024 lookups, one out of every 1024th of the list (lsort_bounds): to single slots where many lookups
 // crowd on few, so that popular slots next to each other (ids in order of popularity) end up in different parts.  A slot that
@@ -44,10 +44,7 @@
 #define LSORT_PARTS 16    // of a list that is split by ranges of slots, at most
 #define LSORT_UNEVEN 3072 // lookups beyond an even share that take a part longer than bounds by rank would (1.4 us per 1024 / 2.5 us), and what 64 samples may err by
 #define LSORT_PIECE 5000  // lookups of a piece of a part that does not fit
-// Lookups up to which ranges of slots split a list where they do so evenly: finding the parts by rank takes 2.5 us more, and longer
-// lists gain more from even parts.  Steps, us, by rank / by ranges: 1 x 12 000 20.9 / 18.9, 8 x 12 000 26.0 / 23.9, 1 x 16 384 21.2 / 19.7,
-// 26 x 16 384 43.4 / 42.4, sort alone 22 / 17.5; three quarters on one slot (uneven: the 64 samples that see it come on top): 1 x 16 384 24 / 27,
-// 26 x 16 384 41.9 / 41.6.
+// Lookups of the longest list that is split into ranges of slots (which lists are: lsort_plan)
 #define LSORT_SPLIT_MAX 16384
 #define LSORT_BITS 9 // of a digit, at most
 #define LSORT_DIGITS (1 << LSORT_BITS)
@@ -503,7 +500,7 @@ __device__ __forceinline__ void lsort_place(LsortLds &s, const int32_t *slots, c
 }
 
 // Part `part` of `parts` of a table's n lookups; part_slots: slots of a part of a list that is split
-// by ranges.  keys_out / vals_out: the table's segment of the sorted pairs.  ANY: the lookups of a slot may come in any order.
+// by ranges, 0 where it is split by rank.  keys_out / vals_out: the table's segment of the sorted pairs.  ANY: the lookups of a slot may come in any order.
 template <bool ANY>
 __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32_t *off, int n, int n_hot_z, int part, int parts, uint32_t part_slots,
                                                int n_samples, int32_t *keys_out, int32_t *vals_out, uint32_t *status)
@@ -511,15 +508,15 @@ __device__ __forceinline__ void lds_sort_block(const int32_t *slots, const int32
     __shared__ __align__(16) LsortLds s;
     const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / FAE_WAVE), lane = fae_lane();
     const uint32_t n_hot = (uint32_t)n_hot_z;
+    bool by_rank = part_slots == 0u;
     uint32_t lo = (uint32_t)part * part_slots; // the part's slots
     uint32_t hi = n_hot + 1u - lo < part_slots ? n_hot + 1u : lo + part_slots;
-    if (ANY && n <= LSORT_COUNTED && part_slots <= LSORT_COUNTED) {
+    if (ANY && !by_rank && n <= LSORT_COUNTED && part_slots <= LSORT_COUNTED) {
         lsort_place(s, slots, off, n, n_hot, lo, hi - lo, n_samples, keys_out, vals_out, status);
         return;
     }
     bool crowd = false; // the last of them is left out of the sort
     int share = 0, shares = 1;
-    bool by_rank = n > LSORT_SPLIT_MAX;
     if (n > LSORT_CAP && !by_rank)
         by_rank = lsort_uneven(slots, n, n_hot, part_slots, parts);
     if (by_rank) {

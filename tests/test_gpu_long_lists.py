@@ -308,3 +308,31 @@ def test_lists_that_the_sort_takes_by_itself(nt, n, rows, lds):
     hp.backward_sgd(HotBatch(n, slots, [None] * nt, [n] * nt), torch.zeros((n, nt, 4), device="cuda"), 0.05)
     hp.sync()
     assert _launches(hp)["lds_sort"] == lds and (_launches(hp)["sort_scatter"] == 0) == bool(lds)
+
+
+def _skewed_us(n, seed, nt=26, dim=64, rows=200_000):
+    """Kernel time of forward and sort in one launch over tables of a bounded Zipf law of 1.2 (the shortest of several)."""
+    rng = np.random.default_rng(seed)
+    ranks = np.minimum(((rows ** -0.2 - 1) * rng.random((nt, n)) + 1) ** -5.0, rows).astype(np.int64) - 1
+    hp = HotPath([rows] * nt, dim)
+    hp.alloc_counts()
+    hp.build([0] * nt, [rows] * nt, seed=3)
+    hb = HotBatch(n, [torch.from_numpy(((r + 3 * seed) * 7919 % rows).astype(np.int32)).cuda() for r in ranks], [None] * nt, [n] * nt)
+    out = torch.empty((n, nt, dim), device="cuda")
+    kernel = [B.fae_kernel_name(k) for k in range(B.FAE_K_COUNT)].index("fwd_sort")
+    times = []
+    for _ in range(12):
+        B.fae_timing_enable(hp.ctx, True)
+        B.fae_timing_reset(hp.ctx)
+        hp.forward_presort(hb, out)
+        hp.sync()
+        times.append(B.fae_timing_read(hp.ctx, kernel)[0] * 1e3)
+    return min(times)
+
+
+@pytest.mark.parametrize("seed", [1, 3])
+def test_skewed_lists_of_16_384(seed):
+    """No slower than lists that are a little longer (28 and 31 us; split into ranges of slots 38 to 41, as one of four ranges had a
+    popular slot and much else)."""
+    us, longer = _skewed_us(16_384, seed), _skewed_us(16_600, seed)
+    assert us < 1.08 * longer, f"{us:.1f} us, 16 600 lookups {longer:.1f}"
