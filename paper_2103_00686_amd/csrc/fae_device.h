@@ -93,7 +93,7 @@ __device__ __forceinline__ void fwd_onehot_wave(const V *W, const int32_t *slots
     if (s0 >= s_end)
         return;
     int sreg = -1;
-    if (lane < SAMPLES && s0 + lane < s_end) {
+    if ((SAMPLES == FAE_WAVE || lane < SAMPLES) && s0 + lane < s_end) {
         sreg = slots[s0 + lane];
         if ((unsigned)sreg >= (unsigned)n_hot) {
             fae_flag(status, FAE_STATUS_ERANGE);
