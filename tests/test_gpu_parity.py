@@ -297,9 +297,9 @@ def test_backward_long_runs_and_many_tiles(dev, S_, sort_variant, reduce_variant
                                          (2, 16385, False)])
 def test_table_count_and_sort_tier_limits(dev, nt, S_, fused):
     """The largest number of tables (the table of a workgroup is looked up in two rounds over the
-    whole prefix of 65 entries), a count in between, and batches on either side of 16 384 lookups per
-    table, up to which the LDS sort takes every list and splits it into ranges of slots (beyond, by the
-    ranks of a sample); tables of very different sizes, one of them a single row."""
+    whole prefix of 65 entries), a count in between, and batches on either side of what the LDS
+    sort and the fused forward + sort launch take (16 384 lookups per table); tables of very
+    different sizes, one of them a single row."""
     rng = np.random.default_rng(nt * 100003 + S_)
     dim, lr = 8, 0.05
     n_hot = [int(x) for x in rng.integers(1, 3000, nt)]

@@ -76,8 +76,9 @@ def test_random_step(dev, case):
     g_np = [rng.standard_normal((S_, nt, dim)).astype(np.float32) for _ in range(n_steps)]
     gouts = [torch.from_numpy(g).to(dev) for g in g_np]
     outs = [torch.full((S_, nt, dim), 7.0, dtype=torch.float32, device=dev) for _ in range(n_steps)]
-    if mode == "fused" and not all(o is None for o in offs):
-        mode = "auto"                                    # forward and sort in one launch: tables of one lookup per sample
+    one_hot_fits = all(o is None for o in offs) and S_ <= 16384
+    if mode == "fused" and not one_hot_fits:
+        mode = "auto"                                    # the fused launch takes one-lookup tables of up to 16 384 samples
     steps, _ = hp.prepare_steps([hb] * n_steps, gouts, outs, lr, presort=mode)
     for k in range(n_steps):
         steps[k]()
